@@ -282,6 +282,16 @@ void build_tables(const pinv_encoding* e, const Dims& d, HostTables* h) {
   }
 }
 
+// The power of two that brings E's largest entry into [2^13, 2^14.5): every
+// phase factor has modulus 1, so |E| is the coil sensitivity.
+int e_shift(const HostTables& h) {
+  if (h.coil.empty()) return 13;
+  double mx = 0.0;
+  for (double v : h.coil) mx = std::max(mx, fabs(v));
+  if (!(mx > 0.0) || !isfinite(mx)) return 0;
+  return std::max(-100, std::min(100, 13 - ilogb(mx)));
+}
+
 // Bytes of the tables as type T in one device buffer (each table 256-aligned).
 template <typename T>
 size_t tables_bytes(const HostTables& h) {
@@ -418,8 +428,15 @@ void drain_frees(pinv_context* c, hipStream_t s, bool wait) {
 // Factorisation block size when the options leave it at 0.
 constexpr int kDefaultNb = 128;
 
+// FP32 plans from this many unknowns form W and R on f16 pieces, two of the
+// tile rows of pinv_half.hip; at N = 1024, M = 2048 W and R take 0.15 and 0.11 ms
+// against 0.20 and 0.20 on FP32 instructions, at N = 4096, M = 32768 8.5 and
+// 7.3 ms against 17.4 and 15.9.
+constexpr int kHalfMinN = 256;
+
 struct BuildForm {
   bool m3 = true;
+  bool half = false;   // W and R on f16 pieces (pinv_half.hip)
   int nb = kDefaultNb;
   int gram = PINV_GRAM_SHARED;
   bool r_fp64 = false;
@@ -450,6 +467,10 @@ size_t plan_footprint(const Dims& d, int prec, const BuildForm& f) {
     // a slab of conj(E) during the W product
     const size_t Np = sp_cols(N), Mp = sp_cols(M);
     b += 2 * 8 * N * Np + 8 * M * Np + 8 * N * Mp + 8 * Np * (size_t)e_slab_rows(N, M);
+  } else if (f.half) {
+    // W^T packed in rows of 32 columns, and R.  The packed factor takes the
+    // Gram workspace's place and the conj(E) slab R's.
+    b += 8 * M * half_cols(N) + cs * N * M;
   } else if (!f.no_r) {
     b += ws * N * M;            // W (and Z for the right pseudoinverse)
     if (right) b += ws * N * M;
@@ -761,6 +782,8 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
              : o->cprod == PINV_CPROD_4M ? false
                                          : o->prec != PINV_FP64 && !r_fp64;
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
+  form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
+               o->route == PINV_ROUTE_CHOLESKY && d->N >= kHalfMinN;
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);
@@ -888,8 +911,14 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     return PINV_OK;
   }
   const bool no_r = form.no_r;
-  const size_t foot = plan_footprint(d, o->prec, form);
-  if (!make_room(c, foot))
+  size_t foot = plan_footprint(d, o->prec, form);
+  bool room = make_room(c, foot);
+  if (!room && form.half) {   // FP32 tiles need no padding of W's rows
+    form.half = false;
+    foot = plan_footprint(d, o->prec, form);
+    room = make_room(c, foot);
+  }
+  if (!room)
     return fail(PINV_ERR_NOMEM, "plan footprint " + std::to_string(foot) +
                                     " B exceeds the free budget");
 
@@ -989,7 +1018,8 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     BCHK(workspace_alloc(&L64, 16 * Gd * Gd, c, s));
   }
   BCHK(hipMemsetAsync(L64, 0, 16 * Gd * Gd, s));
-  if (!no_r) BCHK(workspace_alloc(&W, b3 ? 8 * M * sp_cols(N) : ws * N * M, c, s));
+  if (!no_r)
+    BCHK(workspace_alloc(&W, b3 ? 8 * M * sp_cols(N) : form.half ? 8 * M * half_cols(N) : ws * N * M, c, s));
   int64_t slab = 0;
   if (b3 && !no_r && !p->right && form.route == PINV_ROUTE_CHOLESKY) {
     // split-packed L^-1 and L^-H rows and the conj(E) slab, mapped before the
@@ -1123,6 +1153,14 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     LHS = nullptr;
     BCHK(hipFreeAsync(LS, s));
     LS = nullptr;
+  } else if (form.half) {
+    // the packed factor in the Gram workspace (dead once factored; 12 N Np + 8 N
+    // bytes of its 16 N^2), conj(E) in R until R is formed
+    const int64_t Np = half_cols(N), fit = (int64_t)(N * M) / Np;
+    const int64_t slab = fit >= (int64_t)M ? (int64_t)M : fit / 128 * 128;
+    BCHK(launch_trmm_wh(p->e32, (const double*)L64, G, p->R, slab, e_shift(ht), W, s));
+    BCHK(hipEventRecord(p->ev[3], s));
+    BCHK(launch_trmm_rh((const double*)L64, G, W, (float*)p->R, d.N, d.M, s));
   } else {
     BCHK(launch_trmm_w<float>(p->e32, (const float*)p->Linv, (float*)W, m3, s));
     BCHK(hipEventRecord(p->ev[3], s));

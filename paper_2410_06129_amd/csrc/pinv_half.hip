@@ -1,0 +1,534 @@
+// FP32 products on the f16 matrix pipe: W = L^-1 E^H, R = L^-H W (Eq. 8) and
+// the many-frame apply image = R data (Eq. 3) of FP32 plans.
+//
+// v_mfma_f32_16x16x32_f16 multiplies sixteen times faster than
+// v_mfma_f32_16x16x4_f32, so each FP32 operand value is written as a sum of
+// f16 pieces, x = 2^-s (h + l [+ t]), each piece the rounding of what the ones
+// before it leave, and a real product is the sum of the pieces' products:
+//
+//   two pieces by two:    h h + h l + l h                (12 MFMAs per complex product)
+//   three pieces by two:  h h + h l + l h + t h          (16)
+//
+// accumulated in FP32.  s is a power of two per row and segment that puts the
+// row's largest value in [2^13, 2^14): two pieces then hold 23 bits of every
+// value within 2^-15 of the row's largest and 2^-39 of the largest below that,
+// three pieces ten bits more.  One instruction sums 32 products of a pair of
+// pieces before the FP32 accumulator rounds, against four on the FP32
+// instruction, and the dropped l l products (2^-24 relative, of random sign)
+// are smaller than what that saves.
+//
+// The factor takes three pieces, split straight from FP64: its rounding enters
+// W and R alike, adds up coherently in R data, and with FP32 values made most
+// of an FP32 plan's unrefined error.  E, W, R and the data are rounded
+// independently from one value to the next and take two.
+//
+// Packed layout.  A matrix of `rows` rows and k columns is stored in chunks of
+// 32 columns (zero past k): for each row and chunk 256 bytes, the planes re_h,
+// re_l, im_h, im_l of the 32 columns, 64 bytes each; a third piece is kept
+// beside it, 128 bytes per row and chunk (re_t, im_t).  A tile's chunk is
+// copied to LDS by the memory pipe itself (global_load_lds, 16 bytes a lane, no
+// registers and no store instructions).  The instruction writes a wave's 64
+// pieces side by side, so the order within a row is chosen on the global side:
+// the 16-byte piece j of tile row r comes to slot j ^ (r % 16), and the 16 rows
+// that a fragment read touches at one j then lie in distinct banks.
+#include <type_traits>
+
+#include "pinv_internal.h"
+
+namespace pinv {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void glb_void;
+
+__device__ __forceinline__ f32x4 mfma_f16(f16x8 a, f16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
+// h and l pieces of x0 and x1, each pair in a 32-bit word (x0 in the low half).
+__device__ __forceinline__ void split_h2(float x0, float x1, uint32_t& h, uint32_t& l) {
+  const f16x2 hv{(_Float16)x0, (_Float16)x1};
+  const f16x2 lv{(_Float16)(x0 - (float)hv[0]), (_Float16)(x1 - (float)hv[1])};
+  h = __builtin_bit_cast(uint32_t, hv);
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+
+// The power of two that brings a row whose largest |value| has the FP32 (FP64
+// high word's) exponent field `e` into [2^13, 2^14).  Rows of zeros keep 1;
+// rows that hold an infinity or a NaN stay non-finite at any scale.
+__device__ __forceinline__ int row_shift(int e, int bias) { return e == 0 ? 0 : 13 + bias - e; }
+
+// W^T is stored as 2^12 W: no entry of W exceeds 1 (W W^H = I - lam L^-1 L^-H).
+constexpr int kWShift = 12;
+
+// ---------------------------------------------------------------------------
+// Tiles
+// ---------------------------------------------------------------------------
+// WGM x WGN wavefronts, each WTM x WTN of a BM x BN tile; PA pieces in operand
+// A (rows), two in B (columns).  Two LDS stages: the next chunk is copied in
+// while this one computes, one barrier per chunk.
+template <int BM_, int BN_, int WGM_, int WGN_, int PA_> struct HalfCfg {
+  static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, PA = PA_;
+  static constexpr int NW = WGM * WGN, NT = 64 * NW;
+  static constexpr int WTM = BM / WGM, WTN = BN / WGN, MB = WTM / 16, NB = WTN / 16;
+  static constexpr int A_BYTES = BM * 256, T_BYTES = PA == 3 ? BM * 128 : 0, B_BYTES = BN * 256;
+  static constexpr int STAGE = A_BYTES + T_BYTES + B_BYTES;
+  static_assert(A_BYTES % (1024 * NW) == 0 && T_BYTES % (1024 * NW) == 0 &&
+                    B_BYTES % (1024 * NW) == 0 && (4 * NW) % 16 == 0,
+                "whole wave-wide copies, their row mod 16 the same in every pass");
+};
+
+// Rows row0 .. of a packed matrix: `main` (256 bytes per row and chunk) and,
+// with a third piece, `third` (128).  nc: chunks per row.  Rows past `last`
+// are read as row `last` (their products are not stored).
+struct HalfOperand {
+  const char* main;
+  const char* third;
+  int nc, row0, last;
+};
+
+template <class C> struct HalfAcc { f32x4 re[C::MB][C::NB], im[C::MB][C::NB]; };
+
+template <class C> struct HalfLoader {
+  static constexpr int IA = C::A_BYTES / 1024 / C::NW, IT = C::T_BYTES / 1024 / C::NW,
+                       IB = C::B_BYTES / 1024 / C::NW;
+  const char *a, *t, *b;
+  uint32_t oa[IA], ot[IT ? IT : 1], ob[IB];
+  int w;
+  __device__ __forceinline__ void init(const HalfOperand& A, const HalfOperand& B) {
+    const int lane = threadIdx.x & 63;
+    w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    a = A.main + (size_t)A.row0 * A.nc * 256;
+    b = B.main + (size_t)B.row0 * B.nc * 256;
+    t = C::PA == 3 ? A.third + (size_t)A.row0 * A.nc * 128 : nullptr;
+    const int r4 = 4 * w + (lane >> 4);       // four rows of 16 pieces per copy
+    const uint32_t j4 = ((lane & 15) ^ (r4 & 15)) * 16;
+#pragma unroll
+    for (int i = 0; i < IA; ++i)
+      oa[i] = (uint32_t)min(r4 + 4 * C::NW * i, A.last - A.row0) * (uint32_t)A.nc * 256u + j4;
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+      ob[i] = (uint32_t)min(r4 + 4 * C::NW * i, B.last - B.row0) * (uint32_t)B.nc * 256u + j4;
+    if constexpr (C::PA == 3) {
+      const int r8 = 8 * w + (lane >> 3);     // eight rows of 8 pieces
+      const uint32_t j8 = ((lane & 7) ^ (r8 & 7)) * 16;
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+        ot[i] = (uint32_t)min(r8 + 8 * C::NW * i, A.last - A.row0) * (uint32_t)A.nc * 128u + j8;
+    }
+  }
+  __device__ __forceinline__ void load(char* s, int c) const {
+    const char* pa = a + (size_t)c * 256;
+    const char* pb = b + (size_t)c * 256;
+#pragma unroll
+    for (int i = 0; i < IA; ++i)
+      __builtin_amdgcn_global_load_lds((glb_void*)(pa + oa[i]),
+                                       (lds_void*)(s + (w + i * C::NW) * 1024), 16, 0, 0);
+    if constexpr (C::PA == 3) {
+      const char* pt = t + (size_t)c * 128;
+#pragma unroll
+      for (int i = 0; i < IT; ++i)
+        __builtin_amdgcn_global_load_lds((glb_void*)(pt + ot[i]),
+                                         (lds_void*)(s + C::A_BYTES + (w + i * C::NW) * 1024), 16, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < IB; ++i)
+      __builtin_amdgcn_global_load_lds(
+          (glb_void*)(pb + ob[i]),
+          (lds_void*)(s + C::A_BYTES + C::T_BYTES + (w + i * C::NW) * 1024), 16, 0, 0);
+  }
+};
+
+// One chunk from the stage `s`: lane l holds row l % 16 (of a block of A or B)
+// and columns 8 (l / 16) .. + 8.
+template <class C>
+__device__ __forceinline__ void half_compute(const char* s, HalfAcc<C>& acc) {
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const char* sa = s + (w / C::WGN) * C::WTM * 256 + lr * 256;
+  const char* st = s + C::A_BYTES + (w / C::WGN) * C::WTM * 128 + lr * 128;
+  const char* sb = s + C::A_BYTES + C::T_BYTES + (w % C::WGN) * C::WTN * 256 + lr * 256;
+  f16x8 b[C::NB][4];
+#pragma unroll
+  for (int j = 0; j < C::NB; ++j)
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      b[j][p] = *reinterpret_cast<const f16x8*>(sb + j * 4096 + ((p * 4 + lk) ^ lr) * 16);
+#pragma unroll
+  for (int i = 0; i < C::MB; ++i) {
+    f16x8 a[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      a[p] = *reinterpret_cast<const f16x8*>(sa + i * 4096 + ((p * 4 + lk) ^ lr) * 16);
+    const f16x8 nh = -a[2], nl = -a[3];
+    if constexpr (C::PA == 3) {
+      const f16x8 rt = *reinterpret_cast<const f16x8*>(st + i * 2048 + (lk ^ (lr & 7)) * 16);
+      const f16x8 it = *reinterpret_cast<const f16x8*>(st + i * 2048 + ((4 + lk) ^ (lr & 7)) * 16);
+      const f16x8 nt = -it;
+#pragma unroll
+      for (int j = 0; j < C::NB; ++j) {
+        acc.re[i][j] = mfma_f16(rt, b[j][0], acc.re[i][j]);
+        acc.im[i][j] = mfma_f16(rt, b[j][2], acc.im[i][j]);
+        acc.re[i][j] = mfma_f16(nt, b[j][2], acc.re[i][j]);
+        acc.im[i][j] = mfma_f16(it, b[j][0], acc.im[i][j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < C::NB; ++j) {
+      f32x4 re = acc.re[i][j], im = acc.im[i][j];
+      re = mfma_f16(a[1], b[j][0], re);
+      im = mfma_f16(a[1], b[j][2], im);
+      re = mfma_f16(nl, b[j][2], re);
+      im = mfma_f16(a[3], b[j][0], im);
+      re = mfma_f16(a[0], b[j][1], re);
+      im = mfma_f16(a[0], b[j][3], im);
+      re = mfma_f16(nh, b[j][3], re);
+      im = mfma_f16(a[2], b[j][1], im);
+      re = mfma_f16(a[0], b[j][0], re);
+      im = mfma_f16(a[0], b[j][2], im);
+      re = mfma_f16(nh, b[j][2], re);
+      im = mfma_f16(a[2], b[j][0], im);
+      acc.re[i][j] = re;
+      acc.im[i][j] = im;
+    }
+  }
+}
+
+// The copies into `nxt` run under the products from `cur`.  The two are
+// different stages; `__restrict__` lets the compiler order no read of one
+// behind the copies into the other.
+template <class C>
+__device__ __forceinline__ void half_step(const HalfLoader<C>& ld, char* __restrict__ nxt, int c,
+                                          const char* __restrict__ cur, HalfAcc<C>& acc) {
+  ld.load(nxt, c);
+  __builtin_amdgcn_sched_barrier(0);   // the copies first
+  half_compute<C>(cur, acc);
+}
+
+// vmcnt(0): this wave's copies into LDS have landed; the barrier publishes
+// them and retires every wave's reads of the stage the next copies overwrite.
+__device__ __forceinline__ void half_publish() {
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  __syncthreads();
+}
+
+// acc = sum over chunks c0 .. c1 - 1 (at least one), from the top with DOWN.
+template <class C, bool DOWN>
+__device__ __forceinline__ void half_mainloop(const HalfOperand& A, const HalfOperand& B, int c0,
+                                              int c1, char* s0, char* s1, HalfAcc<C>& acc) {
+#pragma unroll
+  for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+    for (int j = 0; j < C::NB; ++j) acc.re[i][j] = acc.im[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  HalfLoader<C> ld;
+  ld.init(A, B);
+  const int n = c1 - c0;
+  auto at = [&](int k) { return DOWN ? c1 - 1 - min(k, n - 1) : c0 + min(k, n - 1); };
+  ld.load(s0, at(0));
+  half_publish();
+  int k = 0;
+  for (; k + 2 <= n; k += 2) {
+    half_step<C>(ld, s1, at(k + 1), s0, acc);
+    half_publish();
+    half_step<C>(ld, s0, at(k + 2), s1, acc);   // the last pass copies a chunk it does not use
+    half_publish();
+  }
+  if (k < n) half_compute<C>(s0, acc);
+}
+
+// ---------------------------------------------------------------------------
+// The factor: row and column scales, and L^-1 and L^-H in three pieces
+// ---------------------------------------------------------------------------
+// row_e[n], col_e[n]: the largest exponent field of row and column n of the
+// lower triangle (zeroed before).  One workgroup per 64 x 64 block.
+__global__ __launch_bounds__(256) void k_factor_exps(const double* __restrict__ Li, int N,
+                                                     int* __restrict__ row_e, int* __restrict__ col_e) {
+  int bi, bj;
+  tri_index(blockIdx.x, &bi, &bj);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const cx<double>* L = reinterpret_cast<const cx<double>*>(Li);
+  __shared__ int cmax[4][64];
+  const int col = bj * 64 + lane;
+  int cm = 0;
+#pragma unroll 4
+  for (int q = 0; q < 16; ++q) {
+    const int row = bi * 64 + w * 16 + q;
+    int e = 0;
+    if (row < N && col < N) {
+      const cx<double> v = L[(size_t)row * N + col];
+      const int hr = __double2hiint(v.re) & 0x7fffffff, hi = __double2hiint(v.im) & 0x7fffffff;
+      e = max(hr, hi) >> 20;
+    }
+    cm = max(cm, e);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
+    if (lane == 0 && row < N) atomicMax(row_e + row, e);
+  }
+  cmax[w][lane] = cm;
+  __syncthreads();
+  if (w == 0 && col < N)
+    atomicMax(col_e + col, max(max(cmax[0][lane], cmax[1][lane]), max(cmax[2][lane], cmax[3][lane])));
+}
+
+// Packed rows of L^-1 (TRANS false: row n, k = n' <= n) or L^-H (TRANS: row i,
+// value conj(Li[k][i]), k >= i), 8 columns per thread.  Only the chunks that
+// the products read are written: k up to, or from, the row's block of 128.
+template <bool TRANS>
+__global__ __launch_bounds__(256) void k_factor_pack(const double* __restrict__ Li, int N, int nc,
+                                                     const int* __restrict__ e_max,
+                                                     char* __restrict__ main, char* __restrict__ third) {
+  const cx<double>* L = reinterpret_cast<const cx<double>*>(Li);
+  const int64_t total = (int64_t)N * nc * 4;
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < total;
+       u += (int64_t)gridDim.x * blockDim.x) {
+    int r, g;   // row, 8-group: neighbours take one row's groups, or one group's rows
+    if constexpr (TRANS) {
+      g = (int)(u / N);
+      r = (int)(u - (int64_t)g * N);
+    } else {
+      r = (int)(u / (nc * 4));
+      g = (int)(u - (int64_t)r * (nc * 4));
+    }
+    const int blk = r / 128 * 128;
+    if (TRANS ? 8 * g < blk : 8 * g >= blk + 128) continue;
+    const int s = row_shift(e_max[r], 1023);
+    f16x8 p[6];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = 8 * g + j;
+      cx<double> v{0.0, 0.0};
+      if (k < N) v = TRANS ? L[(size_t)k * N + r] : L[(size_t)r * N + k];
+      const double x[2] = {ldexp(v.re, s), ldexp(TRANS ? -v.im : v.im, s)};
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const _Float16 h = (_Float16)x[c];
+        const double r1 = x[c] - (double)h;
+        const _Float16 l = (_Float16)r1;
+        p[2 * c][j] = h;
+        p[2 * c + 1][j] = l;
+        p[4 + c][j] = (_Float16)(r1 - (double)l);
+      }
+    }
+    char* m = main + ((size_t)r * nc + g / 4) * 256 + (g % 4) * 16;
+    char* t = third + ((size_t)r * nc + g / 4) * 128 + (g % 4) * 16;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<f16x8*>(m + q * 64) = p[q];
+    *reinterpret_cast<f16x8*>(t) = p[4];
+    *reinterpret_cast<f16x8*>(t + 64) = p[5];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// conj(E), packed: rows m0 .. m0 + rows of samples, columns n, scaled by 2^es
+// ---------------------------------------------------------------------------
+// Workgroup b takes 64 rows and kGenChunksH chunks; thread t generates columns
+// 8 (t / 64) .. + 8 of row t % 64 of each chunk.
+constexpr int kGenChunksH = 16;
+struct GenHCfg { static constexpr int NT = 256, BK = 32; };
+
+template <int FEAT, bool AL>
+__global__ __launch_bounds__(256) void k_gen_e_h(EncDev<float> e, int m0, int rows, int nc, float scale,
+                                                 char* __restrict__ Es) {
+  const int nbc = (nc + kGenChunksH - 1) / kGenChunksH;
+  const int r0 = (int)(blockIdx.x / nbc) * 64, cb = (int)(blockIdx.x % nbc);
+  LoadGenRowSP<GenHCfg, 64, true, FEAT, AL> g;
+  g.init(e, m0 + r0);
+  const int o = threadIdx.x % 64, gq = (int)(threadIdx.x / 64);
+  const bool live = r0 + o < rows;
+  for (int c = 0; c < kGenChunksH; ++c) {
+    const int ck = cb * kGenChunksH + c;
+    if (ck >= nc) break;
+    g.fetch(ck * 32, e.N);
+    uint32_t pk[4][4];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      float re[2], im[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const cx<float> el = gen_product<FEAT>(g.raw[j + u]);
+        re[u] = g.ok[j + u] ? el.re * scale : 0.f;
+        im[u] = g.ok[j + u] ? -el.im * scale : 0.f;
+      }
+      split_h2(re[0], re[1], pk[0][j / 2], pk[1][j / 2]);
+      split_h2(im[0], im[1], pk[2][j / 2], pk[3][j / 2]);
+    }
+    if (live) {
+      char* d = Es + ((size_t)(r0 + o) * nc + ck) * 256 + gq * 16;
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        *reinterpret_cast<uint4*>(d + p * 64) = uint4{pk[p][0], pk[p][1], pk[p][2], pk[p][3]};
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// W^T (packed, rows m, k = n) and R
+// ---------------------------------------------------------------------------
+// Bound by the f16 pipe's power budget: at N = 9216, M = 131072 the two products
+// take 141 and 133 ms, R at 1340 TFLOP/s of executed f16 products, what a plain
+// bf16 library product of 16384^3 reaches on the same card (1330); three real
+// FP32 products per complex one took 329 and 313 ms.  128 x 128 tiles over eight
+// wavefronts fill the 160 KB of LDS with two stages of 80 KB; the LDS moves
+// 344 KB a chunk (2700 cycles) against 4096 cycles of matrix products.
+typedef HalfCfg<128, 128, 2, 4, 3> TrmmH;
+
+__global__ __launch_bounds__(TrmmH::NT, 1) void k_trmm_wh(const char* __restrict__ Lm,
+                                                          const char* __restrict__ Lt,
+                                                          const int* __restrict__ row_e, int es,
+                                                          const char* __restrict__ Es,
+                                                          char* __restrict__ Wt, int N, int nc, int m0,
+                                                          int rows) {
+  typedef TrmmH C;
+  __shared__ __attribute__((aligned(1024))) char s0[C::STAGE];
+  __shared__ __attribute__((aligned(1024))) char s1[C::STAGE];
+  const int nbi = (N + C::BM - 1) / C::BM, nbj = (rows + C::BN - 1) / C::BN;
+  int r, bj;
+  grouped_tile<8>(xcd_contiguous(blockIdx.x, nbi * nbj), nbi, nbj, &r, &bj);
+  const int bi = nbi - 1 - r;   // longest ranges first
+  HalfAcc<C> acc;
+  half_mainloop<C, false>(HalfOperand{Lm, Lt, nc, bi * C::BM, N - 1},
+                          HalfOperand{Es, nullptr, nc, bj * C::BN, rows - 1}, 0,
+                          min(nc, (bi + 1) * (C::BM / 32)), s0, s1, acc);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / C::WGN, wc = w % C::WGN;
+#pragma unroll
+  for (int i = 0; i < C::MB; ++i) {
+    const int n = bi * C::BM + wr * C::WTM + i * 16 + 4 * (lane >> 4);   // four rows n .. n + 3
+    if (n >= nc * 32) continue;
+    int sh[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      sh[q] = n + q < N ? kWShift - es - row_shift(row_e[n + q], 1023) : 0;
+#pragma unroll
+    for (int j = 0; j < C::NB; ++j) {
+      const int m = bj * C::BN + wc * C::WTN + j * 16 + (lane & 15);
+      if (m >= rows) continue;
+      float re[4], im[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {   // k past N is zero
+        re[q] = n + q < N ? ldexpf(acc.re[i][j][q], sh[q]) : 0.f;
+        im[q] = n + q < N ? ldexpf(acc.im[i][j][q], sh[q]) : 0.f;
+      }
+      uint2 o[4];
+      split_h2(re[0], re[1], o[0].x, o[1].x);
+      split_h2(re[2], re[3], o[0].y, o[1].y);
+      split_h2(im[0], im[1], o[2].x, o[3].x);
+      split_h2(im[2], im[3], o[2].y, o[3].y);
+      char* d = Wt + ((size_t)(m0 + m) * nc + n / 32) * 256 + (n % 32) * 2;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) *reinterpret_cast<uint2*>(d + p * 64) = o[p];
+    }
+  }
+}
+
+__global__ __launch_bounds__(TrmmH::NT, 1) void k_trmm_rh(const char* __restrict__ Hm,
+                                                          const char* __restrict__ Ht,
+                                                          const int* __restrict__ col_e,
+                                                          const char* __restrict__ Wt,
+                                                          float* __restrict__ R, int N, int M, int nc) {
+  typedef TrmmH C;
+  __shared__ __attribute__((aligned(1024))) char s0[C::STAGE];
+  __shared__ __attribute__((aligned(1024))) char s1[C::STAGE];
+  const int nbi = (N + C::BM - 1) / C::BM, nbj = (M + C::BN - 1) / C::BN;
+  int bi, bj;
+  grouped_tile<8>(xcd_contiguous(blockIdx.x, nbi * nbj), nbi, nbj, &bi, &bj);
+  HalfAcc<C> acc;
+  half_mainloop<C, true>(HalfOperand{Hm, Ht, nc, bi * C::BM, N - 1},
+                         HalfOperand{Wt, nullptr, nc, bj * C::BN, M - 1}, bi * (C::BM / 32), nc, s0,
+                         s1, acc);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / C::WGN, wc = w % C::WGN;
+  cx<float>* O = reinterpret_cast<cx<float>*>(R);
+#pragma unroll
+  for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = bi * C::BM + wr * C::WTM + i * 16 + 4 * (lane >> 4) + q;
+      if (n >= N) continue;
+      const int sh = -kWShift - row_shift(col_e[n], 1023);
+#pragma unroll
+      for (int j = 0; j < C::NB; ++j) {
+        const int m = bj * C::BN + wc * C::WTN + j * 16 + (lane & 15);
+        if (m < M)
+          O[(size_t)n * M + m] = cx<float>{ldexpf(acc.re[i][j][q], sh), ldexpf(acc.im[i][j][q], sh)};
+      }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// launchers
+// ---------------------------------------------------------------------------
+static int grid_1d(int64_t n, int most) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, most));
+}
+
+size_t half_factor_bytes(int64_t N) {
+  return (size_t)(N * (half_cols(N) / 32) * 384 + ((2 * N * 4 + 255) & ~int64_t(255)));
+}
+
+static hipError_t pack_factor(const double* Li, int N, bool trans, const int* e, char* main,
+                              char* third, hipStream_t s) {
+  const int nc = (int)(half_cols(N) / 32);
+  const int grid = grid_1d((int64_t)N * nc * 4, 16384);
+  if (trans)
+    hipLaunchKernelGGL(k_factor_pack<true>, dim3(grid), dim3(256), 0, s, Li, N, nc, e, main, third);
+  else
+    hipLaunchKernelGGL(k_factor_pack<false>, dim3(grid), dim3(256), 0, s, Li, N, nc, e, main, third);
+  return hipGetLastError();
+}
+
+hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor, void* Es,
+                          int64_t slab_rows, int es, void* Wt, hipStream_t s) {
+  const int N = e.N, M = e.M;
+  if (N <= 0 || M <= 0) return hipSuccess;
+  if (slab_rows <= 0) return hipErrorInvalidValue;
+  const int nc = (int)(half_cols(N) / 32);
+  char* main = (char*)factor;
+  char* third = main + (size_t)N * nc * 256;
+  int* row_e = (int*)(third + (size_t)N * nc * 128);
+  hipError_t err = hipMemsetAsync(row_e, 0, 2 * (size_t)N * 4, s);
+  if (err != hipSuccess) return err;
+  const int nb = cdiv(N, 64);
+  hipLaunchKernelGGL(k_factor_exps, dim3((unsigned)((int64_t)nb * (nb + 1) / 2)), dim3(256), 0, s, Li,
+                     N, row_e, row_e + N);
+  if ((err = hipGetLastError()) != hipSuccess) return err;
+  if ((err = pack_factor(Li, N, false, row_e, main, third, s)) != hipSuccess) return err;
+  const int nbc = cdiv(nc, kGenChunksH);
+  const float scale = ldexpf(1.f, es);
+  for (int64_t m0 = 0; m0 < M; m0 += slab_rows) {
+    const int rows = (int)std::min<int64_t>(slab_rows, M - m0);
+    err = with_feat_al(enc_features(e), row_aligned(e, 32), [&](auto fc, auto al) {
+      hipLaunchKernelGGL((k_gen_e_h<decltype(fc)::value, decltype(al)::value>),
+                         dim3((unsigned)(cdiv(rows, 64) * nbc)), dim3(256), 0, s, e, (int)m0, rows, nc,
+                         scale, (char*)Es);
+      return hipGetLastError();
+    });
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(k_trmm_wh, dim3((unsigned)(cdiv(N, TrmmH::BM) * cdiv(rows, TrmmH::BN))),
+                       dim3(TrmmH::NT), 0, s, (const char*)main, (const char*)third,
+                       (const int*)row_e, es, (const char*)Es, (char*)Wt, N, nc, (int)m0, rows);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_trmm_rh(const double* Li, void* factor, const void* Wt, float* R, int N, int M,
+                          hipStream_t s) {
+  if (N <= 0 || M <= 0) return hipSuccess;
+  const int nc = (int)(half_cols(N) / 32);
+  char* main = (char*)factor;
+  char* third = main + (size_t)N * nc * 256;
+  const int* col_e = (const int*)(third + (size_t)N * nc * 128) + N;
+  hipError_t err = pack_factor(Li, N, true, col_e, main, third, s);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(k_trmm_rh, dim3((unsigned)(cdiv(N, TrmmH::BM) * cdiv(M, TrmmH::BN))),
+                     dim3(TrmmH::NT), 0, s, (const char*)main, (const char*)third, col_e,
+                     (const char*)Wt, R, N, M, nc);
+  return hipGetLastError();
+}
+
+}  // namespace pinv

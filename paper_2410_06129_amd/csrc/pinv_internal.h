@@ -205,6 +205,19 @@ size_t apply_scratch_bytes_b3(int F, int N, int Mp);
 // At most kRowApplyMaxF frames of complex64 data against an SP R.
 hipError_t launch_apply_rows_sp(const void* R, const float* D, float* X, int N, int M, int F,
                                 Scratch& sc, hipStream_t s);
+// FP32 products on f16 pieces (pinv_half.hip).  Packed matrices have rows of
+// half_cols(k) columns, 8 bytes each (12 with the factor's third piece).
+inline int64_t half_cols(int64_t k) { return (k + 31) / 32 * 32; }
+// Workspace of the packed factor (L^-1 for W, then L^-H for R) and its scales.
+size_t half_factor_bytes(int64_t N);
+// W^T (packed, M rows, k = n) from the FP64 L^-1: conj(E) is written to Es,
+// slab_rows samples at a time (8 slab_rows half_cols(N) bytes), scaled by 2^es
+// so that no entry reaches 2^14.  Then R (complex64) from W^T and the same L^-1;
+// `factor` carries the column scales from one call to the other.
+hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor, void* Es,
+                          int64_t slab_rows, int es, void* Wt, hipStream_t s);
+hipError_t launch_trmm_rh(const double* Li, void* factor, const void* Wt, float* R, int N, int M,
+                          hipStream_t s);
 hipError_t launch_to_f32(const double* in, float* out, size_t n_complex, hipStream_t s);
 hipError_t launch_to_f64(const float* in, double* out, size_t n_complex, hipStream_t s);
 template <typename T> hipError_t launch_srf_diag(const EncDev<T>& e, const T* R, T* out, hipStream_t s);

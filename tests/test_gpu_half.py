@@ -1,0 +1,84 @@
+"""FP32 products on f16 pieces: R against the oracle, beside the same plan on
+FP32 matrix instructions.
+
+Shapes sit at the edges of the 128 x 128 tiles and 32-column chunks: N = 256
+(the smallest that takes this path), 289 and 340 (ragged), 384 (whole tiles);
+M below, at and past a tile, with one sample slab and with several coils, a
+voxel mask, species and an off-resonance map.
+
+Tolerance: a value is held within 2^-24 relative (rms) in two f16 pieces and
+within 2^-25 in FP32, and both accumulate in FP32, so R may be at most twice as
+far from the oracle as the FP32 instructions leave it (the factor's three
+pieces and the longer sums between roundings make it better in general).
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2410_06129_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = {
+    "n256": dict(seed=301, nx=16, ny=16, C=1, K=256, F=3),
+    "n289_odd": dict(seed=302, nx=17, ny=17, C=3, K=391, F=3),
+    "n384_whole": dict(seed=303, nx=32, ny=12, C=2, K=512, F=3),
+    "n340_b0": dict(seed=304, nx=10, ny=17, C=2, K=450, F=3, species=[0.0, 170.0], b0=True),
+}
+
+
+@pytest.fixture(scope="module")
+def P():
+    from paper_2410_06129_amd import pinv
+    return pinv
+
+
+@pytest.fixture(scope="module")
+def ctx(P):
+    c = P.pinv_context_create(0)
+    yield c
+    P.pinv_context_destroy(c)
+
+
+def get_r(P, ctx, enc, **kw):
+    plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED, **kw)
+    P.pinv_plan_wait(plan)
+    R = torch.full((enc.N, enc.M), float("nan"), dtype=torch.complex64, device="cuda")
+    P.pinv_plan_copy_buffer(plan, P.BUF_R, R)
+    torch.cuda.synchronize()
+    P.pinv_plan_release(plan)
+    return R.cpu().numpy().astype(np.complex128)
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("name", list(SHAPES) + ["n289_mask"])
+def test_r_matches_oracle(P, ctx, name):
+    w = synth.small_case(**SHAPES["n289_odd" if name == "n289_mask" else name])
+    enc = w.enc
+    if name == "n289_mask":   # 273 of a 20 x 19 grid's voxels
+        base = synth.small_case(seed=305, nx=20, ny=19, C=3, K=391, F=3).enc
+        enc = dataclasses.replace(base, voxels=synth.circular_mask(20, 19, 0.96))
+        assert enc.N >= 256 and enc.N % 32 != 0
+    ref = oracle.Build(enc, rel=1e-2).recon_matrix()
+    e_half, e_fp32 = rel(get_r(P, ctx, enc), ref), rel(get_r(P, ctx, enc, cprod=P.CPROD_4M), ref)
+    print(f"{name}: N={enc.N} M={enc.M} f16 pieces {e_half:.2e}, FP32 {e_fp32:.2e}")
+    assert e_half <= 2.0 * e_fp32
+
+
+@pytest.mark.parametrize("amp", [1e-15, 1e15])
+def test_r_scales_with_the_coils(P, ctx, amp):
+    """Sensitivities far from 1: every power of two is carried beside the
+    pieces, so R only scales by 1 / amp (amp rounded to a power of two)."""
+    enc = synth.small_case(**SHAPES["n289_odd"]).enc
+    a = 2.0 ** round(np.log2(amp))
+    r1 = get_r(P, ctx, enc)
+    ra = get_r(P, ctx, dataclasses.replace(enc, coil=enc.coil * a))
+    assert np.all(np.isfinite(ra))
+    assert rel(ra * a, r1) < 1e-12
