@@ -431,7 +431,8 @@ constexpr int kDefaultNb = 128;
 // FP32 plans from this many unknowns form W and R on f16 pieces, two of the
 // tile rows of pinv_half.hip; at N = 1024, M = 2048 W and R take 0.15 and 0.11 ms
 // against 0.20 and 0.20 on FP32 instructions, at N = 4096, M = 32768 8.5 and
-// 7.3 ms against 17.4 and 15.9.
+// 7.3 ms against 17.4 and 15.9.  Not with an FP32 Gram over all rows: its error may
+// exceed the shift, and W's entries then need not stay below 1.
 constexpr int kHalfMinN = 256;
 
 struct BuildForm {
@@ -783,7 +784,7 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
                                          : o->prec != PINV_FP64 && !r_fp64;
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
   form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
-               o->route == PINV_ROUTE_CHOLESKY && d->N >= kHalfMinN;
+               o->route == PINV_ROUTE_CHOLESKY && d->N >= kHalfMinN && gram != PINV_GRAM_FULL;
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);

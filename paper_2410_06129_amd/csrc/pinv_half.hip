@@ -1,5 +1,5 @@
-// FP32 products on the f16 matrix pipe: W = L^-1 E^H, R = L^-H W (Eq. 8) and
-// the many-frame apply image = R data (Eq. 3) of FP32 plans.
+// FP32 products on the f16 matrix pipe: W = L^-1 E^H, R = L^-H W (Eq. 8) of
+// FP32 plans.
 //
 // v_mfma_f32_16x16x32_f16 multiplies sixteen times faster than
 // v_mfma_f32_16x16x4_f32, so each FP32 operand value is written as a sum of
@@ -142,7 +142,18 @@ template <class C> struct HalfLoader {
 
 // One chunk from the stage `s`: lane l holds row l % 16 (of a block of A or B)
 // and columns 8 (l / 16) .. + 8.
-template <class C>
+//
+// The chunk's products are summed from zero and then added to the tile's
+// accumulators, so the sums between FP32 roundings of the whole are 32 columns
+// long.  The instruction aligns the products of a group of eight to the largest
+// and cuts what falls below towards minus infinity when they meet a larger sum:
+// a bias of one sign in every element, which adds up coherently over the samples
+// of an apply (one 64 x 64 coil, M = 8192: unrefined images 2.1e-3 off, after one
+// refinement step 1.0e-6; FP32 instructions 1.75e-3 and 3.8e-8).  So every second chunk of operand A is stored negated, and
+// its sums are subtracted (SUB): the bias of one chunk cancels the next one's
+// (5.9e-4 and 3.8e-8), at the same speed.  Sums kept apart by their sign instead,
+// ar br - ai bi, cost 12% of the products' time and left 7.6e-8.
+template <class C, bool SUB>
 __device__ __forceinline__ void half_compute(const char* s, HalfAcc<C>& acc) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -163,35 +174,45 @@ __device__ __forceinline__ void half_compute(const char* s, HalfAcc<C>& acc) {
     for (int p = 0; p < 4; ++p)
       a[p] = *reinterpret_cast<const f16x8*>(sa + i * 4096 + ((p * 4 + lk) ^ lr) * 16);
     const f16x8 nh = -a[2], nl = -a[3];
+    f16x8 rt, it, nt;
     if constexpr (C::PA == 3) {
-      const f16x8 rt = *reinterpret_cast<const f16x8*>(st + i * 2048 + (lk ^ (lr & 7)) * 16);
-      const f16x8 it = *reinterpret_cast<const f16x8*>(st + i * 2048 + ((4 + lk) ^ (lr & 7)) * 16);
-      const f16x8 nt = -it;
+      rt = *reinterpret_cast<const f16x8*>(st + i * 2048 + (lk ^ (lr & 7)) * 16);
+      it = *reinterpret_cast<const f16x8*>(st + i * 2048 + ((4 + lk) ^ (lr & 7)) * 16);
+      nt = -it;
+    }
+    f32x4 re[C::NB], im[C::NB];   // this chunk's sums
 #pragma unroll
-      for (int j = 0; j < C::NB; ++j) {
-        acc.re[i][j] = mfma_f16(rt, b[j][0], acc.re[i][j]);
-        acc.im[i][j] = mfma_f16(rt, b[j][2], acc.im[i][j]);
-        acc.re[i][j] = mfma_f16(nt, b[j][2], acc.re[i][j]);
-        acc.im[i][j] = mfma_f16(it, b[j][0], acc.im[i][j]);
+    for (int j = 0; j < C::NB; ++j) {
+      const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+      if constexpr (C::PA == 3) {
+        re[j] = mfma_f16(rt, b[j][0], zero);
+        im[j] = mfma_f16(rt, b[j][2], zero);
+        re[j] = mfma_f16(nt, b[j][2], re[j]);
+        im[j] = mfma_f16(it, b[j][0], im[j]);
+        re[j] = mfma_f16(a[1], b[j][0], re[j]);
+        im[j] = mfma_f16(a[1], b[j][2], im[j]);
+      } else {
+        re[j] = mfma_f16(a[1], b[j][0], zero);
+        im[j] = mfma_f16(a[1], b[j][2], zero);
       }
     }
 #pragma unroll
     for (int j = 0; j < C::NB; ++j) {
-      f32x4 re = acc.re[i][j], im = acc.im[i][j];
-      re = mfma_f16(a[1], b[j][0], re);
-      im = mfma_f16(a[1], b[j][2], im);
-      re = mfma_f16(nl, b[j][2], re);
-      im = mfma_f16(a[3], b[j][0], im);
-      re = mfma_f16(a[0], b[j][1], re);
-      im = mfma_f16(a[0], b[j][3], im);
-      re = mfma_f16(nh, b[j][3], re);
-      im = mfma_f16(a[2], b[j][1], im);
-      re = mfma_f16(a[0], b[j][0], re);
-      im = mfma_f16(a[0], b[j][2], im);
-      re = mfma_f16(nh, b[j][2], re);
-      im = mfma_f16(a[2], b[j][0], im);
-      acc.re[i][j] = re;
-      acc.im[i][j] = im;
+      re[j] = mfma_f16(nl, b[j][2], re[j]);
+      im[j] = mfma_f16(a[3], b[j][0], im[j]);
+      re[j] = mfma_f16(a[0], b[j][1], re[j]);
+      im[j] = mfma_f16(a[0], b[j][3], im[j]);
+      re[j] = mfma_f16(nh, b[j][3], re[j]);
+      im[j] = mfma_f16(a[2], b[j][1], im[j]);
+      re[j] = mfma_f16(a[0], b[j][0], re[j]);
+      im[j] = mfma_f16(a[0], b[j][2], im[j]);
+      re[j] = mfma_f16(nh, b[j][2], re[j]);
+      im[j] = mfma_f16(a[2], b[j][0], im[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < C::NB; ++j) {
+      acc.re[i][j] = SUB ? acc.re[i][j] - re[j] : acc.re[i][j] + re[j];
+      acc.im[i][j] = SUB ? acc.im[i][j] - im[j] : acc.im[i][j] + im[j];
     }
   }
 }
@@ -199,12 +220,12 @@ __device__ __forceinline__ void half_compute(const char* s, HalfAcc<C>& acc) {
 // The copies into `nxt` run under the products from `cur`.  The two are
 // different stages; `__restrict__` lets the compiler order no read of one
 // behind the copies into the other.
-template <class C>
+template <class C, bool SUB>
 __device__ __forceinline__ void half_step(const HalfLoader<C>& ld, char* __restrict__ nxt, int c,
                                           const char* __restrict__ cur, HalfAcc<C>& acc) {
   ld.load(nxt, c);
   __builtin_amdgcn_sched_barrier(0);   // the copies first
-  half_compute<C>(cur, acc);
+  half_compute<C, SUB>(cur, acc);
 }
 
 // vmcnt(0): this wave's copies into LDS have landed; the barrier publishes
@@ -214,7 +235,8 @@ __device__ __forceinline__ void half_publish() {
   __syncthreads();
 }
 
-// acc = sum over chunks c0 .. c1 - 1 (at least one), from the top with DOWN.
+// acc = sum over chunks c0 .. c1 - 1 (at least one), from the top with DOWN; the
+// second, fourth, ... chunk in that order is negated in A.
 template <class C, bool DOWN>
 __device__ __forceinline__ void half_mainloop(const HalfOperand& A, const HalfOperand& B, int c0,
                                               int c1, char* s0, char* s1, HalfAcc<C>& acc) {
@@ -230,12 +252,12 @@ __device__ __forceinline__ void half_mainloop(const HalfOperand& A, const HalfOp
   half_publish();
   int k = 0;
   for (; k + 2 <= n; k += 2) {
-    half_step<C>(ld, s1, at(k + 1), s0, acc);
+    half_step<C, false>(ld, s1, at(k + 1), s0, acc);
     half_publish();
-    half_step<C>(ld, s0, at(k + 2), s1, acc);   // the last pass copies a chunk it does not use
+    half_step<C, true>(ld, s0, at(k + 2), s1, acc);   // the last pass copies a chunk it does not use
     half_publish();
   }
-  if (k < n) half_compute<C>(s0, acc);
+  if (k < n) half_compute<C, false>(s0, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -274,7 +296,9 @@ __global__ __launch_bounds__(256) void k_factor_exps(const double* __restrict__ 
 
 // Packed rows of L^-1 (TRANS false: row n, k = n' <= n) or L^-H (TRANS: row i,
 // value conj(Li[k][i]), k >= i), 8 columns per thread.  Only the chunks that
-// the products read are written: k up to, or from, the row's block of 128.
+// the products read are written: k up to, or from, the row's block of 128.  Odd
+// chunks are negated, counted from k = 0 for L^-1 and from the end for L^-H, as
+// the products visit them.
 template <bool TRANS>
 __global__ __launch_bounds__(256) void k_factor_pack(const double* __restrict__ Li, int N, int nc,
                                                      const int* __restrict__ e_max,
@@ -294,13 +318,14 @@ __global__ __launch_bounds__(256) void k_factor_pack(const double* __restrict__ 
     const int blk = r / 128 * 128;
     if (TRANS ? 8 * g < blk : 8 * g >= blk + 128) continue;
     const int s = row_shift(e_max[r], 1023);
+    const bool neg = ((TRANS ? nc - 1 - g / 4 : g / 4) & 1) != 0;
     f16x8 p[6];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int k = 8 * g + j;
       cx<double> v{0.0, 0.0};
       if (k < N) v = TRANS ? L[(size_t)k * N + r] : L[(size_t)r * N + k];
-      const double x[2] = {ldexp(v.re, s), ldexp(TRANS ? -v.im : v.im, s)};
+      const double x[2] = {ldexp(neg ? -v.re : v.re, s), ldexp(TRANS != neg ? -v.im : v.im, s)};
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const _Float16 h = (_Float16)x[c];
@@ -367,9 +392,10 @@ __global__ __launch_bounds__(256) void k_gen_e_h(EncDev<float> e, int m0, int ro
 // W^T (packed, rows m, k = n) and R
 // ---------------------------------------------------------------------------
 // Bound by the f16 pipe's power budget: at N = 9216, M = 131072 the two products
-// take 141 and 133 ms, R at 1340 TFLOP/s of executed f16 products, what a plain
-// bf16 library product of 16384^3 reaches on the same card (1330); three real
-// FP32 products per complex one took 329 and 313 ms.  128 x 128 tiles over eight
+// take 142 and 136 ms (the shader clock falls to 1.6-1.7 GHz, the pipe 0.7 busy),
+// R at 1310 TFLOP/s of executed f16 products, what a plain bf16 library product
+// of 16384^3 reaches on the same card (1330); three real FP32 products per complex
+// one took 329 and 313 ms.  128 x 128 tiles over eight
 // wavefronts fill the 160 KB of LDS with two stages of 80 KB; the LDS moves
 // 344 KB a chunk (2700 cycles) against 4096 cycles of matrix products.
 typedef HalfCfg<128, 128, 2, 4, 3> TrmmH;
