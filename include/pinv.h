@@ -114,9 +114,10 @@ typedef struct {
                                    precision).  The build costs what an FP64 build costs. */
 
 /* Complex-product form of the triangular products W, R and the apply (MFMA).
- * FP32 plans on AUTO or 3M with M >= N >= 256 form W and R from f16 pieces of
- * their FP32 operands instead (FP32 accumulation, at least the accuracy of
- * the FP32 instructions, 2.3 times faster); 4M keeps every product on FP32
+ * FP32 plans on AUTO or 3M with M >= N run all but small products W and R, and
+ * those with any R their applies of more than 32 frames, on f16 pieces of the FP32
+ * operands instead (FP32 accumulation, at least the accuracy of the FP32
+ * instructions, 2.3 times faster); 4M keeps every product of an FP32 R on FP32
  * instructions. */
 typedef enum {
   PINV_CPROD_AUTO = 0,   /* 3M for FP32 plans, 4M for FP64 plans and FP64-formed R */

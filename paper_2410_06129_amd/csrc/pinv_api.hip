@@ -106,6 +106,7 @@ struct pinv_context {
   std::vector<PendingFree> pending;
   hipMemPool_t build_pool = nullptr;   // build workspaces (Gram, FP64 factor, W)
   hipMemPool_t plan_pool = nullptr;    // plan buffers (R, L^-1, Gram, tables)
+  hipMemPool_t apply_pool = nullptr;   // packed slabs of many-frame FP32 applies
   // pinned staging for table uploads, reused by every build of the context:
   // stage_ev marks the completion of the last copies out of it
   std::mutex stage_mu;
@@ -428,12 +429,17 @@ void drain_frees(pinv_context* c, hipStream_t s, bool wait) {
 // Factorisation block size when the options leave it at 0.
 constexpr int kDefaultNb = 128;
 
-// FP32 plans from this many unknowns form W and R on f16 pieces, two of the
-// tile rows of pinv_half.hip; at N = 1024, M = 2048 W and R take 0.15 and 0.11 ms
-// against 0.20 and 0.20 on FP32 instructions, at N = 4096, M = 32768 8.5 and
-// 7.3 ms against 17.4 and 15.9.  Not with an FP32 Gram over all rows: its error may
-// exceed the shift, and W's entries then need not stay below 1.
-constexpr int kHalfMinN = 256;
+// Whether an FP32 plan forms W and R on f16 pieces: from 3e8 complex products
+// (N^2 M), or 1.5e9 where N is not a multiple of 32 (W^T's rows are padded, conj(E)
+// then takes a second slab).  Below, the packing and a grid of few 128 x 128 tiles
+// cost more (W + R in us on f16 pieces and on FP32 tiles: N = 256, M = 2056, 1.3e8:
+// 119, 94; M = 8208, 5.4e8: 125, 142; N = 576, M = 2308, 7.7e8: 182, 200; N = 400,
+// M = 3208, 5.1e8: 213, 150; N = 784, M = 3140, 1.9e9: 328, 364; N = 1600, M = 51216:
+// 5042, 9713).  Not with an FP32 Gram over all rows: its error may exceed the
+// shift, and W's entries then need not stay below 1.
+bool half_products(int64_t N, int64_t M, int gram) {
+  return (double)N * N * M >= (N % 32 == 0 ? 3e8 : 1.5e9) && gram != PINV_GRAM_FULL;
+}
 
 struct BuildForm {
   bool m3 = true;
@@ -653,6 +659,10 @@ pinv_status pinv_context_create(int device, size_t budget, pinv_context** out) {
     (void)hipMemPoolSetAttribute(c->plan_pool, hipMemPoolAttrReleaseThreshold, &keep);
   else
     c->plan_pool = nullptr, (void)hipGetLastError();
+  if (hipMemPoolCreate(&c->apply_pool, &props) == hipSuccess)
+    (void)hipMemPoolSetAttribute(c->apply_pool, hipMemPoolAttrReleaseThreshold, &keep);
+  else
+    c->apply_pool = nullptr, (void)hipGetLastError();
   if (hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
     pinv_context_destroy(c);
     return fail(PINV_ERR_DEVICE, "cannot create the staging event");
@@ -680,6 +690,7 @@ pinv_status pinv_context_destroy(pinv_context* c) {
   }
   if (c->build_pool) (void)hipMemPoolDestroy(c->build_pool);
   if (c->plan_pool) (void)hipMemPoolDestroy(c->plan_pool);
+  if (c->apply_pool) (void)hipMemPoolDestroy(c->apply_pool);
   if (c->stage_ev) (void)hipEventDestroy(c->stage_ev);
   if (c->stage) (void)hipHostFree(c->stage);
   delete c;   // the library's streams stay for the next context
@@ -784,7 +795,7 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
                                          : o->prec != PINV_FP64 && !r_fp64;
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
   form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
-               o->route == PINV_ROUTE_CHOLESKY && d->N >= kHalfMinN && gram != PINV_GRAM_FULL;
+               o->route == PINV_ROUTE_CHOLESKY && half_products(d->N, d->M, gram);
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);
@@ -819,6 +830,7 @@ static void trim_pool(pinv_context* c, bool force, bool plans) {
   hipMemPool_t pool;
   if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
   if (c->build_pool) (void)hipMemPoolTrimTo(c->build_pool, 0);
+  if (c->apply_pool) (void)hipMemPoolTrimTo(c->apply_pool, 0);
   if (plans && c->plan_pool) {
     // released plans whose work has finished go back as well
     drain_frees(c, c->aux_nb, false);
@@ -1534,6 +1546,7 @@ pinv_status pinv_apply_grouped(pinv_context* c, int32_t n, const pinv_apply_item
   Scratch sc;   // stream-ordered allocations from the default pool
   sc.reclaim = reclaim_pools;
   sc.reclaim_arg = c;
+  sc.large = c->apply_pool;
   const pinv_status st = apply_items(c, n, items, refine_steps, sc, s);
   if (st != PINV_OK) return st;
   for (int j = 0; j < n; ++j)

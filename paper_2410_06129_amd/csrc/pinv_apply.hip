@@ -615,6 +615,15 @@ static hipError_t run_apply(ApplyBatch b, Scratch& sc, hipStream_t s) {
   return err;
 }
 
+// Whether an FP32 apply of more than kStreamMaxF frames runs on f16 pieces: on
+// AUTO and 3M plans and on those with an FP64-formed R, from 3e8 complex
+// products.  Below, its packing launches cost more than the products save
+// (N = 289, M = 416, 500 frames, 6e7: 41 us on FP32 tiles, 47 on f16 pieces;
+// N = 1024, M = 2048, 128 frames, 2.7e8: 48 and 51; 200 frames: 63 and 53).
+static bool half_apply(int F, int N, int M, bool m3, bool seg) {
+  return (m3 || seg) && (double)F * N * M >= 3e8;
+}
+
 template <typename T, bool M3, bool SEG>
 static hipError_t apply_form(const ApplyBatch& b, Scratch& sc, hipStream_t s) {
   typedef ApplyCfgOf<T, M3> C;
@@ -629,6 +638,15 @@ static hipError_t apply_form(const ApplyBatch& b, Scratch& sc, hipStream_t s) {
         const hipError_t err = launch_apply_stream((const float*)it.R, (const float*)it.D,
                                                    (float*)it.X, it.N, it.M, it.F, M3, sc, s);
         if (err != hipSuccess) return err;
+      } else if (half_apply(it.F, it.N, it.M, M3, SEG)) {
+        hipError_t err = launch_apply_half((const float*)it.R, (const float*)it.D, (float*)it.X, it.N,
+                                           it.M, it.F, sc, s);
+        if (err == hipErrorOutOfMemory) {   // the tiles need less scratch, or none
+          (void)hipGetLastError();
+          many.it[many.n++] = it;
+        } else if (err != hipSuccess) {
+          return err;
+        }
       } else {
         many.it[many.n++] = it;
       }
@@ -653,6 +671,8 @@ size_t apply_scratch_bytes(int F, int N, int M, bool m3, bool seg) {
     typedef ApplyCfgOf<T, decltype(form)::value> C;
     constexpr bool S = std::is_same<T, float>::value && decltype(sg)::value;
     if (std::is_same<T, float>::value && F <= kStreamMaxF) return apply_stream_scratch_bytes(F, N, M);
+    if (std::is_same<T, float>::value && half_apply(F, N, M, decltype(form)::value, S))
+      return apply_half_scratch_bytes(F, N, M);
     return item_work_bytes<typename C::many, S>(F, N, M);
   };
   if (seg)

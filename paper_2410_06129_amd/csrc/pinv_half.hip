@@ -1,5 +1,5 @@
-// FP32 products on the f16 matrix pipe: W = L^-1 E^H, R = L^-H W (Eq. 8) of
-// FP32 plans.
+// FP32 products on the f16 matrix pipe: W = L^-1 E^H, R = L^-H W (Eq. 8) and
+// the many-frame apply image = R data (Eq. 3) of FP32 plans.
 //
 // v_mfma_f32_16x16x32_f16 multiplies sixteen times faster than
 // v_mfma_f32_16x16x4_f32, so each FP32 operand value is written as a sum of
@@ -486,8 +486,254 @@ __global__ __launch_bounds__(TrmmH::NT, 1) void k_trmm_rh(const char* __restrict
 }
 
 // ---------------------------------------------------------------------------
+// Apply: X[f][n] = sum_m D[f][m] R[n][m] for more frames than the streamed apply
+// takes
+// ---------------------------------------------------------------------------
+// The contraction is cut into segments of at most kHalfSegCols columns, each with
+// row scales of its own, so a running FP32 sum covers one segment.  A slab of
+// segments of R and of the data is packed into scratch, multiplied (one tile grid
+// per segment) and its segments' partial images are added into X.  A slab is at
+// most kHalfApplyBytes, which the 256 MB memory-side cache holds between the pass
+// that writes it and the product that reads it.
+constexpr int kHalfSegCols = 4096;
+constexpr size_t kHalfApplyBytes = 256ull << 20;
+constexpr int kHalfFrames = 2048;   // frames per pass over R
+
+// Rows r of `src` (complex64, ld columns a row), columns c0 + seg_len g .. of
+// segment g (zero at and past `cols`): dst[g][r][chunk], and the power of two that
+// scales the row in exps[g][r].  NEG: odd chunks negated (operand A of the
+// tiles).  One workgroup per row and segment, a pair of columns per thread and
+// step.
+template <int VEC, bool NEG>
+__global__ __launch_bounds__(256) void k_pack_half(const float* __restrict__ src, int64_t ld, int rows,
+                                                   int64_t c0, int64_t cols, int seg_len,
+                                                   char* __restrict__ dst, int* __restrict__ exps) {
+  constexpr int STEPS = kHalfSegCols / 512;
+  const int r = (int)(blockIdx.x % rows), g = (int)(blockIdx.x / rows);
+  const cx<float>* z = reinterpret_cast<const cx<float>*>(src) + (int64_t)r * ld + c0 + (int64_t)g * seg_len;
+  const int64_t left = cols - c0 - (int64_t)g * seg_len;
+  const int live = (int)(left < seg_len ? left : seg_len);
+  float4 v[STEPS];
+  int e = 0;
+#pragma unroll
+  for (int i = 0; i < STEPS; ++i) {
+    const int k = 2 * (threadIdx.x + 256 * i);
+    v[i] = float4{0.f, 0.f, 0.f, 0.f};
+    if (VEC == 2) {   // an even number of columns, 16-byte aligned rows and segments
+      if (k < live) v[i] = *reinterpret_cast<const float4*>(z + k);
+    } else {
+      if (k < live) v[i].x = z[k].re, v[i].y = z[k].im;
+      if (k + 1 < live) v[i].z = z[k + 1].re, v[i].w = z[k + 1].im;
+    }
+#pragma unroll
+    for (const float x : {v[i].x, v[i].y, v[i].z, v[i].w})
+      e = max(e, (__float_as_int(x) & 0x7fffffff) >> 23);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
+  __shared__ int we[4];
+  if ((threadIdx.x & 63) == 0) we[threadIdx.x >> 6] = e;
+  __syncthreads();
+  const int s = row_shift(max(max(we[0], we[1]), max(we[2], we[3])), 127);
+  if (threadIdx.x == 0) exps[(size_t)g * rows + r] = s;
+  char* d = dst + ((size_t)g * rows + r) * (seg_len / 32) * 256;
+#pragma unroll
+  for (int i = 0; i < STEPS; ++i) {
+    const int k = 2 * (threadIdx.x + 256 * i);
+    if (k >= seg_len) break;
+    uint32_t o[4];
+    split_h2(ldexpf(v[i].x, s), ldexpf(v[i].z, s), o[0], o[1]);
+    split_h2(ldexpf(v[i].y, s), ldexpf(v[i].w, s), o[2], o[3]);
+    const uint32_t sign = NEG && (k / 32 & 1) ? 0x80008000u : 0u;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      *reinterpret_cast<uint32_t*>(d + (k / 32) * 256 + p * 64 + (k % 32) * 2) = o[p] ^ sign;
+  }
+}
+
+// Tiles of BM frames x BN unknowns, one grid of `tiles` per segment.  With
+// `work` the partial image of segment g goes to work[g][F][N]; else to X (added
+// to what is there with `add`).
+template <class C>
+__global__ __launch_bounds__(C::NT, 1) void k_apply_half(const char* __restrict__ Dp,
+                                                         const int* __restrict__ de,
+                                                         const char* __restrict__ Rp,
+                                                         const int* __restrict__ re, int F, int N, int nc,
+                                                         int64_t cols, int tiles, float* __restrict__ X,
+                                                         float* __restrict__ work, int add) {
+  __shared__ __attribute__((aligned(1024))) char s0[C::STAGE];
+  __shared__ __attribute__((aligned(1024))) char s1[C::STAGE];
+  const int u = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int g = u / tiles, t = u - g * tiles;
+  const int nbi = (F + C::BM - 1) / C::BM;
+  const int bi = t % nbi, bj = t / nbi;
+  const int64_t left = cols - (int64_t)g * nc * 32;   // the last segment may be short
+  const int n = (int)min((int64_t)nc, (left + 31) / 32);
+  HalfAcc<C> acc;
+  half_mainloop<C, false>(HalfOperand{Dp + (size_t)g * F * nc * 256, nullptr, nc, bi * C::BM, F - 1},
+                          HalfOperand{Rp + (size_t)g * N * nc * 256, nullptr, nc, bj * C::BN, N - 1}, 0, n,
+                          s0, s1, acc);
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = w / C::WGN, wc = w % C::WGN;
+  cx<float>* O = reinterpret_cast<cx<float>*>(work ? work + (size_t)g * F * N * 2 : X);
+#pragma unroll
+  for (int j = 0; j < C::NB; ++j) {
+    const int col = bj * C::BN + wc * C::WTN + j * 16 + (lane & 15);
+    if (col >= N) continue;
+    const int sr = re[(size_t)g * N + col];
+#pragma unroll
+    for (int i = 0; i < C::MB; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int f = bi * C::BM + wr * C::WTM + i * 16 + 4 * (lane >> 4) + q;
+        if (f >= F) continue;
+        const int sh = -sr - de[(size_t)g * F + f];
+        cx<float> x{ldexpf(acc.re[i][j][q], sh), ldexpf(acc.im[i][j][q], sh)};
+        cx<float>* o = O + (size_t)f * N + col;
+        if (add) {
+          const cx<float> old = *o;
+          x.re += old.re;
+          x.im += old.im;
+        }
+        *o = x;
+      }
+  }
+}
+
+// X = (add ? X : 0) + sum_g work[g] in segment order, in FP64, rounded once.
+__global__ __launch_bounds__(256) void k_half_reduce(const float* __restrict__ work, int segs, int64_t n,
+                                                     float* __restrict__ X, int add) {
+  const cx<float>* w = reinterpret_cast<const cx<float>*>(work);
+  cx<float>* x = reinterpret_cast<cx<float>*>(X);
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    double re = add ? x[i].re : 0.0, im = add ? x[i].im : 0.0;
+    for (int g = 0; g < segs; ++g) {
+      re += w[(int64_t)g * n + i].re;
+      im += w[(int64_t)g * n + i].im;
+    }
+    x[i] = cx<float>{(float)re, (float)im};
+  }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// Tiles of 128 frames x 128 unknowns, or of 64 x 256 where they leave less of the
+// last frame tile empty or fill the CUs better.  1000 frames at N = 4096, M = 65536:
+// 5.2 ms of products (410 TFLOP/s of complex products, 1240 executed; the power
+// budget again) and 1.0 ms of packing, where the FP32 tiles took 15.6 (18.8 in
+// segments); 300 frames 2.7 ms against 5.9 (7.1).  At 33 to 64 frames the packing
+// (R read and written once) is most of the 1.5 ms, against 2.0 (2.4).
+typedef HalfCfg<128, 128, 2, 4, 2> ApplyH128;
+typedef HalfCfg<64, 256, 1, 8, 2> ApplyH64;
+
+// Segments, slabs and tiles of an apply: a function of F, N and M only.
+struct HalfApply {
+  int frames;     // frames per pass
+  bool wide;      // tiles of 128 frames (else 64)
+  int seg_len, nseg, slab;   // columns per segment, segments, segments per slab
+  size_t r_bytes, d_bytes, e_bytes, w_bytes;
+  size_t bytes() const { return r_bytes + d_bytes + e_bytes + w_bytes; }
+};
+
+static HalfApply half_apply_plan(int F, int N, int M) {
+  HalfApply best{};
+  double best_cost = 1e300;
+  const int64_t fr = std::min(F, kHalfFrames);
+  for (int wide = 0; wide < 2; ++wide) {
+    const int64_t tiles = (int64_t)cdiv(fr, wide ? 128 : 64) * cdiv(N, wide ? 128 : 256);
+    for (int len = kHalfSegCols; len >= 256; len /= 2) {
+      const int nseg = cdiv(M, len);
+      const int sl = cdiv(cdiv(M, nseg), 32) * 32;
+      const size_t per = (size_t)(N + fr) * sl * 8 + (size_t)(N + fr) * 4;
+      const size_t part = (size_t)fr * N * 8;
+      int64_t slab = std::min<int64_t>(nseg, (int64_t)(kHalfApplyBytes / (per + part)));
+      if (slab < 1) slab = per <= kHalfApplyBytes ? 1 : 0;
+      for (; slab >= 1; slab = slab > 1 ? slab / 2 : 0) {
+        // rounds of the tile grid over the 256 CUs, in chunks, with a fixed part
+        // for the tile's start and end; a tile of 64 frames takes 0.55 of one of 128
+        const int nslab = cdiv(nseg, slab);
+        const double cost = (double)nslab * (((int64_t)tiles * slab + 255) / 256) *
+                            ((sl / 32) * (wide ? 1.0 : 1.1) + 6.0) + 4.0 * nslab;
+        if (cost < best_cost * 0.999) {
+          best_cost = cost;
+          best.frames = (int)fr;
+          best.wide = wide;
+          best.seg_len = sl;
+          best.nseg = cdiv(M, sl);
+          best.slab = (int)slab;
+          auto al = [](size_t n) { return (n + 255) & ~size_t(255); };
+          best.r_bytes = al((size_t)N * sl * 8 * slab);
+          best.d_bytes = al((size_t)fr * sl * 8 * slab);
+          best.e_bytes = al((size_t)(N + fr) * 4 * slab);
+          best.w_bytes = slab > 1 ? al(part * slab) : 0;
+        }
+      }
+    }
+  }
+  return best;
+}
+
+size_t apply_half_scratch_bytes(int F, int N, int M) { return half_apply_plan(F, N, M).bytes(); }
+
+hipError_t launch_apply_half(const float* R, const float* D, float* X, int N, int M, int F, Scratch& sc,
+                             hipStream_t s) {
+  if (F <= 0 || N <= 0) return hipSuccess;
+  const HalfApply p = half_apply_plan(F, N, M);
+  if (p.slab < 1) return hipErrorInvalidValue;
+  void* ws = nullptr;
+  hipError_t err = sc.get_large(&ws, p.bytes(), s);
+  if (err != hipSuccess) return err;
+  char* rp = (char*)ws;
+  char* dp = rp + p.r_bytes;
+  int* re = (int*)(dp + p.d_bytes);
+  int* de = re + (size_t)N * p.slab;
+  float* work = p.w_bytes ? (float*)(dp + p.d_bytes + p.e_bytes) : nullptr;
+  const bool vec = M % 2 == 0 && ((uintptr_t)R % 16) == 0 && ((uintptr_t)D % 16) == 0;
+  auto pack = [&](auto neg, const float* src, int rows, int64_t c0, int segs, char* dst, int* exps) {
+    constexpr bool NEG = decltype(neg)::value;
+    const dim3 grid((unsigned)((int64_t)rows * segs)), block(256);
+    if (vec)
+      hipLaunchKernelGGL((k_pack_half<2, NEG>), grid, block, 0, s, src, (int64_t)M, rows, c0, (int64_t)M,
+                         p.seg_len, dst, exps);
+    else
+      hipLaunchKernelGGL((k_pack_half<1, NEG>), grid, block, 0, s, src, (int64_t)M, rows, c0, (int64_t)M,
+                         p.seg_len, dst, exps);
+    return hipGetLastError();
+  };
+  for (int f0 = 0; f0 < F && err == hipSuccess; f0 += p.frames) {
+    const int f = std::min(p.frames, F - f0);
+    const float* d = D + 2 * (size_t)f0 * M;
+    float* x = X + 2 * (size_t)f0 * N;
+    const int tiles = cdiv(f, p.wide ? 128 : 64) * cdiv(N, p.wide ? 128 : 256);
+    for (int g0 = 0; g0 < p.nseg && err == hipSuccess; g0 += p.slab) {
+      const int segs = std::min(p.slab, p.nseg - g0);
+      const int64_t c0 = (int64_t)g0 * p.seg_len;
+      const int add = g0 > 0;
+      if ((err = pack(std::true_type{}, d, f, c0, segs, dp, de)) != hipSuccess) break;
+      if ((err = pack(std::false_type{}, R, N, c0, segs, rp, re)) != hipSuccess) break;
+      auto tile = [&](auto cfg) {
+        typedef decltype(cfg) C;
+        hipLaunchKernelGGL(k_apply_half<C>, dim3((unsigned)(tiles * segs)), dim3(C::NT), 0, s,
+                           (const char*)dp, (const int*)de, (const char*)rp, (const int*)re, f, N,
+                           p.seg_len / 32, (int64_t)M - c0, tiles, x, work, work ? 0 : add);
+        return hipGetLastError();
+      };
+      err = p.wide ? tile(ApplyH128{}) : tile(ApplyH64{});
+      if (err == hipSuccess && work) {
+        const int64_t n = (int64_t)f * N;
+        hipLaunchKernelGGL(k_half_reduce, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 8192)), dim3(256),
+                           0, s, (const float*)work, segs, n, x, add);
+        err = hipGetLastError();
+      }
+    }
+  }
+  const hipError_t ferr = sc.put(ws, s);
+  return err != hipSuccess ? err : ferr;
+}
+
 static int grid_1d(int64_t n, int most) {
   return (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, most));
 }

@@ -50,13 +50,22 @@ struct Scratch {
   int depth = 0;
   void (*reclaim)(void* arg, hipStream_t s) = nullptr;
   void* reclaim_arg = nullptr;
-  hipError_t get(void** p, size_t bytes, hipStream_t s) {
+  // `large`, when set, is a pool for the one block of an apply that may take
+  // hundreds of megabytes (get_large): in the default pool a smaller request can
+  // be served from that block while it is free, and the next apply maps another.
+  hipMemPool_t large = nullptr;
+  hipError_t get(void** p, size_t bytes, hipStream_t s) { return get_from(nullptr, p, bytes, s); }
+  hipError_t get_large(void** p, size_t bytes, hipStream_t s) { return get_from(large, p, bytes, s); }
+  hipError_t get_from(hipMemPool_t pool, void** p, size_t bytes, hipStream_t s) {
     if (!base) {
-      hipError_t e = hipMallocAsync(p, bytes, s);
+      auto once = [&]() {
+        return pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
+      };
+      hipError_t e = once();
       if (e == hipErrorOutOfMemory && reclaim) {
         (void)hipGetLastError();
         reclaim(reclaim_arg, s);
-        e = hipMallocAsync(p, bytes, s);
+        e = once();
       }
       return e;
     }
@@ -218,6 +227,11 @@ hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor
                           int64_t slab_rows, int es, void* Wt, hipStream_t s);
 hipError_t launch_trmm_rh(const double* Li, void* factor, const void* Wt, float* R, int N, int M,
                           hipStream_t s);
+// X = D R^T of F frames on f16 pieces; scratch of apply_half_scratch_bytes (at
+// most 256 MB and the rounding of its parts, whatever the sizes).
+size_t apply_half_scratch_bytes(int F, int N, int M);
+hipError_t launch_apply_half(const float* R, const float* D, float* X, int N, int M, int F, Scratch& sc,
+                             hipStream_t s);
 hipError_t launch_to_f32(const double* in, float* out, size_t n_complex, hipStream_t s);
 hipError_t launch_to_f64(const float* in, double* out, size_t n_complex, hipStream_t s);
 template <typename T> hipError_t launch_srf_diag(const EncDev<T>& e, const T* R, T* out, hipStream_t s);
