@@ -223,126 +223,102 @@ uint64_t plan_key(const pinv_encoding* e, const Dims& d, double lam, int prec, i
   return f.h;
 }
 
-// exp(-i 2 pi turns) with the turn count reduced to (-1/2, 1/2] first.
-inline void phasor(double turns, double* re, double* im) {
-  const double f = turns - nearbyint(turns);
-  *re = cos(2.0 * M_PI * f);
-  *im = -sin(2.0 * M_PI * f);
-}
-
-// Host FP64 tables (Px, Py, Q, coil, b0, t), laid out contiguously.
-struct HostTables {
-  std::vector<double> px, py, q, coil, b0, t;
-  std::vector<int32_t> vxy;   // (iy << 16) | ix of each unknown voxel (masked encodings only)
+// Where an encoding's tables lie in the plan's device buffers.  The phase factors
+// (Px, Py, Q) are formed on the device; the maps, times, voxel positions,
+// trajectory and species frequencies behind them are copied from the host in one
+// piece (FP64 buffer only).  Each table is 256-aligned.
+struct TableLayout {
+  size_t px, py, q, coil, b0, t, vxy, k, hz;   // byte offsets
+  size_t raw, bytes;                           // start of the host's part, total
 };
 
-void build_tables(const pinv_encoding* e, const Dims& d, HostTables* h) {
-  h->px.resize(2 * (size_t)d.K * d.nx);
-  h->py.resize(2 * (size_t)d.K * d.ny);
-  for (int i = 0; i < d.K; ++i) {
-    const double kx = e->k[2 * i], ky = e->k[2 * i + 1];
-    for (int ix = 0; ix < d.nx; ++ix) {
-      const double x = (ix - d.nx / 2.0) / d.nx;
-      phasor(kx * x, &h->px[2 * ((size_t)i * d.nx + ix)], &h->px[2 * ((size_t)i * d.nx + ix) + 1]);
-    }
-    for (int iy = 0; iy < d.ny; ++iy) {
-      const double y = (iy - d.ny / 2.0) / d.ny;
-      phasor(ky * y, &h->py[2 * ((size_t)i * d.ny + iy)], &h->py[2 * ((size_t)i * d.ny + iy) + 1]);
-    }
+TableLayout table_layout(const pinv_encoding* e, const Dims& d, size_t elem, bool raw) {
+  TableLayout l{};
+  size_t at = 0;
+  auto take = [&](size_t* off, size_t bytes) {
+    *off = at;
+    at += align256(bytes);
+  };
+  take(&l.px, 2 * (size_t)d.K * d.nx * elem);
+  take(&l.py, 2 * (size_t)d.K * d.ny * elem);
+  take(&l.q, d.has_q ? 2 * (size_t)d.K * d.S * elem : 0);
+  l.raw = at;
+  take(&l.coil, d.has_coil ? 2 * (size_t)d.C * d.V * elem : 0);
+  take(&l.b0, d.has_b0 ? d.V * elem : 0);
+  take(&l.t, d.has_b0 || (raw && d.has_q) ? d.K * elem : 0);
+  if (raw) {
+    take(&l.vxy, d.masked ? d.V * sizeof(int32_t) : 0);
+    take(&l.k, 2 * (size_t)d.K * sizeof(double));
+    take(&l.hz, e->species_hz ? d.S * sizeof(double) : 0);
   }
-  if (d.has_q) {
-    h->q.resize(2 * (size_t)d.K * d.S);
-    for (int i = 0; i < d.K; ++i)
-      for (int s = 0; s < d.S; ++s) {
-        const double f = e->species_hz ? e->species_hz[s] : 0.0;
-        phasor(f * e->t[i], &h->q[2 * ((size_t)i * d.S + s)], &h->q[2 * ((size_t)i * d.S + s) + 1]);
-      }
-  }
-  // coil maps and the off-resonance map at the unknown voxels only
-  auto grid_voxel = [&](int j) { return d.masked ? (size_t)e->voxels[j] : (size_t)j; };
+  l.bytes = at;
+  return l;
+}
+
+// The host's part of the FP64 tables, packed into `stage` (pinned, l.bytes - l.raw):
+// coil and off-resonance maps at the unknown voxels, sample times, the voxels'
+// grid positions ((iy << 16) | ix), trajectory and species frequencies.
+void stage_tables(const pinv_encoding* e, const Dims& d, const TableLayout& l, char* stage) {
+  auto at = [&](size_t off) { return stage + (off - l.raw); };
   if (d.has_coil) {
-    h->coil.resize(2 * (size_t)d.C * d.V);
-    for (int c = 0; c < d.C; ++c)
-      for (int j = 0; j < d.V; ++j) {
-        const size_t src = 2 * ((size_t)c * d.Vg + grid_voxel(j)), dst = 2 * ((size_t)c * d.V + j);
-        h->coil[dst] = e->coil[src];
-        h->coil[dst + 1] = e->coil[src + 1];
-      }
+    double* o = (double*)at(l.coil);
+    if (!d.masked) {
+      memcpy(o, e->coil, sizeof(double) * 2 * (size_t)d.C * d.V);
+    } else {
+      for (int c = 0; c < d.C; ++c)
+        for (int j = 0; j < d.V; ++j) {
+          const size_t src = 2 * ((size_t)c * d.Vg + e->voxels[j]), dst = 2 * ((size_t)c * d.V + j);
+          o[dst] = e->coil[src];
+          o[dst + 1] = e->coil[src + 1];
+        }
+    }
   }
   if (d.has_b0) {
-    h->b0.resize(d.V);
-    for (int j = 0; j < d.V; ++j) h->b0[j] = e->b0_hz[grid_voxel(j)];
-    h->t.assign(e->t, e->t + d.K);
+    double* o = (double*)at(l.b0);
+    for (int j = 0; j < d.V; ++j) o[j] = e->b0_hz[d.masked ? e->voxels[j] : j];
   }
+  if (d.has_b0 || d.has_q) memcpy(at(l.t), e->t, sizeof(double) * d.K);
   if (d.masked) {
-    h->vxy.resize(d.V);
+    int32_t* o = (int32_t*)at(l.vxy);
     for (int j = 0; j < d.V; ++j) {
-      const int v = e->voxels[j], iy = v / d.nx, ix = v - iy * d.nx;
-      h->vxy[j] = (iy << 16) | ix;
+      const int v = e->voxels[j], iy = v / d.nx;
+      o[j] = (iy << 16) | (v - iy * d.nx);
     }
   }
+  memcpy(at(l.k), e->k, sizeof(double) * 2 * d.K);
+  if (e->species_hz) memcpy(at(l.hz), e->species_hz, sizeof(double) * d.S);
+}
+
+template <typename T>
+EncDev<T> enc_at(const Dims& d, const TableLayout& l, void* dev, const int* vxy, bool with_t) {
+  char* b = (char*)dev;
+  EncDev<T> ev{};
+  ev.px = (const T*)(b + l.px);
+  ev.py = (const T*)(b + l.py);
+  ev.q = d.has_q ? (const T*)(b + l.q) : nullptr;
+  ev.coil = d.has_coil ? (const T*)(b + l.coil) : nullptr;
+  ev.b0 = d.has_b0 ? (const T*)(b + l.b0) : nullptr;
+  ev.t = with_t ? (const T*)(b + l.t) : nullptr;
+  ev.vxy = vxy;
+  ev.nx = d.nx;
+  ev.ny = d.ny;
+  ev.S = d.S;
+  ev.C = d.C;
+  ev.K = d.K;
+  ev.V = d.V;
+  ev.M = d.M;
+  ev.N = d.N;
+  return ev;
 }
 
 // The power of two that brings E's largest entry into [2^13, 2^14.5): every
 // phase factor has modulus 1, so |E| is the coil sensitivity.
-int e_shift(const HostTables& h) {
-  if (h.coil.empty()) return 13;
+int e_shift(const pinv_encoding* e, const Dims& d) {
+  if (!d.has_coil) return 13;
   double mx = 0.0;
-  for (double v : h.coil) mx = std::max(mx, fabs(v));
+  for (size_t i = 0; i < 2 * (size_t)d.C * d.Vg; ++i) mx = std::max(mx, fabs(e->coil[i]));
   if (!(mx > 0.0) || !isfinite(mx)) return 0;
   return std::max(-100, std::min(100, 13 - ilogb(mx)));
-}
-
-// Bytes of the tables as type T in one device buffer (each table 256-aligned).
-template <typename T>
-size_t tables_bytes(const HostTables& h) {
-  size_t tot = 0;
-  for (size_t n : {h.px.size(), h.py.size(), h.q.size(), h.coil.size(), h.b0.size(), h.t.size()})
-    tot += align256(n * sizeof(T));
-  return tot + align256(h.vxy.size() * sizeof(int32_t));
-}
-
-// Converts the tables to T into `host` (pinned staging, tables_bytes<T> long)
-// and copies them to `dev` on s.
-template <typename T>
-pinv_status upload_tables(const HostTables& h, const Dims& d, hipStream_t s, void* host, void* dev,
-                          EncDev<T>* ev) {
-  const size_t n_px = h.px.size(), n_py = h.py.size(), n_q = h.q.size(), n_c = h.coil.size(),
-               n_b = h.b0.size(), n_t = h.t.size();
-  size_t off[6], tot = 0;
-  const size_t ns[6] = {n_px, n_py, n_q, n_c, n_b, n_t};
-  for (int i = 0; i < 6; ++i) {
-    off[i] = tot;
-    tot += align256(ns[i] * sizeof(T));
-  }
-  const std::vector<double>* src[6] = {&h.px, &h.py, &h.q, &h.coil, &h.b0, &h.t};
-  for (int i = 0; i < 6; ++i) {
-    T* dst = (T*)((char*)host + off[i]);
-    for (size_t j = 0; j < ns[i]; ++j) dst[j] = (T)(*src[i])[j];
-  }
-  const size_t off_vxy = tot;
-  if (!h.vxy.empty()) {
-    memcpy((char*)host + off_vxy, h.vxy.data(), h.vxy.size() * sizeof(int32_t));
-    tot += align256(h.vxy.size() * sizeof(int32_t));
-  }
-  HIPCHK(hipMemcpyAsync(dev, host, tot, hipMemcpyHostToDevice, s));
-  char* b = (char*)dev;
-  ev->px = (const T*)(b + off[0]);
-  ev->py = (const T*)(b + off[1]);
-  ev->q = n_q ? (const T*)(b + off[2]) : nullptr;
-  ev->coil = n_c ? (const T*)(b + off[3]) : nullptr;
-  ev->b0 = n_b ? (const T*)(b + off[4]) : nullptr;
-  ev->t = n_t ? (const T*)(b + off[5]) : nullptr;
-  ev->vxy = h.vxy.empty() ? nullptr : (const int*)(b + off_vxy);
-  ev->nx = d.nx;
-  ev->ny = d.ny;
-  ev->S = d.S;
-  ev->C = d.C;
-  ev->K = d.K;
-  ev->V = d.V;
-  ev->M = d.M;
-  ev->N = d.N;
-  return PINV_OK;
 }
 
 // Record that work just enqueued on `s` reads the plan.  Events whose work
@@ -451,7 +427,12 @@ struct BuildForm {
   int route = PINV_ROUTE_CHOLESKY;
   int trunc = PINV_TRUNC_NONE;
   double trunc_value = 0.0;
+  int key_bits = 0;    // the options' part of the cache key
 };
+
+uint64_t form_key(const pinv_encoding* e, const Dims& d, double lam, int prec, const BuildForm& f) {
+  return plan_key(e, d, lam, prec, f.key_bits, f.trunc_value);
+}
 
 // Sweep cap of the Jacobi eigensolver.  Its Grams are ill conditioned with
 // clustered small eigenvalues, so the off-diagonal mass falls only a few times
@@ -697,8 +678,8 @@ pinv_status pinv_context_destroy(pinv_context* c) {
   return PINV_OK;
 }
 
-// Validate a build request and derive the absolute shift, the cache key and
-// the resolved options.
+// Validate a build request and derive the absolute shift, the cache key (unless
+// key_out is null) and the resolved options.
 static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o, Dims* d,
                                double* lam_out, uint64_t* key_out, BuildForm* form) {
   if (!o) return fail(PINV_ERR_INVALID, "NULL options");
@@ -799,7 +780,8 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);
-  *key_out = plan_key(e, *d, lam, o->prec, bits, form->trunc_value);
+  form->key_bits = bits;
+  if (key_out) *key_out = form_key(e, *d, lam, o->prec, *form);
   return PINV_OK;
 }
 
@@ -904,14 +886,16 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   if (!c || !o || !out) return fail(PINV_ERR_INVALID, "NULL argument");
   Dims d;
   double lam;
-  uint64_t key;
+  uint64_t key = 0;
   BuildForm form;
-  pinv_status st = check_build(e, o, &d, &lam, &key, &form);
+  // the key hashes every byte of the encoding (about a millisecond per megabyte):
+  // an uncached build does so once its work is enqueued
+  const bool uncached = (o->flags & PINV_FLAG_UNCACHED) != 0;
+  pinv_status st = check_build(e, o, &d, &lam, uncached ? nullptr : &key, &form);
   if (st != PINV_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(enter_device(c->device));
 
-  const bool uncached = (o->flags & PINV_FLAG_UNCACHED) != 0;
   std::lock_guard<std::mutex> g(c->mu);
   auto hit = uncached ? c->cache.end() : c->cache.find(key);
   if (hit != c->cache.end()) {
@@ -937,7 +921,6 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
 
   pinv_plan* p = new pinv_plan();
   p->ctx = c;
-  p->key = key;
   p->prec = o->prec;
   p->N = d.N;
   p->M = d.M;
@@ -963,8 +946,6 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     return rs;
   };
 
-  HostTables ht;
-  build_tables(e, d, &ht);
   const size_t N = d.N, M = d.M;
   const bool f64 = o->prec == PINV_FP64;
   const size_t cs = f64 ? 16 : 8;
@@ -993,28 +974,34 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   } while (0)
 
   // Plan buffers come stream-ordered from the context's plan pool and the
-  // tables are staged through its reusable pinned buffer: a build in steady
+  // encoding is staged through its reusable pinned buffer: a build in steady
   // state maps no new memory while earlier work still runs on the device.
   p->pooled = c->plan_pool != nullptr;
-  const size_t b64 = tables_bytes<double>(ht), b32 = f64 ? 0 : tables_bytes<float>(ht);
-  BCHK(plan_malloc(&p->tab64, b64, c, s));
-  if (!f64) BCHK(plan_malloc(&p->tab32, b32, c, s));
+  const TableLayout t64 = table_layout(e, d, sizeof(double), true);
+  const TableLayout t32 = table_layout(e, d, sizeof(float), false);
+  BCHK(plan_malloc(&p->tab64, t64.bytes, c, s));
+  if (!f64) BCHK(plan_malloc(&p->tab32, t32.bytes, c, s));
+  char* const tab = (char*)p->tab64;
+  const int* vxy = d.masked ? (const int*)(tab + t64.vxy) : nullptr;
+  p->e64 = enc_at<double>(d, t64, p->tab64, vxy, d.has_b0 || d.has_q);
+  if (!f64) p->e32 = enc_at<float>(d, t32, p->tab32, vxy, d.has_b0);
   {
+    const size_t bytes = t64.bytes - t64.raw;
     std::lock_guard<std::mutex> g(c->stage_mu);
     BCHK(hipEventSynchronize(c->stage_ev));   // earlier copies out of the staging buffer are done
-    if (c->stage_bytes < b64 + b32) {
+    if (c->stage_bytes < bytes) {
       if (c->stage) (void)hipHostFree(c->stage);
       c->stage = nullptr;
       c->stage_bytes = 0;
-      BCHK(hipHostMalloc(&c->stage, b64 + b32, hipHostMallocDefault));
-      c->stage_bytes = b64 + b32;
+      BCHK(hipHostMalloc(&c->stage, bytes, hipHostMallocDefault));
+      c->stage_bytes = bytes;
     }
-    st = upload_tables<double>(ht, d, s, c->stage, p->tab64, &p->e64);
-    if (st == PINV_OK && !f64)
-      st = upload_tables<float>(ht, d, s, (char*)c->stage + b64, p->tab32, &p->e32);
-    if (st == PINV_OK) BCHK(hipEventRecord(c->stage_ev, s));
+    stage_tables(e, d, t64, (char*)c->stage);
+    BCHK(hipMemcpyAsync(tab + t64.raw, c->stage, bytes, hipMemcpyHostToDevice, s));
+    BCHK(hipEventRecord(c->stage_ev, s));
   }
-  if (st != PINV_OK) return cleanup(st);
+  BCHK(launch_tables(p->e64, f64 ? nullptr : &p->e32, (const double*)(tab + t64.k),
+                     e->species_hz ? (const double*)(tab + t64.hz) : nullptr, s));
   for (auto& ev : p->ev) BCHK(hipEventCreate(&ev));
   BCHK(plan_malloc((void**)&p->info, sizeof(int), c, s));
   BCHK(hipMemsetAsync(p->info, 0, sizeof(int), s));
@@ -1171,7 +1158,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     // bytes of its 16 N^2), conj(E) in R until R is formed
     const int64_t Np = half_cols(N), fit = (int64_t)(N * M) / Np;
     const int64_t slab = fit >= (int64_t)M ? (int64_t)M : fit / 128 * 128;
-    BCHK(launch_trmm_wh(p->e32, (const double*)L64, G, p->R, slab, e_shift(ht), W, s));
+    BCHK(launch_trmm_wh(p->e32, (const double*)L64, G, p->R, slab, e_shift(e, d), W, s));
     BCHK(hipEventRecord(p->ev[3], s));
     BCHK(launch_trmm_rh((const double*)L64, G, W, (float*)p->R, d.N, d.M, s));
   } else {
@@ -1193,8 +1180,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   }
   L64 = nullptr;
 #undef BCHK
-  // the pinned staging buffers stay with the plan until its build has finished
-
+  p->key = uncached ? form_key(e, d, lam, o->prec, form) : key;
   p->bytes = plan_resident(d, o->prec, no_r);
   c->used += p->bytes;
   if (uncached) {

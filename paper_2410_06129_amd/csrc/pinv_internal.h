@@ -84,6 +84,11 @@ struct Scratch {
   }
 };
 
+// The tables of an encoding: Px, Py and Q into e's (and f's, rounded) arrays from
+// the trajectory k [K][2], e.t and the species frequencies hz [S] (null: 0 Hz), and
+// f's coil, b0 and t from e's, all on the device.  e.t is set whenever e.q is.
+hipError_t launch_tables(const EncDev<double>& e, const EncDev<float>* f, const double* k,
+                         const double* hz, hipStream_t s);
 template <typename T> hipError_t launch_gram(const EncDev<T>& e, double* G, int flush, hipStream_t s);
 template <typename T> hipError_t launch_gram_shared(const EncDev<T>& e, double* G, hipStream_t s);
 // Cholesky of A + lam I (FP64, in place) with L^-1 formed alongside in Li
