@@ -390,11 +390,11 @@ pinv_status pinv_plan_copy_buffer(const pinv_plan *p, int32_t which, void *dst, 
 
 /* Drop one reference.  The last reference held by neither a caller nor the
  * cache frees the plan without waiting on the host: its buffers return to the
- * context's plan pool once the build and every apply, forward, metric and copy
+ * context once the build and every apply, forward, metric and copy
  * enqueued on the plan, on whatever stream, have completed. */
 pinv_status pinv_plan_release(pinv_plan *p);
 
-/* Hand device memory that the context's stream-ordered pools keep after
+/* Hand device memory that the context keeps after
  * completed work (refinement scratch, build workspaces, buffers of released
  * plans) back to the device.  The library does this by itself for scratch and
  * workspaces when less than a quarter of the device is free, and for all of it

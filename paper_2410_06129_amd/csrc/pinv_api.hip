@@ -48,6 +48,115 @@ static hipError_t enter_device(int device) {
   } while (0)
 
 // ---------------------------------------------------------------------------
+// device memory kept by a context
+// ---------------------------------------------------------------------------
+namespace pinv {
+
+// Block sizes: powers of two up to 1 MB (few, so that small buffers are shared by
+// encodings of similar sizes), whole 2 MB beyond.
+size_t DeviceCache::rounded(size_t bytes) {
+  size_t n = 4096;
+  if (bytes > (1u << 20)) return (bytes + (2u << 20) - 1) & ~size_t((2u << 20) - 1);
+  while (n < bytes) n *= 2;
+  return n;
+}
+
+hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
+  const size_t need = rounded(bytes);
+  std::lock_guard<std::mutex> g(mu_);
+  const size_t most = need + need / (need > (256u << 20) ? 64 : 8);
+  for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
+    Idle& b = it->second;
+    if (b.ev) {
+      const hipError_t q = hipEventQuery(b.ev);
+      (void)hipGetLastError();
+      if (q != hipSuccess) {
+        if (b.s != s) continue;
+        // the same stream, or another one that took over its handle
+        const hipError_t w = hipStreamWaitEvent(s, b.ev, 0);
+        if (w != hipSuccess) return w;
+      }
+      events_.push_back(b.ev);
+    }
+    *p = b.p;
+    live_[b.p] = it->first;
+    idle_.erase(it);
+    return hipSuccess;
+  }
+  const hipError_t e = hipMalloc(p, need);
+  if (e == hipSuccess) live_[*p] = need;
+  return e;
+}
+
+void DeviceCache::add(void* p, hipEvent_t ev, hipStream_t s) {
+  auto it = live_.find(p);
+  if (it == live_.end()) return;
+  idle_.emplace(it->second, Idle{p, ev, s});
+  live_.erase(it);
+}
+
+hipError_t DeviceCache::put(void* p, hipStream_t s) {
+  std::lock_guard<std::mutex> g(mu_);
+  hipEvent_t ev = nullptr;
+  hipError_t e = hipSuccess;
+  if (!events_.empty()) {
+    ev = events_.back();
+    events_.pop_back();
+  } else {
+    e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  }
+  if (e == hipSuccess) e = hipEventRecord(ev, s);
+  if (e != hipSuccess) {   // no event to order a reuse by: wait for the stream instead
+    if (ev) (void)hipEventDestroy(ev);
+    ev = nullptr;
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(s);
+  }
+  add(p, ev, s);
+  return e;
+}
+
+void DeviceCache::put_idle(void* p) {
+  std::lock_guard<std::mutex> g(mu_);
+  add(p, nullptr, nullptr);
+}
+
+void DeviceCache::trim(bool wait) {
+  std::lock_guard<std::mutex> g(mu_);
+  for (auto it = idle_.begin(); it != idle_.end();) {
+    hipEvent_t ev = it->second.ev;
+    if (ev && (wait ? hipEventSynchronize(ev) : hipEventQuery(ev)) != hipSuccess && !wait) {
+      ++it;
+      continue;
+    }
+    (void)hipFree(it->second.p);
+    if (ev) (void)hipEventDestroy(ev);
+    it = idle_.erase(it);
+  }
+  (void)hipGetLastError();
+  if (wait) {
+    for (hipEvent_t e : events_) (void)hipEventDestroy(e);
+    events_.clear();
+  }
+}
+
+void DeviceCache::release_all() {
+  trim(true);
+  std::lock_guard<std::mutex> g(mu_);
+  for (auto& kv : live_) (void)hipFree(kv.first);
+  live_.clear();
+}
+
+size_t DeviceCache::idle_bytes() {
+  std::lock_guard<std::mutex> g(mu_);
+  size_t n = 0;
+  for (auto& kv : idle_) n += kv.first;
+  return n;
+}
+
+}  // namespace pinv
+
+// ---------------------------------------------------------------------------
 // objects
 // ---------------------------------------------------------------------------
 struct pinv_plan {
@@ -78,7 +187,6 @@ struct pinv_plan {
   int sweeps = 0;            // Jacobi sweeps (eigenvalue route)
   void* spec = nullptr;      // eigenvalues of E^H E, largest first (eigenvalue route)
   int* info = nullptr;
-  bool pooled = false;             // device buffers from the context's plan pool
   size_t bytes = 0;
   hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   // One event per use of the plan that may still be in flight (applies,
@@ -96,17 +204,16 @@ struct pinv_plan {
 struct pinv_context {
   int device = 0;
   hipStream_t aux_nb = nullptr;   // the factorisation's look-ahead stream (non-blocking)
-  // Buffers of released plans whose last uses may still run: freed into the
-  // plan pool once all their events have completed (see free_plan_memory).
+  // Buffers of released plans whose last uses may still run: handed to
+  // plan_mem once all their events have completed (see free_plan_memory).
   struct PendingFree {
     std::vector<void*> bufs;
     std::vector<hipEvent_t> evs;
   };
   std::mutex free_mu;
   std::vector<PendingFree> pending;
-  hipMemPool_t build_pool = nullptr;   // build workspaces (Gram, FP64 factor, W)
-  hipMemPool_t plan_pool = nullptr;    // plan buffers (R, L^-1, Gram, tables)
-  hipMemPool_t apply_pool = nullptr;   // packed slabs of many-frame FP32 applies
+  DeviceCache mem;        // build workspaces (Gram, FP64 factor, W) and scratch of applies
+  DeviceCache plan_mem;   // plan buffers (R, L^-1, Gram, tables)
   // pinned staging for table uploads, reused by every build of the context:
   // stage_ev marks the completion of the last copies out of it
   std::mutex stage_mu;
@@ -342,41 +449,28 @@ hipError_t note_use(const pinv_plan* pc, hipStream_t s) {
   return hipEventRecord(ev, s);
 }
 
-// Return a plan's buffers.  Pooled buffers, with the build's and every
-// recorded use's events, go on the context's pending list without waiting on
-// the host or on any stream; drain_frees hands them to the plan pool once
-// those events have completed, on the stream of the allocation that needs
-// the memory, where the pool can reuse it at once.  No stream waits on the
-// events: with few hardware queues per process a wait would also hold back
-// unrelated work sharing the waiting stream's queue.  Buffers from hipMalloc
-// (no plan pool) are freed after the device has finished with them.
+// Return a plan's buffers: with the build's and every recorded use's events they
+// go on the context's pending list without waiting on the host or on any stream;
+// drain_frees hands them to the context's memory once those events have completed.
+// No stream waits on the events: with few hardware queues per process a wait would
+// also hold back unrelated work sharing the waiting stream's queue.
 void free_plan_memory(pinv_plan* p) {
   pinv_context* c = p->ctx;
   void* const bufs[] = {p->tab32, p->tab64, p->R, p->Linv, p->gram, (void*)p->info, p->spec};
-  if (p->pooled) {
-    pinv_context::PendingFree f;
-    for (void* q : bufs)
-      if (q) f.bufs.push_back(q);
-    for (hipEvent_t& e : p->ev)
-      if (e) f.evs.push_back(e), e = nullptr;
-    for (hipEvent_t e : p->uses) f.evs.push_back(e);
-    p->uses.clear();
-    std::lock_guard<std::mutex> g(c->free_mu);
-    c->pending.push_back(std::move(f));
-    return;
-  }
-  (void)hipDeviceSynchronize();
+  pinv_context::PendingFree f;
   for (void* q : bufs)
-    if (q) (void)hipFree(q);
-  for (hipEvent_t e : p->ev)
-    if (e) (void)hipEventDestroy(e);
-  for (hipEvent_t e : p->uses) (void)hipEventDestroy(e);
+    if (q) f.bufs.push_back(q);
+  for (hipEvent_t& e : p->ev)
+    if (e) f.evs.push_back(e), e = nullptr;
+  for (hipEvent_t e : p->uses) f.evs.push_back(e);
   p->uses.clear();
+  std::lock_guard<std::mutex> g(c->free_mu);
+  c->pending.push_back(std::move(f));
 }
 
-// Free the pending buffers whose events have all completed (all of them, after
-// waiting on the host, with `wait`) into the plan pool, stream-ordered on s.
-void drain_frees(pinv_context* c, hipStream_t s, bool wait) {
+// Hand over the pending buffers whose events have all completed (all of them,
+// after waiting on the host, with `wait`).
+void drain_frees(pinv_context* c, bool wait) {
   std::lock_guard<std::mutex> g(c->free_mu);
   for (size_t i = 0; i < c->pending.size();) {
     pinv_context::PendingFree& f = c->pending[i];
@@ -394,7 +488,7 @@ void drain_frees(pinv_context* c, hipStream_t s, bool wait) {
       ++i;
       continue;
     }
-    for (void* q : f.bufs) (void)hipFreeAsync(q, s);
+    for (void* q : f.bufs) c->plan_mem.put_idle(q);
     for (hipEvent_t e : f.evs) (void)hipEventDestroy(e);
     c->pending.erase(c->pending.begin() + i);
   }
@@ -613,37 +707,13 @@ pinv_status pinv_context_create(int device, size_t budget, pinv_context** out) {
     return fail(PINV_ERR_DEVICE, "cannot create the library's streams");
   }
   c->aux_nb = ds.aux_nb;
-  // Keep freed stream-ordered allocations (build workspaces, scratch) mapped
-  // across synchronisations: the pool's default release threshold of 0 hands
-  // them back at every synchronising call, and the next build then pays for
-  // mapping W afresh inside its first kernel.  Memory goes back to the device
-  // only through the explicit trims (pinv_plan_wait, pinv_context_trim).
+  // Keep the metrics' freed stream-ordered allocations mapped across
+  // synchronisations (the default pool's release threshold of 0 hands them back at
+  // every one); they go back through the explicit trims.
   hipMemPool_t pool;
   uint64_t keep = UINT64_MAX;
   if (hipDeviceGetDefaultMemPool(&pool, device) == hipSuccess)
     (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
-  // Build workspaces come from a pool of their own, so the per-call scratch of
-  // applies and refinement (default pool) cannot split a freed multi-GB
-  // workspace and force the next build to map a new one.
-  hipMemPoolProps props;
-  memset(&props, 0, sizeof(props));
-  props.allocType = hipMemAllocationTypePinned;
-  props.handleTypes = hipMemHandleTypeNone;
-  props.location.type = hipMemLocationTypeDevice;
-  props.location.id = device;
-  props.maxSize = tot;
-  if (hipMemPoolCreate(&c->build_pool, &props) == hipSuccess)
-    (void)hipMemPoolSetAttribute(c->build_pool, hipMemPoolAttrReleaseThreshold, &keep);
-  else
-    c->build_pool = nullptr, (void)hipGetLastError();
-  if (hipMemPoolCreate(&c->plan_pool, &props) == hipSuccess)
-    (void)hipMemPoolSetAttribute(c->plan_pool, hipMemPoolAttrReleaseThreshold, &keep);
-  else
-    c->plan_pool = nullptr, (void)hipGetLastError();
-  if (hipMemPoolCreate(&c->apply_pool, &props) == hipSuccess)
-    (void)hipMemPoolSetAttribute(c->apply_pool, hipMemPoolAttrReleaseThreshold, &keep);
-  else
-    c->apply_pool = nullptr, (void)hipGetLastError();
   if (hipEventCreateWithFlags(&c->stage_ev, hipEventDisableTiming) != hipSuccess) {
     pinv_context_destroy(c);
     return fail(PINV_ERR_DEVICE, "cannot create the staging event");
@@ -665,13 +735,9 @@ pinv_status pinv_context_destroy(pinv_context* c) {
     c->lru.clear();
     c->cache.clear();
   }
-  if (c->aux_nb) {
-    drain_frees(c, c->aux_nb, true);
-    (void)hipStreamSynchronize(c->aux_nb);
-  }
-  if (c->build_pool) (void)hipMemPoolDestroy(c->build_pool);
-  if (c->plan_pool) (void)hipMemPoolDestroy(c->plan_pool);
-  if (c->apply_pool) (void)hipMemPoolDestroy(c->apply_pool);
+  drain_frees(c, true);
+  c->mem.release_all();
+  c->plan_mem.release_all();
   if (c->stage_ev) (void)hipEventDestroy(c->stage_ev);
   if (c->stage) (void)hipHostFree(c->stage);
   delete c;   // the library's streams stay for the next context
@@ -798,85 +864,73 @@ pinv_status pinv_encoding_key(const pinv_encoding* e, const pinv_build_opts* o, 
   return PINV_OK;
 }
 
-// Return memory that stream-ordered frees left in the pools to the device, so
-// that allocations outside them (the caller's tensors) can use it: per-call
-// scratch (the device's default pool) and build workspaces (the build pool),
-// and with `plans` also freed plan buffers (the plan pool).  Unforced, only
-// when less than a quarter of the device is free: re-mapping a freed multi-GB
-// buffer costs the next build milliseconds inside its first kernel and slows
-// whatever else runs meanwhile.  Plan memory is handed back only on request or
-// when a plan or workspace allocation fails, so later plans reuse it.
-static void trim_pool(pinv_context* c, bool force, bool plans) {
+// Give idle memory of the context back to the device, so that allocations outside
+// it (the caller's tensors) can use it: workspaces and scratch, and with `plans`
+// also released plans' buffers.  Unforced, only when less than a quarter of the
+// device is free and at least 2% of it is idle here: mapping a multi-GB buffer anew
+// costs the next build milliseconds and slows whatever else runs meanwhile.  Plan
+// memory is handed back only on request or when an allocation fails, so later
+// plans reuse it.
+static void trim_memory(pinv_context* c, bool force, bool plans) {
   size_t fr = 0, tot = 0;
-  if (!force && hipMemGetInfo(&fr, &tot) == hipSuccess && fr >= tot / 4) return;
-  hipMemPool_t pool;
+  if (!force && hipMemGetInfo(&fr, &tot) == hipSuccess &&
+      (fr >= tot / 4 || c->mem.idle_bytes() < tot / 50))
+    return;
+  hipMemPool_t pool;   // metrics' temporaries
   if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
-  if (c->build_pool) (void)hipMemPoolTrimTo(c->build_pool, 0);
-  if (c->apply_pool) (void)hipMemPoolTrimTo(c->apply_pool, 0);
-  if (plans && c->plan_pool) {
-    // released plans whose work has finished go back as well
-    drain_frees(c, c->aux_nb, false);
-    (void)hipStreamSynchronize(c->aux_nb);
-    (void)hipMemPoolTrimTo(c->plan_pool, 0);
+  c->mem.trim(false);
+  if (plans) {
+    drain_frees(c, false);
+    c->plan_mem.trim(false);
   }
 }
 
-// Scratch and workspaces back to the device under memory pressure (the
-// serving loop calls this after each batch).
-extern "C++" void pinv_context_trim_scratch(pinv_context* c) { trim_pool(c, false, false); }
+// Idle memory back to the device under memory pressure (the serving loop calls
+// this after each batch).
+extern "C++" void pinv_context_trim_scratch(pinv_context* c) { trim_memory(c, false, false); }
 
-// Scratch reclaim for calls that allocate from the default pool: the stream's
-// own frees complete, then every pool of the context hands its unused memory
-// (build workspaces and released plans included) back to the device.
-static void reclaim_pools(void* arg, hipStream_t s) {
+// After an allocation failed: the stream's own work completes, then all idle
+// memory (build workspaces and released plans included) goes back to the device.
+static void reclaim_memory(void* arg, hipStream_t s) {
   (void)hipStreamSynchronize(s);
-  trim_pool((pinv_context*)arg, true, true);
+  trim_memory((pinv_context*)arg, true, true);
 }
 
-// A stream-ordered allocation from the default pool for a call's own
-// temporaries, tried once more after reclaim_pools when memory is short.
+// A stream-ordered allocation from the default pool for a metric's own
+// temporaries, tried once more after reclaim_memory when memory is short.
 static hipError_t pool_alloc(pinv_context* c, void** ptr, size_t bytes, hipStream_t s) {
   hipError_t e = hipMallocAsync(ptr, bytes, s);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
-    reclaim_pools(c, s);
+    reclaim_memory(c, s);
     e = hipMallocAsync(ptr, bytes, s);
   }
   return e;
 }
 
-// A build workspace, stream-ordered on s, from the context's build pool.
+// A build workspace; when the device is out of memory, idle memory is handed back
+// and the allocation tried once more.
 static hipError_t workspace_alloc(void** ptr, size_t bytes, pinv_context* c, hipStream_t s) {
-  auto once = [&]() {
-    return c->build_pool ? hipMallocFromPoolAsync(ptr, bytes, c->build_pool, s)
-                         : hipMallocAsync(ptr, bytes, s);
-  };
-  hipError_t e = once();
+  hipError_t e = c->mem.get(ptr, bytes, s);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
-    (void)hipStreamSynchronize(s);
-    trim_pool(c, true, true);
-    e = once();
+    reclaim_memory(c, s);
+    e = c->mem.get(ptr, bytes, s);
   }
   return e;
 }
 
-// A plan buffer, stream-ordered on s from the context's plan pool (plain
-// hipMalloc if the pool could not be created); when the device is out of
-// memory, freed pool memory is handed back and the allocation tried once more.
+// A plan buffer; when the device is out of memory, released plans' work is waited
+// for and their memory handed back as well.
 static hipError_t plan_malloc(void** ptr, size_t bytes, pinv_context* c, hipStream_t s) {
-  auto once = [&]() {
-    return c->plan_pool ? hipMallocFromPoolAsync(ptr, bytes, c->plan_pool, s) : hipMalloc(ptr, bytes);
-  };
-  drain_frees(c, s, false);   // released plans' memory, reusable on s at once
-  hipError_t e = once();
+  drain_frees(c, false);   // released plans' memory, reusable at once
+  hipError_t e = c->plan_mem.get(ptr, bytes, s);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     (void)hipStreamSynchronize(s);
-    drain_frees(c, s, true);
-    (void)hipStreamSynchronize(s);
-    trim_pool(c, true, true);
-    e = once();
+    drain_frees(c, true);
+    trim_memory(c, true, true);
+    e = c->plan_mem.get(ptr, bytes, s);
   }
   return e;
 }
@@ -961,22 +1015,21 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     if (he != hipSuccess) {                                                           \
       fail(he == hipErrorOutOfMemory ? PINV_ERR_NOMEM : PINV_ERR_DEVICE,              \
            std::string(#expr) + ": " + hipGetErrorString(he));                        \
-      if (G) (void)hipFreeAsync(G, s);                                                \
-      if (L64 && L64 != p->Linv) (void)hipFreeAsync(L64, s);                          \
-      if (W) (void)hipFreeAsync(W, s);                                                \
-      if (Z) (void)hipFreeAsync(Z, s);                                                \
-      if (PW) (void)hipFreeAsync(PW, s);                                              \
-      if (LS) (void)hipFreeAsync(LS, s);                                              \
-      if (LHS) (void)hipFreeAsync(LHS, s);                                            \
-      if (ES) (void)hipFreeAsync(ES, s);                                              \
+      if (G) (void)c->mem.put(G, s);                                                \
+      if (L64 && L64 != p->Linv) (void)c->mem.put(L64, s);                          \
+      if (W) (void)c->mem.put(W, s);                                                \
+      if (Z) (void)c->mem.put(Z, s);                                                \
+      if (PW) (void)c->mem.put(PW, s);                                              \
+      if (LS) (void)c->mem.put(LS, s);                                              \
+      if (LHS) (void)c->mem.put(LHS, s);                                            \
+      if (ES) (void)c->mem.put(ES, s);                                              \
       return cleanup(he == hipErrorOutOfMemory ? PINV_ERR_NOMEM : PINV_ERR_DEVICE);   \
     }                                                                                 \
   } while (0)
 
-  // Plan buffers come stream-ordered from the context's plan pool and the
-  // encoding is staged through its reusable pinned buffer: a build in steady
-  // state maps no new memory while earlier work still runs on the device.
-  p->pooled = c->plan_pool != nullptr;
+  // Plan buffers come from the context's memory and the encoding is staged through
+  // its reusable pinned buffer: a build in steady state maps no new memory while
+  // earlier work still runs on the device.
   const TableLayout t64 = table_layout(e, d, sizeof(double), true);
   const TableLayout t32 = table_layout(e, d, sizeof(float), false);
   BCHK(plan_malloc(&p->tab64, t64.bytes, c, s));
@@ -1023,7 +1076,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   int64_t slab = 0;
   if (b3 && !no_r && !p->right && form.route == PINV_ROUTE_CHOLESKY) {
     // split-packed L^-1 and L^-H rows and the conj(E) slab, mapped before the
-    // first stage so no stage's interval includes growing the pool
+    // first stage so no stage's interval includes mapping them
     const size_t Np = sp_cols(N);
     slab = e_slab_rows(N, M);
     BCHK(workspace_alloc(&LS, 8 * N * Np, c, s));
@@ -1039,7 +1092,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     // offset-grid PSF times the coil cross-products, written to the workspace
     // and the kept Gram (both full Hermitian)
     BCHK(launch_psf_gram(p->e64, PW, (double*)G, (double*)p->gram, s));
-    BCHK(hipFreeAsync(PW, s));
+    BCHK(c->mem.put(PW, s));
     PW = nullptr;
   } else {
     if (p->right)
@@ -1073,16 +1126,16 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
         r = launch_eig_select(Af, Vf, (int)N, form.trunc, form.trunc_value, lam, (double*)p->spec,
                               (double*)L64, p->info, EW, &p->rank, s);
       for (void* q : {EW, V2, V, A2})
-        if (q) (void)hipFreeAsync(q, s);
+        if (q) (void)c->mem.put(q, s);
       return r;
     };
     BCHK(eig());
     if (p->sweeps < 0) {
       fail(PINV_ERR_UNSUPPORTED, "the Jacobi eigendecomposition did not converge in " +
                                      std::to_string(kMaxJacobiSweeps) + " sweeps");
-      (void)hipFreeAsync(G, s);
-      if (!f64) (void)hipFreeAsync(L64, s);
-      if (W) (void)hipFreeAsync(W, s);
+      (void)c->mem.put(G, s);
+      if (!f64) (void)c->mem.put(L64, s);
+      if (W) (void)c->mem.put(W, s);
       return cleanup(PINV_ERR_UNSUPPORTED);
     }
     if (!f64) BCHK(launch_to_f32((const double*)L64, (float*)p->Linv, Gd * Gd, s));
@@ -1145,13 +1198,13 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     BCHK(launch_sp_pack<double>((const double*)L64, (int64_t)N, d.N, d.N, false, false, LS, s));
     BCHK(launch_sp_pack<double>((const double*)L64, (int64_t)N, d.N, d.N, true, true, LHS, s));
     BCHK(launch_trmm_w_sp(p->e32, LS, W, ES, slab, s));
-    BCHK(hipFreeAsync(ES, s));
+    BCHK(c->mem.put(ES, s));
     ES = nullptr;
     BCHK(hipEventRecord(p->ev[3], s));
     BCHK(launch_trmm_r_sp(W, LHS, p->R, d.N, d.M, s));
-    BCHK(hipFreeAsync(LHS, s));
+    BCHK(c->mem.put(LHS, s));
     LHS = nullptr;
-    BCHK(hipFreeAsync(LS, s));
+    BCHK(c->mem.put(LS, s));
     LS = nullptr;
   } else if (form.half) {
     // the packed factor in the Gram workspace (dead once factored; 12 N Np + 8 N
@@ -1169,14 +1222,14 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   }
   }   // route
   BCHK(hipEventRecord(p->ev[4], s));
-  if (W) BCHK(hipFreeAsync(W, s));
+  if (W) BCHK(c->mem.put(W, s));
   W = nullptr;
-  if (Z) BCHK(hipFreeAsync(Z, s));
+  if (Z) BCHK(c->mem.put(Z, s));
   Z = nullptr;
-  BCHK(hipFreeAsync(G, s));
+  BCHK(c->mem.put(G, s));
   G = nullptr;
   if (!f64) {
-    BCHK(hipFreeAsync(L64, s));
+    BCHK(c->mem.put(L64, s));
   }
   L64 = nullptr;
 #undef BCHK
@@ -1200,7 +1253,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
 extern "C" pinv_status pinv_context_trim(pinv_context* c) {
   if (!c) return fail(PINV_ERR_INVALID, "context is NULL");
   HIPCHK(enter_device(c->device));
-  trim_pool(c, true, true);
+  trim_memory(c, true, true);
   return PINV_OK;
 }
 
@@ -1209,7 +1262,7 @@ pinv_status pinv_plan_wait(pinv_plan* p) {
   if (!p->waited) {
     HIPCHK(enter_device(p->ctx->device));
     HIPCHK(hipEventSynchronize(p->ev[4]));
-    trim_pool(p->ctx, false, false);
+    trim_memory(p->ctx, false, false);
     HIPCHK(hipMemcpy(&p->info_host, p->info, sizeof(int), hipMemcpyDeviceToHost));
     for (int i = 0; i < 4; ++i) HIPCHK(hipEventElapsedTime(&p->stage_ms[i], p->ev[i], p->ev[i + 1]));
     if (p->no_r) p->stage_ms[2] = p->stage_ms[3] = 0.f;   // no W or R was formed
@@ -1529,10 +1582,10 @@ pinv_status pinv_apply_grouped(pinv_context* c, int32_t n, const pinv_apply_item
   if (refine_steps < 0 || refine_steps > 4) return fail(PINV_ERR_INVALID, "refine_steps in 0..4");
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(enter_device(c->device));
-  Scratch sc;   // stream-ordered allocations from the default pool
-  sc.reclaim = reclaim_pools;
+  Scratch sc;   // blocks of the context's memory
+  sc.cache = &c->mem;
+  sc.reclaim = reclaim_memory;
   sc.reclaim_arg = c;
-  sc.large = c->apply_pool;
   const pinv_status st = apply_items(c, n, items, refine_steps, sc, s);
   if (st != PINV_OK) return st;
   for (int j = 0; j < n; ++j)

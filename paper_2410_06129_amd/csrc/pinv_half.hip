@@ -684,7 +684,7 @@ hipError_t launch_apply_half(const float* R, const float* D, float* X, int N, in
   const HalfApply p = half_apply_plan(F, N, M);
   if (p.slab < 1) return hipErrorInvalidValue;
   void* ws = nullptr;
-  hipError_t err = sc.get_large(&ws, p.bytes(), s);
+  hipError_t err = sc.get(&ws, p.bytes(), s);
   if (err != hipSuccess) return err;
   char* rp = (char*)ws;
   char* dp = rp + p.r_bytes;

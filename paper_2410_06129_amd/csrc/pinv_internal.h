@@ -9,6 +9,7 @@
 #include <mutex>
 #include <type_traits>
 #include <utility>
+#include <vector>
 
 #include "pinv_device.h"
 
@@ -32,40 +33,68 @@ struct ApplyBatch {     // passed by value as a kernel argument
   ApplyItemDev it[kMaxGroup];
 };
 
+// Device memory a context keeps between calls (plan buffers, build workspaces,
+// scratch of applies).  put() hands a block back behind the work enqueued on `s`;
+// get() takes the smallest idle block of at least `bytes`, and at most an eighth
+// more (a 64th above 256 MB), whose last work has completed or was enqueued on the
+// same stream (behind which the caller's work then waits), else a new block.  Nothing waits on the
+// host.  All calls are safe from several threads and streams.  The runtime's
+// stream-ordered pools served this before: each hipFreeAsync took the host 15 to
+// 25 us, and with several sizes in turn they returned gigabyte blocks to the device
+// and mapped them again (50 ms, up to 2 s) in the middle of steady work.
+class DeviceCache {
+ public:
+  hipError_t get(void** p, size_t bytes, hipStream_t s);
+  hipError_t put(void* p, hipStream_t s);
+  // As put, for a block whose work has completed.
+  void put_idle(void* p);
+  // Give idle blocks back to the device: those whose work has completed, or all
+  // after waiting for it.
+  void trim(bool wait);
+  // Everything, blocks still in use included; the device must be idle.
+  void release_all();
+  size_t idle_bytes();
+
+ private:
+  struct Idle {
+    void* p;
+    hipEvent_t ev;     // null: no work pending
+    hipStream_t s;
+  };
+  static size_t rounded(size_t bytes);
+  void add(void* p, hipEvent_t ev, hipStream_t s);   // mu_ held
+  std::mutex mu_;
+  std::multimap<size_t, Idle> idle_;
+  std::map<void*, size_t> live_;
+  std::vector<hipEvent_t> events_;   // spare events
+};
+
 // Scratch memory of one call (split-contraction partials, refinement
-// vectors).  By default each request is a stream-ordered allocation from the
-// device's default pool, returned by put().  Over a fixed region (the
+// vectors, packed operands).  By default each request is a block of the
+// context's DeviceCache, returned by put().  Over a fixed region (the
 // no-allocation entry point) it is a stack: get() hands out the next
 // 256-aligned block, put() of the most recent block pops it (the stream runs
 // the work in order, so a popped block is free for the next request), and a
 // request beyond the region fails with hipErrorOutOfMemory.  `peak` records
-// the most the stack ever held.  `reclaim`, when set, runs once after a
-// pool allocation fails for lack of memory (it hands memory that other pools
-// hold but do not use back to the device), and the allocation is tried again.
+// the most the stack ever held.  `reclaim` runs once after an allocation fails
+// for lack of memory (it hands idle memory back to the device), and the
+// allocation is tried again.
 struct Scratch {
   char* base = nullptr;
   size_t cap = 0, top = 0, peak = 0;
   struct Block { void* p; size_t start; };
   Block stack[16];
   int depth = 0;
+  DeviceCache* cache = nullptr;
   void (*reclaim)(void* arg, hipStream_t s) = nullptr;
   void* reclaim_arg = nullptr;
-  // `large`, when set, is a pool for the one block of an apply that may take
-  // hundreds of megabytes (get_large): in the default pool a smaller request can
-  // be served from that block while it is free, and the next apply maps another.
-  hipMemPool_t large = nullptr;
-  hipError_t get(void** p, size_t bytes, hipStream_t s) { return get_from(nullptr, p, bytes, s); }
-  hipError_t get_large(void** p, size_t bytes, hipStream_t s) { return get_from(large, p, bytes, s); }
-  hipError_t get_from(hipMemPool_t pool, void** p, size_t bytes, hipStream_t s) {
+  hipError_t get(void** p, size_t bytes, hipStream_t s) {
     if (!base) {
-      auto once = [&]() {
-        return pool ? hipMallocFromPoolAsync(p, bytes, pool, s) : hipMallocAsync(p, bytes, s);
-      };
-      hipError_t e = once();
+      hipError_t e = cache->get(p, bytes, s);
       if (e == hipErrorOutOfMemory && reclaim) {
         (void)hipGetLastError();
         reclaim(reclaim_arg, s);
-        e = once();
+        e = cache->get(p, bytes, s);
       }
       return e;
     }
@@ -78,7 +107,7 @@ struct Scratch {
     return hipSuccess;
   }
   hipError_t put(void* p, hipStream_t s) {
-    if (!base) return hipFreeAsync(p, s);
+    if (!base) return cache->put(p, s);
     if (depth > 0 && stack[depth - 1].p == p) top = stack[--depth].start;
     return hipSuccess;
   }
