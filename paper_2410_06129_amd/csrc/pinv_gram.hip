@@ -395,9 +395,15 @@ size_t psf_work_bytes(const EncDev<double>& e, int* splits) {
   const int W = 2 * e.nx - 1, H = 2 * e.ny - 1;
   const int tiles = cdiv(W, kPsfTile) * cdiv(H, kPsfTile);
   const int pairs = e.S * e.S;
-  // enough workgroups to fill the device, at least 256 samples per split
-  int sp = std::max(1, std::min(e.K / 256, cdiv(2048, (long)tiles * pairs)));
-  sp = std::min(sp, 256);
+  // Enough workgroups to fill the device, at least 256 samples per split.  Small
+  // grids have too few tiles for that: up to 512 workgroups (32 MB of partial
+  // grids) a split may be as short as 32 samples (two chunks).  Whole Gram with at
+  // least 256 against 32 samples: 137 -> 51 us (32 x 32, K = 2048), 237 -> 166
+  // (64 x 64, K = 6000), no difference from 96 x 96 on; 16: 35 against 39 us at
+  // 16 x 16, 63 at 32 x 32 (the sum over more partial grids).
+  int sp = std::min(e.K / 256, cdiv(2048, (long)tiles * pairs));
+  sp = std::max(sp, std::min(e.K / 32, cdiv(512, (long)tiles * pairs)));
+  sp = std::max(1, std::min(sp, 256));
   if (splits) *splits = sp;
   const size_t grid = (size_t)pairs * W * H * 16;
   return grid * (size_t)(sp + 1);   // partial grids, then the summed grid
