@@ -128,10 +128,11 @@ hipError_t launch_cholinv(double* A, double* Li, int N, double lam, int* info, h
 // product (else four).  R may be stored in a narrower type TO than T.  With
 // rows / kdim >= 0 the factor is dense instead of lower triangular: W has
 // `rows` rows (W = Q^H E^H, Q^H rows x N) and R sums over kdim rows of W
-// (R = Q W), the eigenvalue route's products.
+// (R = Q W), the eigenvalue route's products.  With Eh (FP64; e.N x e.M complex
+// values) E^H is formed there first and read by the product's tiles.
 template <typename T>
 hipError_t launch_trmm_w(const EncDev<T>& e, const T* Li, T* W, bool m3, hipStream_t s,
-                         int rows = -1);
+                         int rows = -1, T* Eh = nullptr);
 template <typename T, typename TO>
 hipError_t launch_trmm_r(const T* Li, const T* W, TO* R, int N, int M, bool m3, hipStream_t s,
                          int kdim = -1);

@@ -9,12 +9,37 @@ namespace pinv {
 // ---------------------------------------------------------------------------
 // W = L^-1 E^H : W[i][m] = sum_{n <= i} Li[i][n] conj(E[m][n])
 // ---------------------------------------------------------------------------
+// E^H formed once, Eh[n][m] = conj(E[m][n]), for the product to read: FP64 plans
+// form it in the memory that R takes afterwards.  Thread t of a workgroup owns
+// column m0 + t % 64 and every fourth row of 64.
+template <int FEAT>
+__global__ __launch_bounds__(256) void k_gen_eh(EncDev<double> e, double* __restrict__ Eh) {
+  const int nbm = (e.M + 63) / 64;
+  const int m = (int)(blockIdx.x % nbm) * 64 + (int)(threadIdx.x % 64);
+  const int n0 = (int)(blockIdx.x / nbm) * 64;
+  if (m >= e.M) return;
+  const int c = m / e.K, i = m - c * e.K;
+  cx<double>* O = reinterpret_cast<cx<double>*>(Eh);
+#pragma unroll 4
+  for (int n = n0 + (int)(threadIdx.x / 64); n < min(n0 + 64, e.N); n += 4) {
+    const int s = n / e.V, v = n - s * e.V;
+    int ix, iy;
+    voxel_xy(e, v, &ix, &iy);
+    GenRaw<double> raw;
+    gen_load<FEAT>(e, i, s, v, ix, iy, c, raw);
+    const cx<double> z = gen_product<FEAT>(raw);
+    O[(size_t)n * e.M + m] = cx<double>{z.re, -z.im};
+  }
+}
+
+// With STORED, E^H is read from `Eh` instead of generated per tile.
 // `rows` rows of W; Li is lower triangular (tri, rows = N) or dense
 // (rows x N: the eigenvalue route's Q^H).
-template <class Cfg, int FEAT, bool AL>
+template <class Cfg, int FEAT, bool AL, bool STORED = false>
 __global__ __launch_bounds__(256) void k_trmm_w(EncDev<typename Cfg::T> e,
                                                 const typename Cfg::T* __restrict__ Li,
-                                                typename Cfg::T* __restrict__ W, int rows, int tri) {
+                                                typename Cfg::T* __restrict__ W, int rows, int tri,
+                                                const typename Cfg::T* __restrict__ Eh) {
   typedef typename Cfg::T T;
   const int N = e.N, M = e.M;
   const int nbi = (rows + Cfg::BM - 1) / Cfg::BM, nbj = (M + Cfg::BN - 1) / Cfg::BN;
@@ -29,12 +54,21 @@ __global__ __launch_bounds__(256) void k_trmm_w(EncDev<typename Cfg::T> e,
   la.ld = N;
   la.o0 = bi * Cfg::BM;
   la.oend = rows;
-  LoadGenRow<Cfg, Cfg::BN, Cfg::LDB, true, FEAT, AL> lb;
-  lb.init(e, bj * Cfg::BN);
   AccTile<Cfg> acc;
   acc.zero();
   const int kend = tri ? min(N, (bi + 1) * Cfg::BM) : N;
-  mainloop<Cfg>(la, lb, 0, kend, acc, smem_base<Cfg>());
+  if constexpr (STORED) {
+    LoadDenseOC<Cfg, Cfg::BN, Cfg::LDB, T, false> lb;
+    lb.p = reinterpret_cast<const cx<T>*>(Eh);
+    lb.ld = M;
+    lb.o0 = bj * Cfg::BN;
+    lb.oend = M;
+    mainloop<Cfg>(la, lb, 0, kend, acc, smem_base<Cfg>());
+  } else {
+    LoadGenRow<Cfg, Cfg::BN, Cfg::LDB, true, FEAT, AL> lb;
+    lb.init(e, bj * Cfg::BN);
+    mainloop<Cfg>(la, lb, 0, kend, acc, smem_base<Cfg>());
+  }
   cx<T>* O = reinterpret_cast<cx<T>*>(W);
   const int r0 = bi * Cfg::BM, c0 = bj * Cfg::BN;
   acc_foreach<Cfg>(acc, [&](int r, int c, T re, T im) {
@@ -166,17 +200,38 @@ hipError_t launch_right_pinv(const EncDev<T>& e, const T* Li, T* W, T* Z, TO* R,
   return hipGetLastError();
 }
 
+static hipError_t trmm_w_stored(const EncDev<double>& e, const double* Li, double* W, bool m3,
+                                hipStream_t s, int rows, int tri, double* Eh) {
+  return with_form<double>(m3, [&](auto cfg) {
+    typedef decltype(cfg) Cfg;
+    const int tiles = cdiv(rows, Cfg::BM) * cdiv(e.M, Cfg::BN);
+    if (tiles == 0) return hipSuccess;
+    const hipError_t err = with_feat(enc_features(e), [&](auto fc) {
+      hipLaunchKernelGGL((k_gen_eh<decltype(fc)::value>), dim3((unsigned)cdiv(e.M, 64) * cdiv(e.N, 64)),
+                         dim3(256), 0, s, e, Eh);
+      return hipGetLastError();
+    });
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((k_trmm_w<Cfg, 0, false, true>), dim3(tiles), dim3(256), smem_bytes<Cfg>(), s, e,
+                       Li, W, rows, tri, (const double*)Eh);
+    return hipGetLastError();
+  });
+}
+
 template <typename T>
-hipError_t launch_trmm_w(const EncDev<T>& e, const T* Li, T* W, bool m3, hipStream_t s, int rows) {
+hipError_t launch_trmm_w(const EncDev<T>& e, const T* Li, T* W, bool m3, hipStream_t s, int rows, T* Eh) {
   const int tri = rows < 0;
   if (tri) rows = e.N;
+  if constexpr (sizeof(T) == 8) {
+    if (Eh) return trmm_w_stored(e, Li, W, m3, s, rows, tri, Eh);
+  }
   return with_form<T>(m3, [&](auto cfg) {
     typedef decltype(cfg) Cfg;
     const int tiles = cdiv(rows, Cfg::BM) * cdiv(e.M, Cfg::BN);
     if (tiles == 0) return hipSuccess;
     return with_feat_al(enc_features(e), row_aligned(e, Cfg::BK), [&](auto fc, auto al) {
       hipLaunchKernelGGL((k_trmm_w<Cfg, decltype(fc)::value, decltype(al)::value>), dim3(tiles),
-                         dim3(256), smem_bytes<Cfg>(), s, e, Li, W, rows, tri);
+                         dim3(256), smem_bytes<Cfg>(), s, e, Li, W, rows, tri, (const T*)nullptr);
       return hipGetLastError();
     });
   });
@@ -204,9 +259,9 @@ template hipError_t launch_right_pinv<double, double>(const EncDev<double>&, con
 template hipError_t launch_right_pinv<double, float>(const EncDev<double>&, const double*, double*,
                                                      double*, float*, bool, hipStream_t);
 template hipError_t launch_trmm_w<float>(const EncDev<float>&, const float*, float*, bool,
-                                         hipStream_t, int);
+                                         hipStream_t, int, float*);
 template hipError_t launch_trmm_w<double>(const EncDev<double>&, const double*, double*, bool,
-                                          hipStream_t, int);
+                                          hipStream_t, int, double*);
 template hipError_t launch_trmm_r<float, float>(const float*, const float*, float*, int, int, bool,
                                                 hipStream_t, int);
 template hipError_t launch_trmm_r<double, double>(const double*, const double*, double*, int, int,

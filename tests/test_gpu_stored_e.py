@@ -1,0 +1,46 @@
+"""FP64 plans of 640 unknowns or more store E^H before the W product: R element by
+element against the oracle on both sides of that size, over every factor an element
+can have (coils, species, off-resonance, a voxel mask) and sample counts on and off
+the 64-column tiles.  1e-9 of the largest element, as for every FP64 R."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2410_06129_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = {
+    "n639": dict(seed=901, nx=71, ny=9, C=2, K=330, F=1),
+    "n640": dict(seed=902, nx=32, ny=20, C=2, K=320, F=1),
+    "n641_one_coil": dict(seed=903, nx=641, ny=1, C=1, K=705, F=1),
+    "n646_species_b0": dict(seed=904, nx=17, ny=19, C=3, K=217, F=1, species=[0.0, 170.0], b0=True),
+    "mask": dict(seed=905, nx=32, ny=30, C=3, K=255, F=1, b0=True),
+}
+
+
+@pytest.mark.parametrize("form", ["3m", "4m"])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_r_matches_oracle(name, form):
+    from paper_2410_06129_amd import pinv as P
+    enc = synth.small_case(**SHAPES[name]).enc
+    if name == "mask":
+        enc = dataclasses.replace(enc, voxels=synth.circular_mask(32, 30, 0.96))
+    assert (enc.N >= 640) == (name != "n639") and enc.M >= enc.N
+    ctx = P.pinv_context_create(0)
+    try:
+        plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP64, P.FLAG_UNCACHED,
+                            cprod=P.CPROD_3M if form == "3m" else P.CPROD_4M)
+        P.pinv_plan_wait(plan)
+        R = torch.full((enc.N, enc.M), float("nan"), dtype=torch.complex128, device="cuda")
+        P.pinv_plan_copy_buffer(plan, P.BUF_R, R)
+        torch.cuda.synchronize()
+        P.pinv_plan_release(plan)
+    finally:
+        P.pinv_context_destroy(ctx)
+    ref = oracle.Build(enc, rel=1e-2).recon_matrix()
+    assert np.max(np.abs(R.cpu().numpy() - ref)) <= 1e-9 * np.max(np.abs(ref))
