@@ -188,6 +188,13 @@ hipError_t launch_adjoint(const EncDev<T>& e, const SD* D, int F, const SX* X, d
 // Scratch bytes of launch_adjoint<T, ...> for F frames (split partials).
 template <typename T, typename SD, typename SX, typename SO>
 size_t adjoint_scratch_bytes(const EncDev<T>& e, int F);
+// b = E^H D in FP64 (complex64 D, F x M) by gridding: for encodings without an
+// off-resonance map, where grid_adjoint() says that it takes less time than the direct
+// sum.  All-or-nothing scratch: hipErrorOutOfMemory leaves the direct sum to do.
+bool grid_adjoint(const EncDev<double>& e, int F);
+size_t grid_adjoint_scratch_bytes(const EncDev<double>& e, int F);
+hipError_t launch_grid_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
+                               hipStream_t s);
 template <typename SX, typename SO>
 hipError_t launch_resid(const double* G, const double* b, const SX* X, int F, int N, double lam,
                         SO* Out, hipStream_t s);
