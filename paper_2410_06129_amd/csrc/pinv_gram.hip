@@ -85,25 +85,38 @@ __global__ __launch_bounds__(256, 2) void k_gram_rows(EncDev<typename Cfg::T> e,
 // F^H F is accumulated over the K rows of one coil on MFMA (F generated per
 // tile), the coil cross-product is formed in the epilogue from coil columns
 // staged in LDS.  `e` must describe F (no coil table, C = 1, M = K); `coil`
-// is the [C][V] coil table (or null for one unit coil).
+// is the [C][V] coil table (or null for one unit coil).  With STORED, F^H is read
+// from `Fh` (N x K) instead of generated per tile.
 // ---------------------------------------------------------------------------
-template <class Cfg, int FEAT, bool AL>
+template <class Cfg, int FEAT, bool AL, bool STORED = false>
 __global__ __launch_bounds__(256, 2) void k_gram_shared(EncDev<typename Cfg::T> e,
                                                      const typename Cfg::T* __restrict__ coil,
-                                                     int C, double* __restrict__ G) {
+                                                     int C, double* __restrict__ G,
+                                                     const typename Cfg::T* __restrict__ Fh) {
   typedef typename Cfg::T T;
   static_assert(Cfg::BM == Cfg::BN, "square tiles");
   int bi, bj;
   tri_index(blockIdx.x, &bi, &bj);
   const int N = e.N, V = e.V;
-  LoadGenCol<Cfg, Cfg::BM, Cfg::LDA, true, FEAT, AL> la;
-  LoadGenCol<Cfg, Cfg::BN, Cfg::LDB, false, FEAT, AL> lb;
-  la.init(e, bi * Cfg::BM);
-  lb.init(e, bj * Cfg::BN);
   T* smem = smem_base<Cfg>();
   AccTile<Cfg> acc;
   acc.zero();
-  mainloop<Cfg>(la, lb, 0, e.M, acc, smem);
+  if constexpr (STORED) {
+    LoadDenseKC<Cfg, Cfg::BM, Cfg::LDA, T, false> la;
+    LoadDenseKC<Cfg, Cfg::BN, Cfg::LDB, T, true> lb;
+    la.p = lb.p = reinterpret_cast<const cx<T>*>(Fh);
+    la.ld = lb.ld = e.M;
+    la.o0 = bi * Cfg::BM;
+    lb.o0 = bj * Cfg::BN;
+    la.oend = lb.oend = N;
+    mainloop<Cfg>(la, lb, 0, e.M, acc, smem);
+  } else {
+    LoadGenCol<Cfg, Cfg::BM, Cfg::LDA, true, FEAT, AL> la;
+    LoadGenCol<Cfg, Cfg::BN, Cfg::LDB, false, FEAT, AL> lb;
+    la.init(e, bi * Cfg::BM);
+    lb.init(e, bj * Cfg::BN);
+    mainloop<Cfg>(la, lb, 0, e.M, acc, smem);
+  }
   const int r0 = bi * Cfg::BM, c0 = bj * Cfg::BN;
   cx<double>* Gc = reinterpret_cast<cx<double>*>(G);
   if (!coil) {
@@ -376,7 +389,7 @@ hipError_t launch_gram_rows(const EncDev<double>& e, double* G, hipStream_t s) {
 
 
 template <typename T>
-hipError_t launch_gram_shared(const EncDev<T>& e, double* G, hipStream_t s) {
+hipError_t launch_gram_shared(const EncDev<T>& e, double* G, T* Fh, hipStream_t s) {
   typedef typename GramCfgOf<T>::type Cfg;
   EncDev<T> f = e;       // the coil-free encoding F over one coil's K rows
   f.coil = nullptr;
@@ -384,9 +397,19 @@ hipError_t launch_gram_shared(const EncDev<T>& e, double* G, hipStream_t s) {
   f.M = e.K;
   const int nb = cdiv(e.N, Cfg::BM);
   const int tiles = nb * (nb + 1) / 2;
+  if constexpr (sizeof(T) == 8) {
+    if (Fh) {
+      const hipError_t err = launch_gen_eh(f, Fh, s);
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL((k_gram_shared<Cfg, 0, false, true>), dim3(tiles), dim3(256), smem_bytes<Cfg>(), s,
+                         f, e.coil, e.coil ? e.C : 1, G, (const T*)Fh);
+      return hipGetLastError();
+    }
+  }
   return with_feat_al(enc_features(f) & 3, f.K % Cfg::BK == 0, [&](auto fc, auto al) {
     hipLaunchKernelGGL((k_gram_shared<Cfg, decltype(fc)::value & 3, decltype(al)::value>),
-                       dim3(tiles), dim3(256), smem_bytes<Cfg>(), s, f, e.coil, e.coil ? e.C : 1, G);
+                       dim3(tiles), dim3(256), smem_bytes<Cfg>(), s, f, e.coil, e.coil ? e.C : 1, G,
+                       (const T*)nullptr);
     return hipGetLastError();
   });
 }
@@ -442,7 +465,7 @@ hipError_t launch_herm_fill(double* G, int N, hipStream_t s) {
 // explicit instantiations
 template hipError_t launch_gram<float>(const EncDev<float>&, double*, int, hipStream_t);
 template hipError_t launch_gram<double>(const EncDev<double>&, double*, int, hipStream_t);
-template hipError_t launch_gram_shared<float>(const EncDev<float>&, double*, hipStream_t);
-template hipError_t launch_gram_shared<double>(const EncDev<double>&, double*, hipStream_t);
+template hipError_t launch_gram_shared<float>(const EncDev<float>&, double*, float*, hipStream_t);
+template hipError_t launch_gram_shared<double>(const EncDev<double>&, double*, double*, hipStream_t);
 
 }  // namespace pinv

@@ -119,7 +119,10 @@ struct Scratch {
 hipError_t launch_tables(const EncDev<double>& e, const EncDev<float>* f, const double* k,
                          const double* hz, hipStream_t s);
 template <typename T> hipError_t launch_gram(const EncDev<T>& e, double* G, int flush, hipStream_t s);
-template <typename T> hipError_t launch_gram_shared(const EncDev<T>& e, double* G, hipStream_t s);
+// With Fh (FP64; e.N x e.K complex values) F^H is formed there first and read by the tiles.
+template <typename T> hipError_t launch_gram_shared(const EncDev<T>& e, double* G, T* Fh, hipStream_t s);
+// Eh[n][m] = conj(E[m][n]).
+hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s);
 // Cholesky of A + lam I (FP64, in place) with L^-1 formed alongside in Li
 // (zeroed by the caller); nb = 64 or 128 (two-level).
 hipError_t launch_cholinv(double* A, double* Li, int N, double lam, int* info, hipStream_t s,

@@ -200,17 +200,21 @@ hipError_t launch_right_pinv(const EncDev<T>& e, const T* Li, T* W, T* Z, TO* R,
   return hipGetLastError();
 }
 
+hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s) {
+  return with_feat(enc_features(e), [&](auto fc) {
+    hipLaunchKernelGGL((k_gen_eh<decltype(fc)::value>), dim3((unsigned)cdiv(e.M, 64) * cdiv(e.N, 64)),
+                       dim3(256), 0, s, e, Eh);
+    return hipGetLastError();
+  });
+}
+
 static hipError_t trmm_w_stored(const EncDev<double>& e, const double* Li, double* W, bool m3,
                                 hipStream_t s, int rows, int tri, double* Eh) {
   return with_form<double>(m3, [&](auto cfg) {
     typedef decltype(cfg) Cfg;
     const int tiles = cdiv(rows, Cfg::BM) * cdiv(e.M, Cfg::BN);
     if (tiles == 0) return hipSuccess;
-    const hipError_t err = with_feat(enc_features(e), [&](auto fc) {
-      hipLaunchKernelGGL((k_gen_eh<decltype(fc)::value>), dim3((unsigned)cdiv(e.M, 64) * cdiv(e.N, 64)),
-                         dim3(256), 0, s, e, Eh);
-      return hipGetLastError();
-    });
+    const hipError_t err = launch_gen_eh(e, Eh, s);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((k_trmm_w<Cfg, 0, false, true>), dim3(tiles), dim3(256), smem_bytes<Cfg>(), s, e,
                        Li, W, rows, tri, (const double*)Eh);

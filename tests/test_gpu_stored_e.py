@@ -1,7 +1,13 @@
-"""FP64 plans of 640 unknowns or more store E^H before the W product: R element by
+"""Products that read a stored encoding matrix.
+
+FP64 plans of 640 unknowns or more store E^H before the W product: R element by
 element against the oracle on both sides of that size, over every factor an element
 can have (coils, species, off-resonance, a voxel mask) and sample counts on and off
-the 64-column tiles.  1e-9 of the largest element, as for every FP64 R."""
+the 64-column tiles.  1e-9 of the largest element, as for every FP64 R.
+
+The shared-trajectory Gram stores F^H where R's or W's memory holds it: two coils of an
+FP32 plan just do, one coil does not; sizes on and off the 64-voxel tiles and 8-sample
+chunks.  1e-12 of the largest element (FP64 sums of at most 1000 unit-size terms)."""
 import dataclasses
 
 import numpy as np
@@ -44,3 +50,25 @@ def test_r_matches_oracle(name, form):
         P.pinv_context_destroy(ctx)
     ref = oracle.Build(enc, rel=1e-2).recon_matrix()
     assert np.max(np.abs(R.cpu().numpy() - ref)) <= 1e-9 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("coils", [1, 2])
+@pytest.mark.parametrize("nx,ny,K", [(1, 1, 9), (8, 8, 64), (13, 5, 131), (16, 12, 200)])
+def test_shared_gram_matches_oracle(nx, ny, K, coils, prec):
+    from paper_2410_06129_amd import pinv as P
+    enc = synth.small_case(seed=910 + K, nx=nx, ny=ny, C=coils, K=K, F=1, b0=True).enc
+    ctx = P.pinv_context_create(0)
+    try:
+        plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG,
+                            {"fp64": P.FP64, "fp32": P.FP32, "bf16x3": P.BF16X3}[prec], P.FLAG_UNCACHED)
+        P.pinv_plan_wait(plan)
+        assert P.pinv_plan_info_get(plan)["gram_form"] == P.GRAM_SHARED
+        G = torch.full((enc.N, enc.N), float("nan"), dtype=torch.complex128, device="cuda")
+        P.pinv_plan_copy_buffer(plan, P.BUF_GRAM, G)
+        torch.cuda.synchronize()
+        P.pinv_plan_release(plan)
+    finally:
+        P.pinv_context_destroy(ctx)
+    Go = oracle.gram(enc)
+    assert np.max(np.abs(G.cpu().numpy() - Go)) <= 1e-12 * np.max(np.abs(Go))
