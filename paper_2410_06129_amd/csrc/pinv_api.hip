@@ -1327,8 +1327,10 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
       e = sc.get(&b, 16 * (size_t)F * N, s);
       bool formed = false;
       if constexpr (sizeof(TS) == 4) {
-        if (e == hipSuccess && grid_adjoint(p->e64, F)) {
-          e = launch_grid_adjoint(p->e64, d, F, (double*)b, sc, s);
+        const bool grid = grid_adjoint(p->e64, F);
+        if (e == hipSuccess && (grid || stored_adjoint(p->e64, F))) {
+          e = grid ? launch_grid_adjoint(p->e64, d, F, (double*)b, sc, s)
+                   : launch_stored_adjoint(p->e64, d, F, (double*)b, sc, s);
           formed = e == hipSuccess;
           if (e == hipErrorOutOfMemory) {   // the direct sum needs less scratch, or none
             (void)hipGetLastError();
@@ -1469,10 +1471,11 @@ size_t item_scratch_bytes(const pinv_plan* p, int F, int steps) {
     if (p->gram_exact)
       refine += al(16 * F * N) + (p->prec == PINV_FP64
                                       ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
-                                  : grid_adjoint(p->e64, F)
-                                      ? std::max(grid_adjoint_scratch_bytes(p->e64, F),
-                                                 adjoint_scratch_bytes<double, float, float, double>(p->e64, F))
-                                      : adjoint_scratch_bytes<double, float, float, double>(p->e64, F));
+                                      : std::max(grid_adjoint(p->e64, F) ? grid_adjoint_scratch_bytes(p->e64, F)
+                                                 : stored_adjoint(p->e64, F)
+                                                     ? stored_adjoint_scratch_bytes(p->e64, F)
+                                                     : 0,
+                                                 adjoint_scratch_bytes<double, float, float, double>(p->e64, F)));
     else
       refine += al(16 * F * M) + (p->prec == PINV_FP64
                                       ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)

@@ -404,12 +404,12 @@ __global__ __launch_bounds__(256) void k_grid_combine(EncDev<double> e, const cx
   b[u] = z;
 }
 
-// Gridding does fewer multiply-adds than the direct sum, from about 20 x 20 voxels on
-// and the more so the larger the image, and its contractions are short where the direct
-// sum's is M long.  A refinement step, direct sum against gridding (K = 2000 to 10000):
-// 20 x 20, 8 coils, 200 frames 937 / 619 us; 32 x 32, 8 coils, 2 frames 1773 / 675;
-// 64 x 64, 8 coils, 1 frame 4743 / 2330; one coil and frame of 48 x 48 1201 / 1168, of
-// 32 x 32 575 / 584.
+// Gridding does fewer multiply-adds than a sum over all voxels, but its contractions
+// run at half the matrix cores' rate where a product with a stored F^H reaches 0.73.
+// A refinement step by the direct sum, stored F^H and gridding (ratio of multiply-adds):
+// 24 x 24, 8 coils, 200 frames 905, 546, 588 us (1.46); 28 x 28 1001, 737, 708 (1.87);
+// 48 x 48, 4 coils, 100 frames 2018, 1543, 1249 (4.4); 64 x 64, 8 coils, 1 frame 4354,
+// 2590, 1928 (7.5); level at one frame of 32 x 32, one coil (6e6 multiply-adds).
 bool grid_adjoint(const EncDev<double>& e, int F) {
   if (e.b0 || e.nx < kGridMin || e.ny < kGridMin || F <= 0) return false;
   const double rows = (double)F * e.C * e.S, img = (double)e.nx * e.ny;
@@ -417,7 +417,7 @@ bool grid_adjoint(const EncDev<double>& e, int F) {
   if (64.0 * 2.0 * img * e.C * e.S > (double)kGridBytes) return false;
   const double direct = 3.0 * rows * e.K * e.V;
   const double grid = rows * (2.0 * 529.0 * e.K + 3.0 * img * (4.0 * e.nx + 2.0 * e.ny));
-  return direct >= grid && direct >= 1e7;
+  return direct >= 1.75 * grid && direct >= 1e7;
 }
 
 size_t grid_adjoint_scratch_bytes(const EncDev<double>& e, int F) {

@@ -121,8 +121,8 @@ hipError_t launch_tables(const EncDev<double>& e, const EncDev<float>* f, const 
 template <typename T> hipError_t launch_gram(const EncDev<T>& e, double* G, int flush, hipStream_t s);
 // With Fh (FP64; e.N x e.K complex values) F^H is formed there first and read by the tiles.
 template <typename T> hipError_t launch_gram_shared(const EncDev<T>& e, double* G, T* Fh, hipStream_t s);
-// Eh[n][m] = conj(E[m][n]).
-hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s);
+// Eh[j][m] = conj(E[m][n0 + j]), n rows (default: all).
+hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s, int n0 = 0, int n = -1);
 // Cholesky of A + lam I (FP64, in place) with L^-1 formed alongside in Li
 // (zeroed by the caller); nb = 64 or 128 (two-level).
 hipError_t launch_cholinv(double* A, double* Li, int N, double lam, int* info, hipStream_t s,
@@ -198,6 +198,11 @@ bool grid_adjoint(const EncDev<double>& e, int F);
 size_t grid_adjoint_scratch_bytes(const EncDev<double>& e, int F);
 hipError_t launch_grid_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                hipStream_t s);
+// The same through a stored F^H, where stored_adjoint() says so.
+bool stored_adjoint(const EncDev<double>& e, int F);
+size_t stored_adjoint_scratch_bytes(const EncDev<double>& e, int F);
+hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
+                                 hipStream_t s);
 template <typename SX, typename SO>
 hipError_t launch_resid(const double* G, const double* b, const SX* X, int F, int N, double lam,
                         SO* Out, hipStream_t s);

@@ -11,24 +11,25 @@ namespace pinv {
 // ---------------------------------------------------------------------------
 // E^H formed once, Eh[n][m] = conj(E[m][n]), for the product to read: FP64 plans
 // form it in the memory that R takes afterwards.  Thread t of a workgroup owns
-// column m0 + t % 64 and every fourth row of 64.
+// column m0 + t % 64 and every fourth row of 64.  Rows nb .. ne of E^H, Eh holding row
+// nb first.
 template <int FEAT>
-__global__ __launch_bounds__(256) void k_gen_eh(EncDev<double> e, double* __restrict__ Eh) {
+__global__ __launch_bounds__(256) void k_gen_eh(EncDev<double> e, double* __restrict__ Eh, int nb, int ne) {
   const int nbm = (e.M + 63) / 64;
   const int m = (int)(blockIdx.x % nbm) * 64 + (int)(threadIdx.x % 64);
-  const int n0 = (int)(blockIdx.x / nbm) * 64;
+  const int n0 = nb + (int)(blockIdx.x / nbm) * 64;
   if (m >= e.M) return;
   const int c = m / e.K, i = m - c * e.K;
   cx<double>* O = reinterpret_cast<cx<double>*>(Eh);
 #pragma unroll 4
-  for (int n = n0 + (int)(threadIdx.x / 64); n < min(n0 + 64, e.N); n += 4) {
+  for (int n = n0 + (int)(threadIdx.x / 64); n < min(n0 + 64, ne); n += 4) {
     const int s = n / e.V, v = n - s * e.V;
     int ix, iy;
     voxel_xy(e, v, &ix, &iy);
     GenRaw<double> raw;
     gen_load<FEAT>(e, i, s, v, ix, iy, c, raw);
     const cx<double> z = gen_product<FEAT>(raw);
-    O[(size_t)n * e.M + m] = cx<double>{z.re, -z.im};
+    O[(size_t)(n - nb) * e.M + m] = cx<double>{z.re, -z.im};
   }
 }
 
@@ -200,10 +201,11 @@ hipError_t launch_right_pinv(const EncDev<T>& e, const T* Li, T* W, T* Z, TO* R,
   return hipGetLastError();
 }
 
-hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s) {
+hipError_t launch_gen_eh(const EncDev<double>& e, double* Eh, hipStream_t s, int n0, int n) {
+  if (n < 0) n = e.N;
   return with_feat(enc_features(e), [&](auto fc) {
-    hipLaunchKernelGGL((k_gen_eh<decltype(fc)::value>), dim3((unsigned)cdiv(e.M, 64) * cdiv(e.N, 64)),
-                       dim3(256), 0, s, e, Eh);
+    hipLaunchKernelGGL((k_gen_eh<decltype(fc)::value>), dim3((unsigned)cdiv(e.M, 64) * cdiv(n, 64)),
+                       dim3(256), 0, s, e, Eh, n0, n0 + n);
     return hipGetLastError();
   });
 }

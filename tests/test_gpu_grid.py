@@ -8,7 +8,7 @@ is no multiple of the 16 of a chunk; species, a voxel mask, coils and none, fram
 a 64-row tile and do not.
 
 Tolerance: two steps of refinement converge (each reduces the error by the condition
-number, at most about 1e4, times 2^-24), so what is left is the image's own rounding
+number, at most about 1.6e4, times 2^-24), so what is left is the image's own rounding
 to complex64, 2^-24 at most per value, and the last correction's: 1e-7 of each frame.
 """
 import dataclasses
@@ -24,14 +24,14 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 CASES = {
-    "odd": dict(seed=1002, nx=25, ny=21, C=3, K=1201, F=22),
-    "wide": dict(seed=1003, nx=34, ny=16, C=2, K=1003, F=32),
-    "one_coil": dict(seed=1004, nx=24, ny=25, C=1, K=1300, F=65),
-    "species": dict(seed=1005, nx=22, ny=21, C=4, K=1100, F=5, species=[0.0, 140.0]),
-    "mask": dict(seed=1006, nx=28, ny=26, C=4, K=1000, F=3),
-    "cartesian": dict(seed=1007, nx=24, ny=24, C=2, K=900, F=7),
-    "wrapped": dict(seed=1008, nx=19, ny=24, C=3, K=800, F=6),
-    "dense": dict(seed=1009, nx=20, ny=20, C=2, K=3001, F=4),
+    "odd": dict(seed=1002, nx=31, ny=29, C=3, K=1201, F=22),
+    "wide": dict(seed=1003, nx=64, ny=16, C=2, K=2003, F=32),
+    "one_coil": dict(seed=1004, nx=32, ny=29, C=1, K=1300, F=65),
+    "species": dict(seed=1005, nx=28, ny=29, C=4, K=1700, F=5, species=[0.0, 140.0]),
+    "mask": dict(seed=1006, nx=34, ny=33, C=4, K=2000, F=3),
+    "cartesian": dict(seed=1007, nx=30, ny=30, C=2, K=1300, F=7),
+    "wrapped": dict(seed=1008, nx=27, ny=32, C=3, K=1500, F=6),
+    "dense": dict(seed=1009, nx=28, ny=28, C=2, K=3001, F=4),
 }
 
 
@@ -39,11 +39,11 @@ def encoding(name):
     w = synth.small_case(**CASES[name])
     enc, rng = w.enc, np.random.default_rng(CASES[name]["seed"])
     if name == "mask":
-        enc = dataclasses.replace(enc, voxels=synth.circular_mask(28, 26, 0.95))
+        enc = dataclasses.replace(enc, voxels=synth.circular_mask(34, 33, 0.97))
     if name == "cartesian":
-        enc = dataclasses.replace(enc, k=np.concatenate([synth.cartesian_full(24, 24)] * 2)[:enc.K])
+        enc = dataclasses.replace(enc, k=np.concatenate([synth.cartesian_full(30, 30)] * 2)[:enc.K])
     if name == "wrapped":
-        enc = dataclasses.replace(enc, k=(rng.random((enc.K, 2)) - 0.5) * [61.0, 90.0])
+        enc = dataclasses.replace(enc, k=(rng.random((enc.K, 2)) - 0.5) * [80.0, 100.0])
     if name == "dense":
         k = enc.k.copy()
         k[1000:] = (rng.random((enc.K - 1000, 2)) - 0.5) * 3.0
@@ -78,10 +78,10 @@ def refined(P, ctx, enc, d):
 @pytest.mark.parametrize("name", list(CASES))
 def test_refined_images_match_oracle(P, ctx, name):
     enc = encoding(name)
-    # more multiply-adds in the direct sum than in gridding, and at least 1e7
+    # 1.75 times gridding's multiply-adds in the direct sum, and at least 1e7
     rows, img = CASES[name]["F"] * enc.C * enc.S, enc.nx * enc.ny
     direct = 3 * rows * enc.K * enc.V
-    assert direct >= max(1e7, rows * (1058 * enc.K + 3 * img * (4 * enc.nx + 2 * enc.ny)))
+    assert direct >= max(1e7, 1.75 * rows * (1058 * enc.K + 3 * img * (4 * enc.nx + 2 * enc.ny)))
     rng = np.random.default_rng(7)
     d = synth.unit_complex_noise((CASES[name]["F"], enc.M), rng).astype(np.complex64)
     x = refined(P, ctx, enc, d)

@@ -7,7 +7,12 @@ the 64-column tiles.  1e-9 of the largest element, as for every FP64 R.
 
 The shared-trajectory Gram stores F^H where R's or W's memory holds it: two coils of an
 FP32 plan just do, one coil does not; sizes on and off the 64-voxel tiles and 8-sample
-chunks.  1e-12 of the largest element (FP64 sums of at most 1000 unit-size terms)."""
+chunks.  1e-12 of the largest element (FP64 sums of at most 1000 unit-size terms).
+
+Refinement of FP32 plans forms E^H d through a stored F^H where gridding does not: a
+map, species, odd voxel and sample counts, one frame and 64 frames of one coil more,
+a contraction in splits, and columns in two slabs.  Two steps converge to the image's
+own rounding to complex64: 1e-7 of each frame."""
 import dataclasses
 
 import numpy as np
@@ -72,3 +77,42 @@ def test_shared_gram_matches_oracle(nx, ny, K, coils, prec):
         P.pinv_context_destroy(ctx)
     Go = oracle.gram(enc)
     assert np.max(np.abs(G.cpu().numpy() - Go)) <= 1e-12 * np.max(np.abs(Go))
+
+
+REFINED = {
+    "one_frame": dict(seed=921, nx=13, ny=11, C=3, K=301, F=1, b0=True),
+    "one_coil_65": dict(seed=922, nx=12, ny=9, C=1, K=333, F=65),
+    "map_one_coil": dict(seed=923, nx=16, ny=8, C=1, K=500, F=3, b0=True),
+    "species_map": dict(seed=924, nx=11, ny=12, C=4, K=700, F=17, species=[0.0, 170.0], b0=True),
+    "mask": dict(seed=925, nx=15, ny=14, C=5, K=201, F=26, b0=True),
+    "slabs": dict(seed=926, nx=24, ny=24, C=8, K=600, F=3600, species=[0.0, 170.0], b0=True),
+}
+
+
+@pytest.mark.parametrize("name", list(REFINED))
+def test_refined_images_match_oracle(name):
+    from paper_2410_06129_amd import pinv as P
+    enc = synth.small_case(**REFINED[name]).enc
+    if name == "mask":
+        enc = dataclasses.replace(enc, voxels=synth.circular_mask(15, 14, 0.97))
+    F = REFINED[name]["F"]
+    if name == "slabs":   # F^H and its product with every frame and coil: 512 MB
+        assert 16 * enc.N * (enc.K + F * enc.C) > 512 << 20
+    d = synth.unit_complex_noise((F, enc.M), np.random.default_rng(9)).astype(np.complex64)
+    ctx = P.pinv_context_create(0)
+    try:
+        plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED)
+        P.pinv_plan_wait(plan)
+        x = torch.full((F, enc.N), float("nan"), dtype=torch.complex64, device="cuda")
+        P.pinv_apply(ctx, plan, torch.from_numpy(d).cuda(), x, refine_steps=2)
+        torch.cuda.synchronize()
+        P.pinv_plan_release(plan)
+    finally:
+        P.pinv_context_destroy(ctx)
+    x = x.cpu().numpy().astype(np.complex128)
+    assert np.all(np.isfinite(x.view(np.float64)))
+    pick = slice(None, None, 97 if F > 1000 else 1)
+    ref = d[pick].astype(np.complex128) @ oracle.Build(enc, rel=1e-2).recon_matrix().T
+    err = np.linalg.norm(x[pick] - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    print(f"{name}: {err.max():.1e}")
+    assert err.max() <= 1e-7
