@@ -1347,15 +1347,15 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
   }
   for (int it = 0; it < steps && e == hipSuccess; ++it) {
     if (p->gram_exact) {
-      e = launch_resid<TS, TS>((const double*)p->gram, (const double*)b, x, F, p->N, p->lam, (TS*)r, s);
+      e = launch_resid<TS, TS>((const double*)p->gram, (const double*)b, x, F, p->N, p->lam, (TS*)r, sc, s);
     } else {
       e = launch_forward<double, TS, TS>(p->e64, x, F, d, (double*)rd, s);
       if (e == hipSuccess)
         e = launch_adjoint<double, double, TS, TS>(p->e64, (const double*)rd, F, x, p->lam, (TS*)r,
                                                    sc, s);
     }
-    if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, (const TS*)r, F, p->N, (TS*)t, s);
-    if (e == hipSuccess) e = launch_tri_frames<TS, 1, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, s);
+    if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, (const TS*)r, F, p->N, (TS*)t, sc, s);
+    if (e == hipSuccess) e = launch_tri_frames<TS, 1, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, sc, s);
   }
   for (void* q : {rd, b, t, r})   // most recent first (the fixed-region scratch is a stack)
     if (q) (void)sc.put(q, s);
@@ -1381,8 +1381,8 @@ static pinv_status solve_item(pinv_plan* p, const void* data, int F, void* image
   else
     e = launch_adjoint<float, float, float, float>(p->e32, (const float*)data, F, nullptr, 0.0, x,
                                                    sc, s);
-  if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, x, F, p->N, (TS*)t, s);
-  if (e == hipSuccess) e = launch_tri_frames<TS, 2, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, s);
+  if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, x, F, p->N, (TS*)t, sc, s);
+  if (e == hipSuccess) e = launch_tri_frames<TS, 2, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, sc, s);
   const hipError_t f = sc.put(t, s);
   HIPCHK(e);
   HIPCHK(f);
@@ -1406,8 +1406,8 @@ static pinv_status solve_right_item(pinv_plan* p, const void* data, int F, void*
   if (e == hipSuccess) e = sc.get(&t, 2 * sizeof(TS) * (size_t)F * M, s);
   if (e == hipSuccess) e = sc.get(&r, 2 * sizeof(TS) * (size_t)F * M, s);
   if (e == hipSuccess && sizeof(TS) == 4) e = sc.get(&d64, 16 * (size_t)F * M, s);
-  if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>(Li, d, F, p->M, (TS*)t, s);
-  if (e == hipSuccess) e = launch_tri_frames<TS, 2, double>(Li, (const TS*)t, F, p->M, (double*)y, s);
+  if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>(Li, d, F, p->M, (TS*)t, sc, s);
+  if (e == hipSuccess) e = launch_tri_frames<TS, 2, double>(Li, (const TS*)t, F, p->M, (double*)y, sc, s);
   const double* b = nullptr;
   if constexpr (sizeof(TS) == 4) {
     if (e == hipSuccess) e = launch_to_f64((const float*)d, (double*)d64, (size_t)F * M, s);
@@ -1417,10 +1417,10 @@ static pinv_status solve_right_item(pinv_plan* p, const void* data, int F, void*
   }
   for (int it = 0; it < steps && e == hipSuccess; ++it) {
     e = launch_resid<double, TS>((const double*)p->gram, b, (const double*)y, F, p->M, p->lam,
-                                 (TS*)r, s);
-    if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>(Li, (const TS*)r, F, p->M, (TS*)t, s);
+                                 (TS*)r, sc, s);
+    if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>(Li, (const TS*)r, F, p->M, (TS*)t, sc, s);
     if (e == hipSuccess)
-      e = launch_tri_frames<TS, 1, double>(Li, (const TS*)t, F, p->M, (double*)y, s);
+      e = launch_tri_frames<TS, 1, double>(Li, (const TS*)t, F, p->M, (double*)y, sc, s);
   }
   if (e == hipSuccess)
     e = launch_adjoint<double, double, TS, TS>(p->e64, (const double*)y, F, nullptr, 0.0,
@@ -1459,27 +1459,30 @@ size_t item_scratch_bytes(const pinv_plan* p, int F, int steps) {
     const size_t adj = p->prec == PINV_FP64
                            ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
                            : adjoint_scratch_bytes<float, float, float, float>(p->e32, F);
-    peak = std::max(peak, al(2 * ts * F * N) + adj);
+    const size_t tri = tri_scratch_bytes(F, (int)N);
+    peak = std::max(peak, al(2 * ts * F * N) + std::max(adj, tri));
   }
   if (steps > 0 && p->right) {
     const size_t adj = p->prec == PINV_FP64
                            ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
                            : adjoint_scratch_bytes<double, double, float, float>(p->e64, F);
-    peak = std::max(peak, al(16 * F * M) + 2 * al(2 * ts * F * M) + (ts == 4 ? al(16 * F * M) : 0) + adj);
+    const size_t tri = tri_scratch_bytes(F, (int)M);
+    peak = std::max(peak, al(16 * F * M) + 2 * al(2 * ts * F * M) + (ts == 4 ? al(16 * F * M) : 0) +
+                              std::max({adj, tri, resid_scratch_bytes(F, (int)M)}));
   } else if (steps > 0) {
-    size_t refine = 2 * al(2 * ts * F * N);
-    if (p->gram_exact)
-      refine += al(16 * F * N) + (p->prec == PINV_FP64
-                                      ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
-                                      : std::max(grid_adjoint(p->e64, F) ? grid_adjoint_scratch_bytes(p->e64, F)
-                                                 : stored_adjoint(p->e64, F)
-                                                     ? stored_adjoint_scratch_bytes(p->e64, F)
-                                                     : 0,
-                                                 adjoint_scratch_bytes<double, float, float, double>(p->e64, F)));
+    size_t adj;
+    if (p->prec == PINV_FP64)
+      adj = adjoint_scratch_bytes<double, double, double, double>(p->e64, F);
+    else if (p->gram_exact)
+      adj = std::max(grid_adjoint(p->e64, F)     ? grid_adjoint_scratch_bytes(p->e64, F)
+                     : stored_adjoint(p->e64, F) ? stored_adjoint_scratch_bytes(p->e64, F)
+                                                 : 0,
+                     adjoint_scratch_bytes<double, float, float, double>(p->e64, F));
     else
-      refine += al(16 * F * M) + (p->prec == PINV_FP64
-                                      ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
-                                      : adjoint_scratch_bytes<double, double, float, float>(p->e64, F));
+      adj = adjoint_scratch_bytes<double, double, float, float>(p->e64, F);
+    const size_t tri = tri_scratch_bytes(F, (int)N);
+    const size_t refine = 2 * al(2 * ts * F * N) + al(16 * F * (p->gram_exact ? N : M)) +
+                          std::max({adj, tri, resid_scratch_bytes(F, (int)N)});
     peak = std::max(peak, refine);
   }
   return peak;

@@ -205,7 +205,7 @@ hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F,
                                  hipStream_t s);
 template <typename SX, typename SO>
 hipError_t launch_resid(const double* G, const double* b, const SX* X, int F, int N, double lam,
-                        SO* Out, hipStream_t s);
+                        SO* Out, Scratch& sc, hipStream_t s);
 hipError_t launch_herm_fill(double* G, int N, hipStream_t s);
 // The eigenvalue route: Jacobi eigendecomposition of the FP64 Hermitian N x N
 // matrix A (A2, V, V2: same-size workspaces; the results end in *A_out and
@@ -228,7 +228,10 @@ size_t psf_work_bytes(const EncDev<double>& e, int* splits);
 hipError_t launch_psf_gram(const EncDev<double>& e, void* work, double* G, double* Gk,
                            hipStream_t s);
 template <typename T, int MODE, typename SO>
-hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, hipStream_t s);
+hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, Scratch& sc, hipStream_t s);
+// Scratch bytes of these two for F frames (parts of a split contraction).
+size_t resid_scratch_bytes(int F, int N);
+size_t tri_scratch_bytes(int F, int N);
 // Split-precision (BF16x3) plans keep their operands split-packed (SP): a
 // complex matrix with k contiguous, rows of sp_cols(K) columns (zero past K),
 // each 8 consecutive k of a row stored as bf16 planes re_hi, re_lo, im_hi,

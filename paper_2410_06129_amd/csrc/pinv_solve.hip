@@ -107,10 +107,13 @@ __global__ __launch_bounds__(256, (MinBlocks<Cfg, FEAT>::value)) void k_adjoint(
 //   mode 0: Y[f][i] = sum_{n <= i} Xin[f][n] Li[i][n]          (L^-1 x, per frame)
 //   mode 1: X[f][i] += sum_{n >= i} Yin[f][n] conj(Li[n][i])   (L^-H y, accumulated)
 //   mode 2: X[f][i] = sum_{n >= i} Yin[f][n] conj(Li[n][i])    (L^-H y)
-template <class Cfg, int MODE, typename SO>
-__global__ __launch_bounds__(256) void k_tri_frames(const typename Cfg::T* __restrict__ Li,
-                                                    const typename Cfg::T* __restrict__ In, int F,
-                                                    int N, SO* __restrict__ Out) {
+// (S = storage type of L^-1 and of the frames.)
+// With `work`, workgroup split * tiles + tile takes one of `splits` equal parts of its
+// tile's contraction and stores the raw sum to work[split] (k_parts_sum adds them).
+template <class Cfg, int MODE, typename SO, typename S>
+__global__ __launch_bounds__(256) void k_tri_frames(const S* __restrict__ Li, const S* __restrict__ In, int F,
+                                                    int N, SO* __restrict__ Out, int splits,
+                                                    typename Cfg::T* __restrict__ work) {
   typedef typename Cfg::T T;
   const int nbj = (N + Cfg::BN - 1) / Cfg::BN;
   const int nbi = (F + Cfg::BM - 1) / Cfg::BM;
@@ -120,35 +123,46 @@ __global__ __launch_bounds__(256) void k_tri_frames(const typename Cfg::T* __res
   // workgroups t and t + half, which the dispatcher tends to place on one CU,
   // carry one long and one short tile.
   const int total = nbi * nbj, half = (total + 1) / 2;
-  const int t = (int)blockIdx.x;
+  const int split = (int)blockIdx.x / total, t = (int)blockIdx.x - split * total;
   const int r = t < half ? t : total - 1 + half - t;
   const int jr = r / nbi;                       // 0 = longest block column
   const int bi = r - jr * nbi;
   const int bj = MODE == 0 ? nbj - 1 - jr : jr;
-  LoadDenseKC<Cfg, Cfg::BM, Cfg::LDA, T, false> la;
-  la.p = reinterpret_cast<const cx<T>*>(In);
+  LoadDenseKC<Cfg, Cfg::BM, Cfg::LDA, S, false> la;
+  la.p = reinterpret_cast<const cx<S>*>(In);
   la.ld = N;
   la.o0 = bi * Cfg::BM;
   la.oend = F;
   AccTile<Cfg> acc;
   acc.zero();
+  int k0 = MODE == 0 ? 0 : bj * Cfg::BN, k1 = MODE == 0 ? min(N, (bj + 1) * Cfg::BN) : N;
+  const int part = ((k1 - k0 + Cfg::BK - 1) / Cfg::BK + splits - 1) / splits * Cfg::BK;
+  k0 = min(k1, k0 + split * part);
+  k1 = min(k1, k0 + part);
   if (MODE == 0) {
-    LoadDenseKC<Cfg, Cfg::BN, Cfg::LDB, T, false> lb;   // (o=i, k=n) at Li[i*N+n]
-    lb.p = reinterpret_cast<const cx<T>*>(Li);
+    LoadDenseKC<Cfg, Cfg::BN, Cfg::LDB, S, false> lb;   // (o=i, k=n) at Li[i*N+n]
+    lb.p = reinterpret_cast<const cx<S>*>(Li);
     lb.ld = N;
     lb.o0 = bj * Cfg::BN;
     lb.oend = N;
-    mainloop<Cfg>(la, lb, 0, min(N, (bj + 1) * Cfg::BN), acc, smem_base<Cfg>());
+    mainloop<Cfg>(la, lb, k0, k1, acc, smem_base<Cfg>());
   } else {
-    LoadDenseOC<Cfg, Cfg::BN, Cfg::LDB, T, true> lb;    // (o=i, k=n) at conj Li[n*N+i]
-    lb.p = reinterpret_cast<const cx<T>*>(Li);
+    LoadDenseOC<Cfg, Cfg::BN, Cfg::LDB, S, true> lb;    // (o=i, k=n) at conj Li[n*N+i]
+    lb.p = reinterpret_cast<const cx<S>*>(Li);
     lb.ld = N;
     lb.o0 = bj * Cfg::BN;
     lb.oend = N;
-    mainloop<Cfg>(la, lb, bj * Cfg::BN, N, acc, smem_base<Cfg>());
+    mainloop<Cfg>(la, lb, k0, k1, acc, smem_base<Cfg>());
   }
   cx<SO>* O = reinterpret_cast<cx<SO>*>(Out);
   const int r0 = bi * Cfg::BM, c0 = bj * Cfg::BN;
+  if (work) {
+    cx<T>* W = reinterpret_cast<cx<T>*>(work) + (size_t)split * F * N;
+    acc_foreach<Cfg>(acc, [&](int r, int c, T re, T im) {
+      if (r0 + r < F && c0 + c < N) W[(size_t)(r0 + r) * N + c0 + c] = cx<T>{re, im};
+    });
+    return;
+  }
   acc_foreach<Cfg>(acc, [&](int r, int c, T re, T im) {
     const int row = r0 + r, col = c0 + c;
     if (row < F && col < N) {
@@ -165,15 +179,20 @@ __global__ __launch_bounds__(256) void k_tri_frames(const typename Cfg::T* __res
 
 // Normal-equation residual through the Gram (Eq. 6):
 //   Out[f][a] = b[f][a] - sum_n G[a][n] X[f][n] - lam X[f][a]
-// with G the full Hermitian FP64 Gram [N][N] and b = E^H d in FP64.
+// with G the full Hermitian FP64 Gram [N][N] and b = E^H d in FP64.  With `work` the
+// contraction is in `splits` parts, as in k_tri_frames.
 template <class Cfg, typename SX, typename SO>
 __global__ __launch_bounds__(256, MinBlocks<Cfg>::value) void k_resid(const double* __restrict__ G,
                                                const double* __restrict__ b,
                                                const SX* __restrict__ X, int F, int N, double lam,
-                                               SO* __restrict__ Out) {
+                                               SO* __restrict__ Out, int splits,
+                                               double* __restrict__ work) {
   typedef typename Cfg::T T;
   const int nbj = (N + Cfg::BN - 1) / Cfg::BN;
-  const int t = blockIdx.x;
+  const int tiles = (F + Cfg::BM - 1) / Cfg::BM * nbj;
+  const int split = blockIdx.x / tiles, t = blockIdx.x - split * tiles;
+  const int part = ((N + Cfg::BK - 1) / Cfg::BK + splits - 1) / splits * Cfg::BK;
+  const int k0 = min(N, split * part), k1 = min(N, k0 + part);
   const int bi = t / nbj, bj = t % nbj;
   LoadDenseKC<Cfg, Cfg::BM, Cfg::LDA, SX, false> la;     // X[f][n]
   la.p = reinterpret_cast<const cx<SX>*>(X);
@@ -187,7 +206,15 @@ __global__ __launch_bounds__(256, MinBlocks<Cfg>::value) void k_resid(const doub
   lb.oend = N;
   AccTile<Cfg> acc;
   acc.zero();
-  mainloop<Cfg>(la, lb, 0, N, acc, smem_base<Cfg>());
+  mainloop<Cfg>(la, lb, k0, k1, acc, smem_base<Cfg>());
+  if (work) {
+    cx<double>* W = reinterpret_cast<cx<double>*>(work) + (size_t)split * F * N;
+    const int r0 = bi * Cfg::BM, c0 = bj * Cfg::BN;
+    acc_foreach<Cfg>(acc, [&](int r, int c, T re, T im) {
+      if (r0 + r < F && c0 + c < N) W[(size_t)(r0 + r) * N + c0 + c] = cx<double>{re, im};
+    });
+    return;
+  }
   cx<SO>* O = reinterpret_cast<cx<SO>*>(Out);
   const cx<double>* bc = reinterpret_cast<const cx<double>*>(b);
   const cx<SX>* Xc = reinterpret_cast<const cx<SX>*>(X);
@@ -204,6 +231,42 @@ __global__ __launch_bounds__(256, MinBlocks<Cfg>::value) void k_resid(const doub
   });
 }
 
+
+// A split contraction's parts summed in order, n values each: mode 0 or 2 Out = sum,
+// mode 1 Out += sum, mode 3 Out = b - sum - lam X.
+template <int MODE, typename SX, typename SO>
+__global__ __launch_bounds__(256) void k_parts_sum(const double* __restrict__ work, int splits, int64_t n,
+                                                   const double* __restrict__ b, const SX* __restrict__ X,
+                                                   double lam, SO* __restrict__ Out) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const cx<double>* W = reinterpret_cast<const cx<double>*>(work);
+  cx<SO>* O = reinterpret_cast<cx<SO>*>(Out);
+  cx<double> z = W[i];
+  for (int q = 1; q < splits; ++q) {
+    z.re += W[q * n + i].re;
+    z.im += W[q * n + i].im;
+  }
+  if (MODE == 1) {
+    const cx<SO> x = O[i];
+    O[i] = cx<SO>{SO(x.re + z.re), SO(x.im + z.im)};
+  } else if (MODE == 3) {
+    const cx<double> bb = reinterpret_cast<const cx<double>*>(b)[i];
+    const cx<SX> x = reinterpret_cast<const cx<SX>*>(X)[i];
+    O[i] = cx<SO>{SO(bb.re - z.re - lam * (double)x.re), SO(bb.im - z.im - lam * (double)x.im)};
+  } else {
+    O[i] = cx<SO>{SO(z.re), SO(z.im)};
+  }
+}
+
+// Parts of a contraction of `chunks` chunks over `tiles` workgroups: enough to put one
+// workgroup on each of 512 places, of at least 8 chunks.  A refinement's residual and
+// triangular products at few frames were three chains of N / 8 chunks on a few CUs, whole
+// against in parts: N = 1024, 64 frames 455 / 89 us; 2304, 1 frame 991 / 162; 4096, 1 frame
+// 1748 / 420, 250 frames (2 parts) 1797 / 1624; 16384, 1 frame 7.0 / 6.2 ms.
+static int few_splits(long tiles, int chunks) {
+  return (int)std::max<long>(1, std::min<long>(512 / std::max<long>(tiles, 1), chunks / 8));
+}
 
 // Elementwise FP64 -> FP32 complex copy (n complex values).
 __global__ void k_to_f32(const double* __restrict__ in, float* __restrict__ out, size_t n2) {
@@ -417,26 +480,84 @@ hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F,
   return err != hipSuccess ? err : ferr;
 }
 
+static int resid_splits(int F, int N) {
+  typedef F64Cfg3 Cfg;
+  return few_splits((long)cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN), cdiv(N, Cfg::BK));
+}
+// Triangular products in parts are summed in FP64, also from an FP32 factor: in FP32 the
+// parts' rounding adds to the refined images' error (one coil of 64 x 64, 50 frames, one
+// step: 4.0e-8 in one FP32 sum, 4.4e-8 in FP32 parts, 2.6e-8 like this).
+static int tri_splits(int F, int N) {   // (a tile's mean contraction: N / 2)
+  typedef F64Cfg3 Cfg;
+  return few_splits((long)cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN), cdiv(N, 2 * Cfg::BK));
+}
+
+size_t resid_scratch_bytes(int F, int N) {
+  const int q = resid_splits(F, N);
+  return q > 1 ? (size_t)q * F * N * 16 : 0;
+}
+size_t tri_scratch_bytes(int F, int N) {
+  const int q = tri_splits(F, N);
+  return q > 1 ? (size_t)q * F * N * 16 : 0;
+}
+
+// Scratch for a split's parts; without it the contraction runs whole (*splits = 1).
+static hipError_t parts_get(void** work, int* splits, size_t bytes, Scratch& sc, hipStream_t s) {
+  *work = nullptr;
+  if (*splits <= 1) return hipSuccess;
+  hipError_t err = sc.get(work, bytes, s);
+  if (err == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    *work = nullptr;
+    *splits = 1;
+    err = hipSuccess;
+  }
+  return err;
+}
+
 template <typename SX, typename SO>
 hipError_t launch_resid(const double* G, const double* b, const SX* X, int F, int N, double lam,
-                        SO* Out, hipStream_t s) {
+                        SO* Out, Scratch& sc, hipStream_t s) {
   typedef F64Cfg3 Cfg;
   const int tiles = cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN);
   if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_resid<Cfg, SX, SO>), dim3(tiles), dim3(256), smem_bytes<Cfg>(), s, G, b, X,
-                     F, N, lam, Out);
-  return hipGetLastError();
+  int splits = resid_splits(F, N);
+  void* work = nullptr;
+  hipError_t err = parts_get(&work, &splits, resid_scratch_bytes(F, N), sc, s);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL((k_resid<Cfg, SX, SO>), dim3(tiles * splits), dim3(256), smem_bytes<Cfg>(), s, G, b, X,
+                     F, N, lam, Out, splits, (double*)work);
+  if (!work) return hipGetLastError();
+  const int64_t n = (int64_t)F * N;
+  hipLaunchKernelGGL((k_parts_sum<3, SX, SO>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                     (const double*)work, splits, n, b, X, lam, Out);
+  err = hipGetLastError();
+  const hipError_t ferr = sc.put(work, s);
+  return err != hipSuccess ? err : ferr;
 }
 
-
 template <typename T, int MODE, typename SO>
-hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, hipStream_t s) {
-  typedef typename PickCfg<T>::type Cfg;
-  const int tiles = cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN);
-  if (tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_tri_frames<Cfg, MODE, SO>), dim3(tiles), dim3(256), smem_bytes<Cfg>(), s,
-                     Li, In, F, N, Out);
-  return hipGetLastError();
+hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, Scratch& sc, hipStream_t s) {
+  if (F <= 0 || N <= 0) return hipSuccess;
+  int splits = tri_splits(F, N);
+  void* work = nullptr;
+  hipError_t err = parts_get(&work, &splits, tri_scratch_bytes(F, N), sc, s);
+  if (err != hipSuccess) return err;
+  if (!work) {
+    typedef typename PickCfg<T>::type Cfg;
+    hipLaunchKernelGGL((k_tri_frames<Cfg, MODE, SO, T>), dim3(cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN)), dim3(256),
+                       smem_bytes<Cfg>(), s, Li, In, F, N, Out, 1, (T*)nullptr);
+    return hipGetLastError();
+  }
+  typedef F64Cfg3 Cfg;
+  hipLaunchKernelGGL((k_tri_frames<Cfg, MODE, SO, T>), dim3(cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN) * splits),
+                     dim3(256), smem_bytes<Cfg>(), s, Li, In, F, N, Out, splits, (double*)work);
+  const int64_t n = (int64_t)F * N;
+  hipLaunchKernelGGL((k_parts_sum<MODE, double, SO>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                     (const double*)work, splits, n, (const double*)nullptr, (const double*)nullptr, 0.0, Out);
+  err = hipGetLastError();
+  const hipError_t ferr = sc.put(work, s);
+  return err != hipSuccess ? err : ferr;
 }
 
 
@@ -464,27 +585,27 @@ template hipError_t launch_forward<double, double, double>(const EncDev<double>&
 template hipError_t launch_forward<double, float, float>(const EncDev<double>&, const float*, int,
                                                          const float*, double*, hipStream_t);
 template hipError_t launch_resid<float, float>(const double*, const double*, const float*, int, int,
-                                               double, float*, hipStream_t);
+                                               double, float*, Scratch&, hipStream_t);
 template hipError_t launch_resid<double, double>(const double*, const double*, const double*, int,
-                                                 int, double, double*, hipStream_t);
+                                                 int, double, double*, Scratch&, hipStream_t);
 template hipError_t launch_resid<double, float>(const double*, const double*, const double*, int,
-                                                int, double, float*, hipStream_t);
+                                                int, double, float*, Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<float, 1, double>(const float*, const float*, int, int, double*,
-                                                        hipStream_t);
+                                                        Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<float, 2, double>(const float*, const float*, int, int, double*,
-                                                        hipStream_t);
+                                                        Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<float, 0, float>(const float*, const float*, int, int, float*,
-                                                       hipStream_t);
+                                                       Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<float, 1, float>(const float*, const float*, int, int, float*,
-                                                       hipStream_t);
+                                                       Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<double, 0, double>(const double*, const double*, int, int,
-                                                         double*, hipStream_t);
+                                                         double*, Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<double, 1, double>(const double*, const double*, int, int,
-                                                         double*, hipStream_t);
+                                                         double*, Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<double, 2, double>(const double*, const double*, int, int,
-                                                         double*, hipStream_t);
+                                                         double*, Scratch&, hipStream_t);
 template hipError_t launch_tri_frames<float, 2, float>(const float*, const float*, int, int, float*,
-                                                       hipStream_t);
+                                                       Scratch&, hipStream_t);
 template hipError_t launch_adjoint<double, double, float, float>(const EncDev<double>&, const double*, int,
     const float*, double, float*, Scratch&, hipStream_t);
 template size_t adjoint_scratch_bytes<double, double, float, float>(const EncDev<double>&, int);
