@@ -1431,8 +1431,9 @@ static pinv_status solve_right_item(pinv_plan* p, const void* data, int F, void*
   return PINV_OK;
 }
 
-// Scratch bytes one item's apply takes from a fixed region (the stack peak of
-// the steps apply_items runs for it).
+// Scratch bytes one item's apply needs from a fixed region (the stack peak of
+// the steps apply_items runs for it).  Steps with a faster form that takes more (f16
+// pieces, gridding, a stored F^H, contractions in parts) use it where the region holds it.
 size_t item_scratch_bytes(const pinv_plan* p, int F, int steps) {
   if (F <= 0) return 0;
   auto al = [](size_t n) { return (n + 255) & ~size_t(255); };
@@ -1459,30 +1460,23 @@ size_t item_scratch_bytes(const pinv_plan* p, int F, int steps) {
     const size_t adj = p->prec == PINV_FP64
                            ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
                            : adjoint_scratch_bytes<float, float, float, float>(p->e32, F);
-    const size_t tri = tri_scratch_bytes(F, (int)N);
-    peak = std::max(peak, al(2 * ts * F * N) + std::max(adj, tri));
+    peak = std::max(peak, al(2 * ts * F * N) + adj);
   }
   if (steps > 0 && p->right) {
     const size_t adj = p->prec == PINV_FP64
                            ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
                            : adjoint_scratch_bytes<double, double, float, float>(p->e64, F);
-    const size_t tri = tri_scratch_bytes(F, (int)M);
-    peak = std::max(peak, al(16 * F * M) + 2 * al(2 * ts * F * M) + (ts == 4 ? al(16 * F * M) : 0) +
-                              std::max({adj, tri, resid_scratch_bytes(F, (int)M)}));
+    peak = std::max(peak, al(16 * F * M) + 2 * al(2 * ts * F * M) + (ts == 4 ? al(16 * F * M) : 0) + adj);
   } else if (steps > 0) {
-    size_t adj;
-    if (p->prec == PINV_FP64)
-      adj = adjoint_scratch_bytes<double, double, double, double>(p->e64, F);
-    else if (p->gram_exact)
-      adj = std::max(grid_adjoint(p->e64, F)     ? grid_adjoint_scratch_bytes(p->e64, F)
-                     : stored_adjoint(p->e64, F) ? stored_adjoint_scratch_bytes(p->e64, F)
-                                                 : 0,
-                     adjoint_scratch_bytes<double, float, float, double>(p->e64, F));
+    size_t refine = 2 * al(2 * ts * F * N);
+    if (p->gram_exact)
+      refine += al(16 * F * N) + (p->prec == PINV_FP64
+                                      ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
+                                      : adjoint_scratch_bytes<double, float, float, double>(p->e64, F));
     else
-      adj = adjoint_scratch_bytes<double, double, float, float>(p->e64, F);
-    const size_t tri = tri_scratch_bytes(F, (int)N);
-    const size_t refine = 2 * al(2 * ts * F * N) + al(16 * F * (p->gram_exact ? N : M)) +
-                          std::max({adj, tri, resid_scratch_bytes(F, (int)N)});
+      refine += al(16 * F * M) + (p->prec == PINV_FP64
+                                      ? adjoint_scratch_bytes<double, double, double, double>(p->e64, F)
+                                      : adjoint_scratch_bytes<double, double, float, float>(p->e64, F));
     peak = std::max(peak, refine);
   }
   return peak;

@@ -671,8 +671,6 @@ size_t apply_scratch_bytes(int F, int N, int M, bool m3, bool seg) {
     typedef ApplyCfgOf<T, decltype(form)::value> C;
     constexpr bool S = std::is_same<T, float>::value && decltype(sg)::value;
     if (std::is_same<T, float>::value && F <= kStreamMaxF) return apply_stream_scratch_bytes(F, N, M);
-    if (std::is_same<T, float>::value && half_apply(F, N, M, decltype(form)::value, S))
-      return apply_half_scratch_bytes(F, N, M);
     return item_work_bytes<typename C::many, S>(F, N, M);
   };
   if (seg)

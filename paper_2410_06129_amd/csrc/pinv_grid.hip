@@ -41,7 +41,7 @@ struct GridPlan {
   size_t grid, work;
 };
 
-static GridPlan grid_plan(const EncDev<double>& e, int F) {
+static GridPlan grid_plan(const EncDev<double>& e, int F, size_t room) {
   GridPlan g{};
   g.gx = 2 * e.nx;
   g.gy = 2 * e.ny;
@@ -73,7 +73,12 @@ static GridPlan grid_plan(const EncDev<double>& e, int F) {
   const size_t row = 16 * (size_t)g.gy * g.gx + half, rows = (size_t)e.C * e.S;
   int q = 64;   // whole 64-row tiles per pass
   while (q > 1 && (rows * (q / 2)) % 64 == 0) q /= 2;
-  int f = (int)std::min<size_t>((size_t)F, std::max<size_t>(1, kGridBytes / (row * rows)));
+  // as many frames as a pass may take; none where the scratch left holds neither all of
+  // them nor a quarter of a pass (many short passes take longer than the direct sum)
+  const size_t left = room > g.tables + 512 ? room - g.tables - 512 : 0, fit = std::min(kGridBytes, left);
+  int f = (int)std::min<size_t>((size_t)F, fit / (row * rows));
+  if (f < F && fit < kGridBytes / 4) f = 0;
+  if (f == 0) return g;
   if (f < F) {
     if (f >= q) f = f / q * q;
     const int passes = cdiv(F, f);
@@ -414,20 +419,16 @@ bool grid_adjoint(const EncDev<double>& e, int F) {
   if (e.b0 || e.nx < kGridMin || e.ny < kGridMin || F <= 0) return false;
   const double rows = (double)F * e.C * e.S, img = (double)e.nx * e.ny;
   // a frame's grids fit a pass (and its rows a launch's y dimension)
-  if (64.0 * 2.0 * img * e.C * e.S > (double)kGridBytes) return false;
+  if (grid_plan(e, 1, SIZE_MAX).frames == 0) return false;
   const double direct = 3.0 * rows * e.K * e.V;
   const double grid = rows * (2.0 * 529.0 * e.K + 3.0 * img * (4.0 * e.nx + 2.0 * e.ny));
   return direct >= 1.75 * grid && direct >= 1e7;
 }
 
-size_t grid_adjoint_scratch_bytes(const EncDev<double>& e, int F) {
-  const GridPlan g = grid_plan(e, F);
-  return ((g.tables + 255) & ~size_t(255)) + g.work;
-}
-
 hipError_t launch_grid_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                hipStream_t s) {
-  const GridPlan g = grid_plan(e, F);
+  const GridPlan g = grid_plan(e, F, sc.room());
+  if (g.frames == 0) return hipErrorOutOfMemory;
   void *tab = nullptr, *work = nullptr;
   hipError_t err = sc.get(&tab, g.tables, s);
   if (err != hipSuccess) return err;

@@ -676,8 +676,6 @@ static HalfApply half_apply_plan(int F, int N, int M) {
   return best;
 }
 
-size_t apply_half_scratch_bytes(int F, int N, int M) { return half_apply_plan(F, N, M).bytes(); }
-
 hipError_t launch_apply_half(const float* R, const float* D, float* X, int N, int M, int F, Scratch& sc,
                              hipStream_t s) {
   if (F <= 0 || N <= 0) return hipSuccess;

@@ -106,6 +106,11 @@ struct Scratch {
     peak = std::max(peak, top);
     return hipSuccess;
   }
+  // Bytes the next get may ask for.
+  size_t room() const {
+    const size_t start = (top + 255) & ~size_t(255);
+    return !base ? SIZE_MAX : depth >= 16 || start >= cap ? 0 : cap - start;
+  }
   hipError_t put(void* p, hipStream_t s) {
     if (!base) return cache->put(p, s);
     if (depth > 0 && stack[depth - 1].p == p) top = stack[--depth].start;
@@ -193,14 +198,12 @@ template <typename T, typename SD, typename SX, typename SO>
 size_t adjoint_scratch_bytes(const EncDev<T>& e, int F);
 // b = E^H D in FP64 (complex64 D, F x M) by gridding: for encodings without an
 // off-resonance map, where grid_adjoint() says that it takes less time than the direct
-// sum.  All-or-nothing scratch: hipErrorOutOfMemory leaves the direct sum to do.
+// sum.  hipErrorOutOfMemory (too little scratch) leaves the direct sum to do.
 bool grid_adjoint(const EncDev<double>& e, int F);
-size_t grid_adjoint_scratch_bytes(const EncDev<double>& e, int F);
 hipError_t launch_grid_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                hipStream_t s);
 // The same through a stored F^H, where stored_adjoint() says so.
 bool stored_adjoint(const EncDev<double>& e, int F);
-size_t stored_adjoint_scratch_bytes(const EncDev<double>& e, int F);
 hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                  hipStream_t s);
 template <typename SX, typename SO>
@@ -229,9 +232,6 @@ hipError_t launch_psf_gram(const EncDev<double>& e, void* work, double* G, doubl
                            hipStream_t s);
 template <typename T, int MODE, typename SO>
 hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, Scratch& sc, hipStream_t s);
-// Scratch bytes of these two for F frames (parts of a split contraction).
-size_t resid_scratch_bytes(int F, int N);
-size_t tri_scratch_bytes(int F, int N);
 // Split-precision (BF16x3) plans keep their operands split-packed (SP): a
 // complex matrix with k contiguous, rows of sp_cols(K) columns (zero past K),
 // each 8 consecutive k of a row stored as bf16 planes re_hi, re_lo, im_hi,
@@ -280,9 +280,8 @@ hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor
                           int64_t slab_rows, int es, void* Wt, hipStream_t s);
 hipError_t launch_trmm_rh(const double* Li, void* factor, const void* Wt, float* R, int N, int M,
                           hipStream_t s);
-// X = D R^T of F frames on f16 pieces; scratch of apply_half_scratch_bytes (at
-// most 256 MB and the rounding of its parts, whatever the sizes).
-size_t apply_half_scratch_bytes(int F, int N, int M);
+// X = D R^T of F frames on f16 pieces; at most 256 MB of scratch and the rounding of its
+// parts, whatever the sizes (hipErrorOutOfMemory leaves the tiles to do).
 hipError_t launch_apply_half(const float* R, const float* D, float* X, int N, int M, int F, Scratch& sc,
                              hipStream_t s);
 hipError_t launch_to_f32(const double* in, float* out, size_t n_complex, hipStream_t s);

@@ -418,13 +418,13 @@ struct StoredPlan {
   int splits, kchunk, n;   // contraction split, columns per slab (0: a slab does not fit)
   size_t bytes;
 };
-static StoredPlan stored_plan(const EncDev<double>& e, int F) {
+static StoredPlan stored_plan(const EncDev<double>& e, int F, size_t room) {
   typedef F64Cfg3 Cfg;
   const int64_t rows = (int64_t)F * e.C;
   StoredPlan p{};
   const int nchunks = cdiv(e.K, Cfg::BK);
   auto columns = [&](int splits) {
-    const int64_t n = (int64_t)(kStoredBytes / (16 * ((size_t)e.K + splits * rows)));
+    const int64_t n = (int64_t)(std::min(kStoredBytes, room) / (16 * ((size_t)e.K + splits * rows)));
     return (int)std::min<int64_t>(e.N, n >= e.N ? n : n / Cfg::BN * Cfg::BN);
   };
   const int n1 = columns(1);
@@ -448,15 +448,15 @@ static StoredPlan stored_plan(const EncDev<double>& e, int F) {
 // 16 x 16 without a map, 8 coils, 500 frames 785 / 425, 8 x 8, 4 coils, 5 frames 83 / 83.
 // With one coil, at most 64 frames and no map nothing is formed twice (212 / 217).
 bool stored_adjoint(const EncDev<double>& e, int F) {
-  return F > 0 && (e.C > 1 || e.b0 || F > F64Cfg3::BM) && stored_plan(e, F).n > 0;
+  return F > 0 && (e.C > 1 || e.b0 || F > F64Cfg3::BM) && stored_plan(e, F, SIZE_MAX).n > 0;
 }
-
-size_t stored_adjoint_scratch_bytes(const EncDev<double>& e, int F) { return stored_plan(e, F).bytes; }
 
 hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                  hipStream_t s) {
   typedef F64Cfg3 Cfg;
-  const StoredPlan p = stored_plan(e, F);
+  const StoredPlan p = stored_plan(e, F, sc.room());
+  // (slabs of few columns would read the data over and over)
+  if (p.n == 0 || (p.n < e.N && p.bytes < kStoredBytes / 4)) return hipErrorOutOfMemory;
   void* work = nullptr;
   hipError_t err = sc.get(&work, p.bytes, s);
   if (err != hipSuccess) return err;
@@ -492,20 +492,11 @@ static int tri_splits(int F, int N) {   // (a tile's mean contraction: N / 2)
   return few_splits((long)cdiv(F, Cfg::BM) * cdiv(N, Cfg::BN), cdiv(N, 2 * Cfg::BK));
 }
 
-size_t resid_scratch_bytes(int F, int N) {
-  const int q = resid_splits(F, N);
-  return q > 1 ? (size_t)q * F * N * 16 : 0;
-}
-size_t tri_scratch_bytes(int F, int N) {
-  const int q = tri_splits(F, N);
-  return q > 1 ? (size_t)q * F * N * 16 : 0;
-}
-
 // Scratch for a split's parts; without it the contraction runs whole (*splits = 1).
-static hipError_t parts_get(void** work, int* splits, size_t bytes, Scratch& sc, hipStream_t s) {
+static hipError_t parts_get(void** work, int* splits, int F, int N, Scratch& sc, hipStream_t s) {
   *work = nullptr;
   if (*splits <= 1) return hipSuccess;
-  hipError_t err = sc.get(work, bytes, s);
+  hipError_t err = sc.get(work, (size_t)*splits * F * N * 16, s);
   if (err == hipErrorOutOfMemory) {
     (void)hipGetLastError();
     *work = nullptr;
@@ -523,7 +514,7 @@ hipError_t launch_resid(const double* G, const double* b, const SX* X, int F, in
   if (tiles == 0) return hipSuccess;
   int splits = resid_splits(F, N);
   void* work = nullptr;
-  hipError_t err = parts_get(&work, &splits, resid_scratch_bytes(F, N), sc, s);
+  hipError_t err = parts_get(&work, &splits, F, N, sc, s);
   if (err != hipSuccess) return err;
   hipLaunchKernelGGL((k_resid<Cfg, SX, SO>), dim3(tiles * splits), dim3(256), smem_bytes<Cfg>(), s, G, b, X,
                      F, N, lam, Out, splits, (double*)work);
@@ -541,7 +532,7 @@ hipError_t launch_tri_frames(const T* Li, const T* In, int F, int N, SO* Out, Sc
   if (F <= 0 || N <= 0) return hipSuccess;
   int splits = tri_splits(F, N);
   void* work = nullptr;
-  hipError_t err = parts_get(&work, &splits, tri_scratch_bytes(F, N), sc, s);
+  hipError_t err = parts_get(&work, &splits, F, N, sc, s);
   if (err != hipSuccess) return err;
   if (!work) {
     typedef typename PickCfg<T>::type Cfg;

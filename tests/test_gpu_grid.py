@@ -100,3 +100,23 @@ def test_a_frame_with_infinities_stays_alone(P, ctx):
     x = refined(P, ctx, enc, d)
     assert not np.any(np.isfinite(x[3]))
     assert np.array_equal(np.delete(x, 3, 0), np.delete(good, 3, 0))
+
+
+def test_noalloc_takes_what_the_region_holds(P, ctx):
+    """The call asks for at most 531 of the fixed region's 537 MB (the refinement vectors'
+    177 and up to four parts of the direct sum), and E^H d is formed beside the vectors,
+    with room for shorter passes over the grids only: it is not refused, and agrees with
+    the allocating call to the images' rounding (two of them: 2e-7)."""
+    F = 5400
+    enc = synth.small_case(seed=1010, nx=32, ny=32, C=2, K=600, F=1).enc
+    plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED)
+    P.pinv_plan_wait(plan)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    d = torch.view_as_complex(torch.randn(F, enc.M, 2, device="cuda", generator=g))
+    x, y = (torch.full((F, enc.N), float("nan"), dtype=torch.complex64, device="cuda") for _ in range(2))
+    P.pinv_apply(ctx, plan, d, x, refine_steps=2)
+    P.pinv_apply_noalloc(ctx, plan, d, y, refine_steps=2)
+    torch.cuda.synchronize()
+    P.pinv_plan_release(plan)
+    err = torch.linalg.vector_norm(y - x, dim=1) / torch.linalg.vector_norm(x, dim=1)
+    assert float(err.max()) <= 2e-7
