@@ -65,6 +65,27 @@ hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
   const size_t need = rounded(bytes);
   std::lock_guard<std::mutex> g(mu_);
   const size_t most = need + need / (need > (256u << 20) ? 64 : 8);
+  // Under graph capture: a block that this capture gave back on this stream, or a new one,
+  // kept until the context is destroyed.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (s && hipStreamGetCaptureInfo(s, &cap, &id) != hipSuccess) (void)hipGetLastError();
+  if (cap == hipStreamCaptureStatusActive) {
+    for (auto& c : captured_) {
+      Captured& b = c.second;
+      if (!b.idle || b.id != id || b.s != s || b.bytes < need || b.bytes > most) continue;
+      b.idle = false;
+      *p = c.first;
+      return hipSuccess;
+    }
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // allows the allocation
+    hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
+    if (r != hipSuccess) return r;
+    r = hipMalloc(p, need);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (r == hipSuccess) captured_[*p] = Captured{need, id, s, false};
+    return r;
+  }
   for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
     Idle& b = it->second;
     if (b.ev) {
@@ -97,6 +118,11 @@ void DeviceCache::add(void* p, hipEvent_t ev, hipStream_t s) {
 
 hipError_t DeviceCache::put(void* p, hipStream_t s) {
   std::lock_guard<std::mutex> g(mu_);
+  auto c = captured_.find(p);
+  if (c != captured_.end()) {
+    c->second.idle = c->second.s == s;
+    return hipSuccess;
+  }
   hipEvent_t ev = nullptr;
   hipError_t e = hipSuccess;
   if (!events_.empty()) {
@@ -145,6 +171,8 @@ void DeviceCache::release_all() {
   std::lock_guard<std::mutex> g(mu_);
   for (auto& kv : live_) (void)hipFree(kv.first);
   live_.clear();
+  for (auto& kv : captured_) (void)hipFree(kv.first);
+  captured_.clear();
 }
 
 size_t DeviceCache::idle_bytes() {

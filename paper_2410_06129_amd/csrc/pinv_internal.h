@@ -67,6 +67,15 @@ class DeviceCache {
   std::multimap<size_t, Idle> idle_;
   std::map<void*, size_t> live_;
   std::vector<hipEvent_t> events_;   // spare events
+  // Blocks handed out to a stream under graph capture, which belong to that capture for
+  // good: a replay may use them at any time.
+  struct Captured {
+    size_t bytes;
+    unsigned long long id;   // of the capture
+    hipStream_t s;
+    bool idle;
+  };
+  std::map<void*, Captured> captured_;
 };
 
 // Scratch memory of one call (split-contraction partials, refinement
