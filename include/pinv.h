@@ -277,8 +277,9 @@ pinv_status pinv_encoding_key(const pinv_encoding *e, const pinv_build_opts *o, 
  * plan (see conventions).  A factor-only plan (PINV_FLAG_NO_R) gives
  * image = L^-H L^-1 E^H data instead, E^H data formed with E generated in the
  * plan's precision.  refine_steps (0..4) adds iterative refinement on
- * the normal equations (Eq. 6): r = E^H (d - E x) - lambda x in FP64 with E
- * regenerated in FP64, then x += L^-H L^-1 r.  Plans with M < N refine on the
+ * the normal equations (Eq. 6): r = E^H (d - E x) - lambda x in FP64 (E^H d by
+ * gridding to FP64 rounding where there is no off-resonance map, else with E
+ * formed in FP64), then x += L^-H L^-1 r.  Plans with M < N refine on the
  * sample side instead: y = G'^-1 d with G' = E E^H + lambda I refined against
  * the FP64 G', then x = E^H y with E in FP64.  Applies of a few frames read
  * R once, bound by HBM bandwidth: at most 8 frames of an FP64 plan and 2 of

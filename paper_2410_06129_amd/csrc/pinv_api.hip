@@ -1348,31 +1348,33 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
   const TS* d = (const TS*)data;
   TS* x = (TS*)image;
   void *b = nullptr, *rd = nullptr, *r = nullptr, *t = nullptr;
-  hipError_t e = sc.get(&r, 2 * sizeof(TS) * (size_t)F * N, s);
-  if (e == hipSuccess) e = sc.get(&t, 2 * sizeof(TS) * (size_t)F * N, s);
-  if (e == hipSuccess) {
-    if (p->gram_exact) {
-      e = sc.get(&b, 16 * (size_t)F * N, s);
-      bool formed = false;
-      if constexpr (sizeof(TS) == 4) {
-        const bool grid = grid_adjoint(p->e64, F);
-        if (e == hipSuccess && (grid || stored_adjoint(p->e64, F))) {
-          e = grid ? launch_grid_adjoint(p->e64, d, F, (double*)b, sc, s)
-                   : launch_stored_adjoint(p->e64, d, F, (double*)b, sc, s);
-          formed = e == hipSuccess;
-          if (e == hipErrorOutOfMemory) {   // the direct sum needs less scratch, or none
-            (void)hipGetLastError();
-            e = hipSuccess;
-          }
+  hipError_t e;
+  // (b before r and t: the forms of E^H d that take more scratch than the direct sum then
+  // find half of a fixed region free whenever the whole call fits it, so they run there
+  // as they do elsewhere)
+  if (p->gram_exact) {
+    e = sc.get(&b, 16 * (size_t)F * N, s);
+    bool formed = false;
+    if constexpr (sizeof(TS) == 4) {
+      const bool grid = grid_adjoint(p->e64, F);
+      if (e == hipSuccess && (grid || stored_adjoint(p->e64, F))) {
+        e = grid ? launch_grid_adjoint(p->e64, d, F, (double*)b, sc, s)
+                 : launch_stored_adjoint(p->e64, d, F, (double*)b, sc, s);
+        formed = e == hipSuccess;
+        if (e == hipErrorOutOfMemory) {   // the direct sum needs less scratch, or none
+          (void)hipGetLastError();
+          e = hipSuccess;
         }
       }
-      if (e == hipSuccess && !formed)
-        e = launch_adjoint<double, TS, TS, double>(p->e64, d, F, (const TS*)nullptr, 0.0, (double*)b,
-                                                   sc, s);
-    } else {
-      e = sc.get(&rd, 16 * (size_t)F * M, s);
     }
+    if (e == hipSuccess && !formed)
+      e = launch_adjoint<double, TS, TS, double>(p->e64, d, F, (const TS*)nullptr, 0.0, (double*)b,
+                                                 sc, s);
+  } else {
+    e = sc.get(&rd, 16 * (size_t)F * M, s);
   }
+  if (e == hipSuccess) e = sc.get(&r, 2 * sizeof(TS) * (size_t)F * N, s);
+  if (e == hipSuccess) e = sc.get(&t, 2 * sizeof(TS) * (size_t)F * N, s);
   for (int it = 0; it < steps && e == hipSuccess; ++it) {
     if (p->gram_exact) {
       e = launch_resid<TS, TS>((const double*)p->gram, (const double*)b, x, F, p->N, p->lam, (TS*)r, sc, s);
@@ -1385,7 +1387,7 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
     if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, (const TS*)r, F, p->N, (TS*)t, sc, s);
     if (e == hipSuccess) e = launch_tri_frames<TS, 1, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, sc, s);
   }
-  for (void* q : {rd, b, t, r})   // most recent first (the fixed-region scratch is a stack)
+  for (void* q : {t, r, rd, b})   // most recent first (the fixed-region scratch is a stack)
     if (q) (void)sc.put(q, s);
   HIPCHK(e);
   return PINV_OK;

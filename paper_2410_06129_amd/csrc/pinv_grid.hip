@@ -418,8 +418,11 @@ __global__ __launch_bounds__(256) void k_grid_combine(EncDev<double> e, const cx
 bool grid_adjoint(const EncDev<double>& e, int F) {
   if (e.b0 || e.nx < kGridMin || e.ny < kGridMin || F <= 0) return false;
   const double rows = (double)F * e.C * e.S, img = (double)e.nx * e.ny;
-  // a frame's grids fit a pass (and its rows a launch's y dimension)
-  if (grid_plan(e, 1, SIZE_MAX).frames == 0) return false;
+  // tables and a pass over a frame's grids at least fit 256 MB, what a call that fits the
+  // fixed region of applies without allocation leaves (and a frame's rows a launch's y
+  // dimension)
+  const GridPlan one = grid_plan(e, 1, SIZE_MAX);
+  if (one.frames == 0 || one.tables > kGridBytes / 4 - 1024 || one.work > kGridBytes / 4) return false;
   const double direct = 3.0 * rows * e.K * e.V;
   const double grid = rows * (2.0 * 529.0 * e.K + 3.0 * img * (4.0 * e.nx + 2.0 * e.ny));
   return direct >= 1.75 * grid && direct >= 1e7;

@@ -1,6 +1,6 @@
 // The apply without allocation: pinv_apply with its scratch (split-contraction
 // partials, refinement vectors, factor-only intermediates) taken from a fixed
-// device array instead of the stream-ordered pool, for callers that cannot
+// device array instead of the context's memory cache, for callers that cannot
 // allocate device memory.
 #include <hip/hip_runtime.h>
 

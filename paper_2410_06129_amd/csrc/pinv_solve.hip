@@ -423,21 +423,18 @@ static StoredPlan stored_plan(const EncDev<double>& e, int F, size_t room) {
   const int64_t rows = (int64_t)F * e.C;
   StoredPlan p{};
   const int nchunks = cdiv(e.K, Cfg::BK);
-  auto columns = [&](int splits) {
-    const int64_t n = (int64_t)(std::min(kStoredBytes, room) / (16 * ((size_t)e.K + splits * rows)));
+  auto columns = [&](int splits, size_t bytes) {
+    const int64_t n = (int64_t)(bytes / (16 * ((size_t)e.K + splits * rows)));
     return (int)std::min<int64_t>(e.N, n >= e.N ? n : n / Cfg::BN * Cfg::BN);
   };
-  const int n1 = columns(1);
+  // (the split, which the sums' order follows from, does not depend on the room)
+  const int n1 = columns(1, kStoredBytes);
   if (n1 <= 0) return p;
   p.splits = pick_split((long)cdiv(rows, Cfg::BM) * cdiv(n1, Cfg::BN),
                         resident_blocks(k_adjoint_rows<Cfg>, 256, smem_bytes<Cfg>()), nchunks);
+  if (columns(p.splits, kStoredBytes / 4) <= 0) p.splits = 1;
   p.kchunk = cdiv(nchunks, p.splits) * Cfg::BK;
-  p.n = columns(p.splits);
-  if (p.n <= 0) {
-    p.splits = 1;
-    p.kchunk = nchunks * Cfg::BK;
-    p.n = n1;
-  }
+  p.n = columns(p.splits, std::min(kStoredBytes, room));
   p.bytes = 16 * (size_t)p.n * ((size_t)e.K + p.splits * rows);
   return p;
 }
@@ -448,15 +445,14 @@ static StoredPlan stored_plan(const EncDev<double>& e, int F, size_t room) {
 // 16 x 16 without a map, 8 coils, 500 frames 785 / 425, 8 x 8, 4 coils, 5 frames 83 / 83.
 // With one coil, at most 64 frames and no map nothing is formed twice (212 / 217).
 bool stored_adjoint(const EncDev<double>& e, int F) {
-  return F > 0 && (e.C > 1 || e.b0 || F > F64Cfg3::BM) && stored_plan(e, F, SIZE_MAX).n > 0;
+  return F > 0 && (e.C > 1 || e.b0 || F > F64Cfg3::BM) && stored_plan(e, F, kStoredBytes / 4).n > 0;
 }
 
 hipError_t launch_stored_adjoint(const EncDev<double>& e, const float* D, int F, double* b, Scratch& sc,
                                  hipStream_t s) {
   typedef F64Cfg3 Cfg;
   const StoredPlan p = stored_plan(e, F, sc.room());
-  // (slabs of few columns would read the data over and over)
-  if (p.n == 0 || (p.n < e.N && p.bytes < kStoredBytes / 4)) return hipErrorOutOfMemory;
+  if (p.n == 0) return hipErrorOutOfMemory;
   void* work = nullptr;
   hipError_t err = sc.get(&work, p.bytes, s);
   if (err != hipSuccess) return err;
