@@ -41,9 +41,12 @@ if ROOT not in sys.path:
 import numpy as np  # noqa: E402
 
 METRIC = "R-build TFLOP/s + apply frames/s vs plain FP64 GPU at stated error; p50/p99"
-PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense FP32 matrix
 PEAK_FP64_MFMA = 78.6
 PEAK_BF16_MFMA = 2500.0  # TFLOP/s, MI355X dense BF16 matrix (no sparsity)
+PEAK_F16_MFMA = 2500.0   # TFLOP/s, MI355X dense FP16 matrix (no sparsity)
+# FP32 products on f16 pieces: executed f16 flops per complex-equivalent flop (16 or 12
+# real products of pieces per complex product against the 4 counted)
+F16_TRMM, F16_APPLY = 4.0, 3.0
 PEAK_HBM = 8.0e12        # B/s
 ROW_APPLY_MAX_F = 2      # FP32 and BF16X3 plans stream R row by row (VALU) for at most this many frames,
 STREAM_MAX_F = 32        # and into the matrix cores up to this many
@@ -102,7 +105,11 @@ def refine_flops(enc, F: int, steps: int) -> float:
     if steps <= 0:
         return 0.0
     N, M = enc.N, enc.M
-    return 8.0 * M * N * F + steps * 16.0 * N * N * F
+    adjoint = 8.0 * M * N * F
+    if enc.b0_hz is None:   # E^H d by gridding: 529 cells by real weights, two transforms
+        rows, img = F * enc.C * enc.S, enc.nx * enc.ny
+        adjoint = min(adjoint, rows * (4.0 * 529 * enc.K + 8.0 * img * (4 * enc.nx + 2 * enc.ny)))
+    return adjoint + steps * 16.0 * N * N * F
 
 
 # ----------------------------------------------------------------------------
@@ -181,11 +188,11 @@ def measured_traffic(kernel: str, workload: str):
             "source": "profiles/pmc_traffic.json"}
 
 
-# the FP32 plan's kernels (3M, 128x64 tiles) and the BF16X3 plan's split
+# the FP32 plan's kernels (f16 pieces) and the BF16X3 plan's split
 # kernels, by their template signature
-PMC_KERNELS = {"trmm_w": "k_trmm_w<pinv::TileCfg<float, 128, 64, 8, true, 2>,",
-               "trmm_r": "k_trmm_r<pinv::TileCfg<float, 128, 64, 8, true, 2>, float>",
-               "apply": "k_apply<pinv::TileCfg<float, 128, 64, 8, true, 2>, false>",
+PMC_KERNELS = {"trmm_w": "k_trmm_wh(",
+               "trmm_r": "k_trmm_rh(",
+               "apply": "k_apply_half<pinv::HalfCfg<128, 128,",
                "trmm_w_bf16x3": "k_trmm_w_sp(",
                "trmm_r_bf16x3": "k_trmm_r_sp(",
                "apply_bf16x3": "k_apply<pinv::TileCfgB3<128, 64, 2, 2, 1>, false>",
@@ -229,7 +236,7 @@ def pmc_mfma_summary(d) -> dict:
     disp = defaultdict(set)
     names = dict(PMC_KERNELS, gram_psf="k_psf(", chol_trailing="k_chol_trailing", chol_panel="k_chol_panel",
                  gen_e_bf16x3="k_gen_e_sp<", gram_shared="k_gram_shared<", gram_full="k_gram<",
-                 chol_diag="k_chol_diag", adjoint_fp64="k_adjoint<", resid="k_resid", tri_frames="k_tri_frames",
+                 chol_diag="k_chol_diag", adjoint_fp64="k_grid_spread<", resid="k_resid", tri_frames="k_tri_frames",
                  trmm_w_fp64_formed="k_trmm_w<pinv::TileCfg<double",
                  trmm_r_fp64_formed="k_trmm_r<pinv::TileCfg<double, 64, 64, 8, false, 2>, float>",
                  apply_seg="k_apply<pinv::TileCfg<float, 128, 64, 8, false, 2>, true>")
@@ -813,14 +820,16 @@ def build_only(args) -> dict:
         st = np.median(np.array(times), axis=0)
         total = float(st.sum())
         exec_total = sum(ex.values())
-        peak = PEAK_FP64_MFMA if prec == P.FP64 or flags else PEAK_FP32_MFMA
+        peak = PEAK_FP64_MFMA
+        # a BF16X3 build's products run on the BF16 pipe (see bf16_mfma), an FP32 build's on
+        # the F16 pipe: their counted rate has no single peak
         b3 = prec == P.BF16X3
+        mixed = not (prec == P.FP64 or flags)
         out["builds"][name] = {
             "stage_ms": stage_dict(st), "build_ms": total,
             "tflops_executed": exec_total / (total * 1e-3) / 1e12,
-            # a BF16X3 build's products run on the BF16 pipe: see bf16_mfma
-            "frac_of_peak_executed": None if b3 else exec_total / (total * 1e-3) / 1e12 / peak,
-            "peak": None if b3 else peak,
+            "frac_of_peak_executed": None if mixed else exec_total / (total * 1e-3) / 1e12 / peak,
+            "peak": None if mixed else peak,
             "bf16_mfma": bf16x3_mfma(ex, stage_dict(st)) if b3 else None,
             "tflops_standard_count_effective": build_flops_standard(enc) / (total * 1e-3) / 1e12,
             "stage_tflops_executed": {k: ex[k] / (st[i] * 1e-3) / 1e12 if st[i] > 0 else None
@@ -1061,10 +1070,11 @@ def headline(args) -> dict:
     torch.cuda.empty_cache()
 
     # --- roofline of the dominant kernel of the step (HIP-event stage times on
-    # the build stream; each of W and R is one kernel launch) ---
-    kern = {"trmm_w": (float(st_mean[2]), ex["trmm_w"], PEAK_FP32_MFMA),
-            "trmm_r": (float(st_mean[3]), ex["trmm_r"], PEAK_FP32_MFMA),
-            "apply": (a0, 8.0 * N * M * F, PEAK_FP32_MFMA)}
+    # the build stream; W with the packing of its operands) ---
+    # (rates in executed f16 flops of the pieces' products)
+    kern = {"trmm_w": (float(st_mean[2]), F16_TRMM * ex["trmm_w"], PEAK_F16_MFMA),
+            "trmm_r": (float(st_mean[3]), F16_TRMM * ex["trmm_r"], PEAK_F16_MFMA),
+            "apply": (a0, F16_APPLY * 8.0 * N * M * F, PEAK_F16_MFMA)}
     name = max(kern, key=lambda k: kern[k][0])
     kms, kfl, kpeak = kern[name]
     achieved = kfl / (kms * 1e-3) / 1e12
@@ -1072,7 +1082,7 @@ def headline(args) -> dict:
     roof = {"kernel": name, "bound": "mfma", "achieved": achieved, "peak": kpeak, "unit": "TFLOP/s",
             "frac": achieved / kpeak, "traffic": tr["bytes_per_launch"] if tr else None,
             "traffic_detail": tr,
-            "mfma_pipe_frac": achieved * 0.75 / kpeak,   # 3M: 6 of the 8 counted real flops run
+            "mfma_pipe_frac": achieved / kpeak, "pipe": "f16, products of two and three pieces",
             "per_kernel": {k: {"ms": v[0], "tflops": v[1] / (v[0] * 1e-3) / 1e12, "peak": v[2],
                                "frac": v[1] / (v[0] * 1e-3) / 1e12 / v[2]} for k, v in kern.items()}}
 
@@ -1081,13 +1091,15 @@ def headline(args) -> dict:
         "warmup": args.warmup, "ms_per_step": ms_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": w.name, "N": N, "M": M, "F": F, "coils": enc.C,
-                   "precision": "fp32 mfma products, fp64 gram and factorisation",
+                   "precision": "fp32 products on f16 pieces, fp64 gram and factorisation",
                    "refine_steps": refine, "lambda_rel": w.rel_lambda},
         "value_basis": "executed complex-equivalent flops per step / step time",
         "step_tflops_standard_count_effective": step_std / (ms_step * 1e-3) / 1e12,
         "build": {"ms": build_ms, "stage_ms": stage_dict(st_mean),
                   "tflops_executed": build_exec / (build_ms * 1e-3) / 1e12,
-                  "frac_fp32_peak_executed": build_exec / (build_ms * 1e-3) / 1e12 / PEAK_FP32_MFMA,
+                  # (the products' executed f16 flops against the F16 pipe, over the whole build)
+                  "frac_f16_peak_executed": F16_TRMM * (ex["trmm_w"] + ex["trmm_r"]) / (build_ms * 1e-3)
+                                            / 1e12 / PEAK_F16_MFMA,
                   "tflops_standard_count_effective":
                       build_flops_standard(enc) / (build_ms * 1e-3) / 1e12,
                   "executed_flops": ex},
