@@ -527,7 +527,8 @@ void drain_frees(pinv_context* c, bool wait) {
 // Factorisation block size when the options leave it at 0.
 constexpr int kDefaultNb = 128;
 
-// Whether an FP32 plan forms W and R on f16 pieces: from 3e8 complex products
+// Whether an FP32 plan forms W and R on f16 pieces: from 256 unknowns (fewer leave
+// most of a 128-row tile empty; none were measured) and 3e8 complex products
 // (N^2 M), or 1.5e9 where N is not a multiple of 32 (W^T's rows are padded, conj(E)
 // then takes a second slab).  Below, the packing and a grid of few 128 x 128 tiles
 // cost more (W + R in us on f16 pieces and on FP32 tiles: N = 256, M = 2056, 1.3e8:
@@ -536,7 +537,7 @@ constexpr int kDefaultNb = 128;
 // 5042, 9713).  Not with an FP32 Gram over all rows: its error may exceed the
 // shift, and W's entries then need not stay below 1.
 bool half_products(int64_t N, int64_t M, int gram) {
-  return (double)N * N * M >= (N % 32 == 0 ? 3e8 : 1.5e9) && gram != PINV_GRAM_FULL;
+  return N >= 256 && (double)N * N * M >= (N % 32 == 0 ? 3e8 : 1.5e9) && gram != PINV_GRAM_FULL;
 }
 
 struct BuildForm {
@@ -561,10 +562,16 @@ uint64_t form_key(const pinv_encoding* e, const Dims& d, double lam, int prec, c
 // per sweep until it is below their gaps: 29 sweeps at N = 1024, 35 at 2304.
 constexpr int kMaxJacobiSweeps = 60;
 
-// Device bytes a build needs at its peak: plan buffers plus build workspaces.
 // FP64 plans of at least this many unknowns store E^H before the W product.
 constexpr size_t kStoredColumns = 640;
 
+// The Gram and factor workspace of order Gd, whose place the packed factor of a plan on
+// f16 pieces takes once L^-1 is formed.
+size_t gram_work_bytes(size_t Gd, const BuildForm& f) {
+  return std::max(16 * Gd * Gd, f.half ? half_factor_bytes((int64_t)Gd) : size_t(0));
+}
+
+// Device bytes a build needs at its peak: plan buffers plus build workspaces.
 size_t plan_footprint(const Dims& d, int prec, const BuildForm& f) {
   const size_t N = d.N, M = d.M;
   const bool right = d.M < d.N;
@@ -572,7 +579,7 @@ size_t plan_footprint(const Dims& d, int prec, const BuildForm& f) {
   const size_t cs = prec == PINV_FP64 ? 16 : 8;
   const size_t ws = f.r_fp64 ? 16 : cs;   // W (and Z) element size
   size_t b = 0;
-  b += 16 * Gd * Gd;            // Gram / factor workspace (FP64)
+  b += gram_work_bytes(Gd, f);  // Gram / factor workspace (FP64)
   b += 16 * Gd * Gd;            // L^-1 in FP64 during the factorisation
   b += cs * Gd * Gd;            // L^-1 kept
   if (!f.no_r && prec == PINV_BF16X3) {
@@ -1095,7 +1102,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   BCHK(plan_malloc(&p->gram, 16 * Gd * Gd, c, s));
   if (form.route == PINV_ROUTE_EIGEN) BCHK(plan_malloc(&p->spec, 8 * Gd, c, s));
   p->gram_exact = !(form.gram == PINV_GRAM_FULL && !f64);
-  BCHK(workspace_alloc(&G, 16 * Gd * Gd, c, s));
+  BCHK(workspace_alloc(&G, gram_work_bytes(Gd, form), c, s));
   if (f64) {
     L64 = p->Linv;
   } else {
@@ -1255,8 +1262,8 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     BCHK(c->mem.put(LS, s));
     LS = nullptr;
   } else if (form.half) {
-    // the packed factor in the Gram workspace (dead once factored; 12 N Np + 8 N
-    // bytes of its 16 N^2), conj(E) in R until R is formed
+    // the packed factor in the Gram workspace (dead once factored), conj(E) in R until
+    // R is formed
     const int64_t Np = half_cols(N), fit = (int64_t)(N * M) / Np;
     const int64_t slab = fit >= (int64_t)M ? (int64_t)M : fit / 128 * 128;
     BCHK(launch_trmm_wh(p->e32, (const double*)L64, G, p->R, slab, e_shift(e, d), W, s));

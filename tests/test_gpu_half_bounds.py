@@ -1,0 +1,56 @@
+"""Where FP32 plans leave f16 pieces for FP32 instructions: R on both sides of each bound
+against the oracle, beside the same plan on FP32 instructions (4M), whose error R may
+double at most (a value is held within 2^-24 rms in two pieces, 2^-25 in FP32)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2410_06129_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    from paper_2410_06129_amd import pinv
+    return pinv
+
+
+@pytest.fixture(scope="module")
+def ctx(P):
+    c = P.pinv_context_create(0)
+    yield c
+    P.pinv_context_destroy(c)
+
+
+def get_r(P, ctx, enc, lam=1e-2, **kw):
+    plan = P.pinv_build(ctx, enc, lam, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED, **kw)
+    P.pinv_plan_wait(plan)
+    R = torch.full((enc.N, enc.M), float("nan"), dtype=torch.complex64, device="cuda")
+    P.pinv_plan_copy_buffer(plan, P.BUF_R, R)
+    torch.cuda.synchronize()
+    P.pinv_plan_release(plan)
+    return R.cpu().numpy().astype(np.complex128)
+
+
+def rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+def on_pieces(P, enc, lam=1e-2):
+    """Plans of an N that is no multiple of 32 pad W's rows on f16 pieces."""
+    assert enc.N % 32
+    return (P.pinv_encoding_key(enc, lam, prec=P.FP32)[1]
+            != P.pinv_encoding_key(enc, lam, prec=P.FP32, cprod=P.CPROD_4M)[1])
+
+
+@pytest.mark.parametrize("nx,ny", [(17, 15), (20, 13)])   # 255 and 260 unknowns
+def test_fewest_unknowns(P, ctx, nx, ny):
+    enc = synth.small_case(seed=321, nx=nx, ny=ny, C=8, K=2900, F=1).enc
+    assert enc.N ** 2 * enc.M >= 1.5e9 and on_pieces(P, enc) == (enc.N >= 256)
+    ref = oracle.Build(enc, rel=1e-2).recon_matrix()
+    e_auto, e_4m = rel(get_r(P, ctx, enc), ref), rel(get_r(P, ctx, enc, cprod=P.CPROD_4M), ref)
+    print(f"N={enc.N}: {e_auto:.2e}, FP32 {e_4m:.2e}")
+    assert e_auto <= 2.0 * e_4m
