@@ -447,11 +447,15 @@ EncDev<T> enc_at(const Dims& d, const TableLayout& l, void* dev, const int* vxy,
 }
 
 // The power of two that brings E's largest entry into [2^13, 2^14.5): every
-// phase factor has modulus 1, so |E| is the coil sensitivity.
+// phase factor has modulus 1, so |E| is the coil sensitivity at the unknown voxels.
 int e_shift(const pinv_encoding* e, const Dims& d) {
   if (!d.has_coil) return 13;
   double mx = 0.0;
-  for (size_t i = 0; i < 2 * (size_t)d.C * d.Vg; ++i) mx = std::max(mx, fabs(e->coil[i]));
+  for (int c = 0; c < d.C; ++c)
+    for (int j = 0; j < d.V; ++j) {
+      const double* z = e->coil + 2 * ((size_t)c * d.Vg + (d.masked ? (size_t)e->voxels[j] : (size_t)j));
+      mx = std::max(mx, std::max(fabs(z[0]), fabs(z[1])));
+    }
   if (!(mx > 0.0) || !isfinite(mx)) return 0;
   return std::max(-100, std::min(100, 13 - ilogb(mx)));
 }

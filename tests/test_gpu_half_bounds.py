@@ -1,6 +1,8 @@
 """Where FP32 plans leave f16 pieces for FP32 instructions: R on both sides of each bound
 against the oracle, beside the same plan on FP32 instructions (4M), whose error R may
 double at most (a value is held within 2^-24 rms in two pieces, 2^-25 in FP32)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -54,3 +56,21 @@ def test_fewest_unknowns(P, ctx, nx, ny):
     e_auto, e_4m = rel(get_r(P, ctx, enc), ref), rel(get_r(P, ctx, enc, cprod=P.CPROD_4M), ref)
     print(f"N={enc.N}: {e_auto:.2e}, FP32 {e_4m:.2e}")
     assert e_auto <= 2.0 * e_4m
+
+
+def test_maps_outside_the_mask_have_no_effect(P, ctx):
+    """Sensitivities of voxels that are no unknowns (an unregularised ratio of coil images
+    in the background) leave R as it is."""
+    base = synth.small_case(seed=322, nx=20, ny=19, C=14, K=1451, F=1).enc
+    vox = synth.circular_mask(20, 19, 0.96)
+    outside = np.setdiff1d(np.arange(380), vox)
+    r = []
+    for filler in (0.0, 1e12, float("inf"), float("nan")):
+        coil = base.coil.copy()
+        coil[:, outside] = filler
+        enc = dataclasses.replace(base, coil=coil, voxels=vox)
+        assert on_pieces(P, enc)
+        r.append(get_r(P, ctx, enc))
+    assert np.all(np.isfinite(r[0])) and np.linalg.norm(r[0]) > 0
+    for other in r[1:]:
+        assert np.array_equal(r[0], other)
