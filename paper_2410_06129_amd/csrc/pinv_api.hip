@@ -1270,7 +1270,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     // R is formed
     const int64_t Np = half_cols(N), fit = (int64_t)(N * M) / Np;
     const int64_t slab = fit >= (int64_t)M ? (int64_t)M : fit / 128 * 128;
-    BCHK(launch_trmm_wh(p->e32, (const double*)L64, G, p->R, slab, e_shift(e, d), W, s));
+    BCHK(launch_trmm_wh(p->e64, (const double*)L64, G, p->R, slab, e_shift(e, d), W, s));
     BCHK(hipEventRecord(p->ev[3], s));
     BCHK(launch_trmm_rh((const double*)L64, G, W, (float*)p->R, d.N, d.M, s));
   } else {

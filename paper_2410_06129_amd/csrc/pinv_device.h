@@ -966,10 +966,10 @@ template <class Cfg, int OUTER> struct LoadSP {
 // column n of E, element (o, k) = E[o, k] (or its conjugate).  Each thread
 // generates KPT consecutive columns of one row and splits them into packed
 // hi/lo words as it goes (finish), so store_b3 only moves 16-byte pieces.
-// ALIGNED as for LoadGenRow.
-template <class Cfg, int OUTER, bool CONJ, int FEAT, bool ALIGNED = false>
+// ALIGNED as for LoadGenRow.  (finish and store_b3: elements in FP32.)
+template <class Cfg, int OUTER, bool CONJ, int FEAT, bool ALIGNED = false, class ET = float>
 struct LoadGenRowSP {
-  typedef float T;
+  typedef ET T;
   static constexpr int TPR = Cfg::NT / OUTER;        // threads per row
   static constexpr int KPT = Cfg::BK / TPR;          // consecutive columns per thread
   static constexpr int GPT = KPT / 8;                // 8-groups per thread

@@ -54,6 +54,13 @@ __device__ __forceinline__ void split_h2(float x0, float x1, uint32_t& h, uint32
   l = __builtin_bit_cast(uint32_t, lv);
 }
 
+__device__ __forceinline__ void split_h2(double x0, double x1, uint32_t& h, uint32_t& l) {
+  const f16x2 hv{(_Float16)(float)x0, (_Float16)(float)x1};
+  const f16x2 lv{(_Float16)(float)(x0 - (double)hv[0]), (_Float16)(float)(x1 - (double)hv[1])};
+  h = __builtin_bit_cast(uint32_t, hv);
+  l = __builtin_bit_cast(uint32_t, lv);
+}
+
 // The power of two that brings a row whose largest |value| has the FP32 (FP64
 // high word's) exponent field `e` into [2^13, 2^14).  Rows of zeros keep 1;
 // rows that hold an infinity or a NaN stay non-finite at any scale.
@@ -349,16 +356,17 @@ __global__ __launch_bounds__(256) void k_factor_pack(const double* __restrict__ 
 // conj(E), packed: rows m0 .. m0 + rows of samples, columns n, scaled by 2^es
 // ---------------------------------------------------------------------------
 // Workgroup b takes 64 rows and kGenChunksH chunks; thread t generates columns
-// 8 (t / 64) .. + 8 of row t % 64 of each chunk.
+// 8 (t / 64) .. + 8 of row t % 64 of each chunk, in FP64, so that the split is E's only
+// rounding.
 constexpr int kGenChunksH = 16;
 struct GenHCfg { static constexpr int NT = 256, BK = 32; };
 
 template <int FEAT, bool AL>
-__global__ __launch_bounds__(256) void k_gen_e_h(EncDev<float> e, int m0, int rows, int nc, float scale,
+__global__ __launch_bounds__(256) void k_gen_e_h(EncDev<double> e, int m0, int rows, int nc, double scale,
                                                  char* __restrict__ Es) {
   const int nbc = (nc + kGenChunksH - 1) / kGenChunksH;
   const int r0 = (int)(blockIdx.x / nbc) * 64, cb = (int)(blockIdx.x % nbc);
-  LoadGenRowSP<GenHCfg, 64, true, FEAT, AL> g;
+  LoadGenRowSP<GenHCfg, 64, true, FEAT, AL, double> g;
   g.init(e, m0 + r0);
   const int o = threadIdx.x % 64, gq = (int)(threadIdx.x / 64);
   const bool live = r0 + o < rows;
@@ -369,12 +377,12 @@ __global__ __launch_bounds__(256) void k_gen_e_h(EncDev<float> e, int m0, int ro
     uint32_t pk[4][4];
 #pragma unroll
     for (int j = 0; j < 8; j += 2) {
-      float re[2], im[2];
+      double re[2], im[2];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const cx<float> el = gen_product<FEAT>(g.raw[j + u]);
-        re[u] = g.ok[j + u] ? el.re * scale : 0.f;
-        im[u] = g.ok[j + u] ? -el.im * scale : 0.f;
+        const cx<double> el = gen_product<FEAT>(g.raw[j + u]);
+        re[u] = g.ok[j + u] ? el.re * scale : 0.0;
+        im[u] = g.ok[j + u] ? -el.im * scale : 0.0;
       }
       split_h2(re[0], re[1], pk[0][j / 2], pk[1][j / 2]);
       split_h2(im[0], im[1], pk[2][j / 2], pk[3][j / 2]);
@@ -751,7 +759,7 @@ static hipError_t pack_factor(const double* Li, int N, bool trans, const int* e,
   return hipGetLastError();
 }
 
-hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor, void* Es,
+hipError_t launch_trmm_wh(const EncDev<double>& e, const double* Li, void* factor, void* Es,
                           int64_t slab_rows, int es, void* Wt, hipStream_t s) {
   const int N = e.N, M = e.M;
   if (N <= 0 || M <= 0) return hipSuccess;
@@ -768,7 +776,7 @@ hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor
   if ((err = hipGetLastError()) != hipSuccess) return err;
   if ((err = pack_factor(Li, N, false, row_e, main, third, s)) != hipSuccess) return err;
   const int nbc = cdiv(nc, kGenChunksH);
-  const float scale = ldexpf(1.f, es);
+  const double scale = ldexp(1.0, es);
   for (int64_t m0 = 0; m0 < M; m0 += slab_rows) {
     const int rows = (int)std::min<int64_t>(slab_rows, M - m0);
     err = with_feat_al(enc_features(e), row_aligned(e, 32), [&](auto fc, auto al) {

@@ -285,7 +285,7 @@ size_t half_factor_bytes(int64_t N);
 // slab_rows samples at a time (8 slab_rows half_cols(N) bytes), scaled by 2^es
 // so that no entry reaches 2^14.  Then R (complex64) from W^T and the same L^-1;
 // `factor` carries the column scales from one call to the other.
-hipError_t launch_trmm_wh(const EncDev<float>& e, const double* Li, void* factor, void* Es,
+hipError_t launch_trmm_wh(const EncDev<double>& e, const double* Li, void* factor, void* Es,
                           int64_t slab_rows, int es, void* Wt, hipStream_t s);
 hipError_t launch_trmm_rh(const double* Li, void* factor, const void* Wt, float* R, int N, int M,
                           hipStream_t s);

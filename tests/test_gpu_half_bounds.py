@@ -74,3 +74,15 @@ def test_maps_outside_the_mask_have_no_effect(P, ctx):
     assert np.all(np.isfinite(r[0])) and np.linalg.norm(r[0]) > 0
     for other in r[1:]:
         assert np.array_equal(r[0], other)
+
+
+@pytest.mark.parametrize("lam", [1e-5, 1e-3])
+def test_no_further_than_fp32(P, ctx, lam):
+    """Short contractions round little, so E's own rounding is most of the error: one, into
+    two pieces (2^-24), against those of FP32 tables and their products."""
+    enc = synth.small_case(seed=324, nx=16, ny=16, C=8, K=1000, F=1).enc
+    ref = oracle.Build(enc, rel=lam).recon_matrix()
+    e_auto = rel(get_r(P, ctx, enc, lam), ref)
+    e_4m = rel(get_r(P, ctx, enc, lam, cprod=P.CPROD_4M), ref)
+    print(f"{e_auto:.2e}, FP32 {e_4m:.2e}")
+    assert e_auto <= e_4m
