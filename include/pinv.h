@@ -116,8 +116,11 @@ typedef struct {
 /* Complex-product form of the triangular products W, R and the apply (MFMA).
  * FP32 plans on AUTO or 3M with M >= N run all but small products W and R, and
  * those with any R their applies of more than 32 frames, on f16 pieces of the FP32
- * operands instead (FP32 accumulation, at least the accuracy of the FP32
- * instructions, 2.3 times faster); 4M keeps every product of an FP32 R on FP32
+ * operands instead (FP32 accumulation, 2.3 times faster).  W and R do so where the
+ * pieces leave R at least as accurate as the FP32 instructions: sensitivities within
+ * 2^12 of the largest over the unknown voxels (the largest coil's at each) and over
+ * the coils, and a shift up to ten times the Gram's mean diagonal (the bound in full
+ * stands at half_range in pinv_api.hip); elsewhere, and on 4M, they run on FP32
  * instructions. */
 typedef enum {
   PINV_CPROD_AUTO = 0,   /* 3M for FP32 plans, 4M for FP64 plans and FP64-formed R */

@@ -446,20 +446,6 @@ EncDev<T> enc_at(const Dims& d, const TableLayout& l, void* dev, const int* vxy,
   return ev;
 }
 
-// The power of two that brings E's largest entry into [2^13, 2^14.5): every
-// phase factor has modulus 1, so |E| is the coil sensitivity at the unknown voxels.
-int e_shift(const pinv_encoding* e, const Dims& d) {
-  if (!d.has_coil) return 13;
-  double mx = 0.0;
-  for (int c = 0; c < d.C; ++c)
-    for (int j = 0; j < d.V; ++j) {
-      const double* z = e->coil + 2 * ((size_t)c * d.Vg + (d.masked ? (size_t)e->voxels[j] : (size_t)j));
-      mx = std::max(mx, std::max(fabs(z[0]), fabs(z[1])));
-    }
-  if (!(mx > 0.0) || !isfinite(mx)) return 0;
-  return std::max(-100, std::min(100, 13 - ilogb(mx)));
-}
-
 // Record that work just enqueued on `s` reads the plan.  Events whose work
 // has finished are re-recorded; one still pending is never overwritten, so a
 // stream handle that was destroyed and handed out again cannot hide work.
@@ -544,9 +530,55 @@ bool half_products(int64_t N, int64_t M, int gram) {
   return N >= 256 && (double)N * N * M >= (N % 32 == 0 ? 3e8 : 1.5e9) && gram != PINV_GRAM_FULL;
 }
 
+// Whether E and W keep FP32's accuracy in two f16 pieces under one power of two each, a
+// bound on their range over the unknowns: with b_v = max_c |C_c(v)|, a_c = max_v |C_c(v)|
+// and the Gram's diagonal K g_v (every phase factor has modulus 1, so |E| is the coil
+// sensitivity):
+//   - b_v and a_c above 2^-12 of the largest: a value keeps 23 bits down to 2^-15 of the
+//     largest, and less below;
+//   - b_v^2 / (K g_v + lam) and a_c^2 / (K mean g + lam) at least 2^-23: a row of W has
+//     entries of about sqrt(b_v^2 / (K g_v + lam)), and 2^12 W loses bits below 2^-14;
+//   - lam up to ten times the mean diagonal.
+// Voxels and coils of zeros are exact.  *es: the power of two that brings E's largest
+// entry into [2^13, 2^14.5).  The error of R by rows, here and on FP32 instructions
+// (N = 1024, 8 coils, K = 8192): 3.9e-6 and 5.9e-6 (lam 1e-3 of the mean diagonal),
+// 1.0e-6 and 1.9e-6 (1e-2); the worst row's against FP32's 0.8 times at sensitivities
+// over 2^10 (bound 2^-21.9) and lam 1e-3, but 64 over 2^20, 3.2 over 2^10 and lam 1
+// (2^-31.8); lam 1e4: 2.1e-7 and 1.1e-7.
+bool half_range(const pinv_encoding* e, const Dims& d, double lam, int* es) {
+  *es = 13;
+  if (!d.has_coil) return lam <= 10.0 * d.K && 1.0 >= 0x1p-23 * (d.K + lam);
+  std::vector<double> b(d.V, 0.0), g(d.V, 0.0), a(d.C, 0.0);
+  double top = 0.0, mean = 0.0;
+  for (int c = 0; c < d.C; ++c) {
+    for (int j = 0; j < d.V; ++j) {
+      const double* z = e->coil + 2 * ((size_t)c * d.Vg + (d.masked ? (size_t)e->voxels[j] : (size_t)j));
+      const double m = std::max(fabs(z[0]), fabs(z[1]));
+      if (!(m <= 0x1p100)) return false;   // NaN included
+      b[j] = std::max(b[j], m);
+      a[c] = std::max(a[c], m);
+      g[j] += z[0] * z[0] + z[1] * z[1];
+    }
+    top = std::max(top, a[c]);
+  }
+  if (!(top >= 0x1p-80)) return false;
+  for (double v : g) mean += v / d.V;
+  if (!(lam <= 10.0 * d.K * mean)) return false;
+  auto held = [&](double m, double diag) {
+    return m == 0.0 || (m >= 0x1p-12 * top && m * m >= 0x1p-23 * (d.K * diag + lam));
+  };
+  for (int j = 0; j < d.V; ++j)
+    if (!held(b[j], g[j])) return false;
+  for (double m : a)
+    if (!held(m, mean)) return false;
+  *es = 13 - ilogb(top);
+  return true;
+}
+
 struct BuildForm {
   bool m3 = true;
   bool half = false;   // W and R on f16 pieces (pinv_half.hip)
+  int es = 0;          // their power of two for E
   int nb = kDefaultNb;
   int gram = PINV_GRAM_SHARED;
   bool r_fp64 = false;
@@ -884,7 +916,8 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
                                          : o->prec != PINV_FP64 && !r_fp64;
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
   form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
-               o->route == PINV_ROUTE_CHOLESKY && half_products(d->N, d->M, gram);
+               o->route == PINV_ROUTE_CHOLESKY && half_products(d->N, d->M, gram) &&
+               half_range(e, *d, lam, &form->es);
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);
@@ -1270,7 +1303,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
     // R is formed
     const int64_t Np = half_cols(N), fit = (int64_t)(N * M) / Np;
     const int64_t slab = fit >= (int64_t)M ? (int64_t)M : fit / 128 * 128;
-    BCHK(launch_trmm_wh(p->e64, (const double*)L64, G, p->R, slab, e_shift(e, d), W, s));
+    BCHK(launch_trmm_wh(p->e64, (const double*)L64, G, p->R, slab, form.es, W, s));
     BCHK(hipEventRecord(p->ev[3], s));
     BCHK(launch_trmm_rh((const double*)L64, G, W, (float*)p->R, d.N, d.M, s));
   } else {

@@ -86,3 +86,38 @@ def test_no_further_than_fp32(P, ctx, lam):
     e_4m = rel(get_r(P, ctx, enc, lam, cprod=P.CPROD_4M), ref)
     print(f"{e_auto:.2e}, FP32 {e_4m:.2e}")
     assert e_auto <= e_4m
+
+
+def ramp(shape, axis, bits):
+    """Powers of two from 1 down to 2^-bits along an axis, in a shuffled order."""
+    n = shape[axis]
+    w = 2.0 ** -np.round(bits * np.random.default_rng(5).permutation(n) / max(n - 1, 1))
+    return w.reshape([-1 if i == axis else 1 for i in range(len(shape))])
+
+
+@pytest.mark.parametrize("axis,bits,lam,pieces", [
+    (1, 0, 1e-3, True), (1, 9, 1e-3, True), (1, 14, 1e-3, False), (1, 23, 1e-3, False), (1, 10, 1.0, False),
+    (0, 4, 1e-3, True), (0, 14, 1e-3, False), (0, 23, 1e-3, False),
+    (1, 0, 8.0, True), (1, 0, 12.0, False), (1, 0, 1e4, False),
+])
+def test_uneven_sensitivities(P, ctx, axis, bits, lam, pieces):
+    """Sensitivities that differ between voxels (axis 1) or coils (axis 0) by up to 2^bits,
+    and large shifts: no row of R, and no coil's columns, may be further from the FP64
+    plan's than twice the FP32 instructions leave the worst of them."""
+    base = synth.small_case(seed=323, nx=19, ny=17, C=8, K=1900, F=1).enc
+    enc = dataclasses.replace(base, coil=base.coil * ramp(base.coil.shape, axis, bits))
+    assert on_pieces(P, enc, lam) == pieces
+    plan = P.pinv_build(ctx, enc, lam, P.LAMBDA_REL_MEAN_DIAG, P.FP64, P.FLAG_UNCACHED)
+    ref = torch.empty((enc.N, enc.M), dtype=torch.complex128, device="cuda")
+    P.pinv_plan_copy_buffer(plan, P.BUF_R, ref)
+    torch.cuda.synchronize()
+    P.pinv_plan_release(plan)
+    ref = ref.cpu().numpy().reshape(enc.N, enc.C, enc.K)
+
+    def worst(**kw):
+        d = get_r(P, ctx, enc, lam, **kw).reshape(ref.shape) - ref
+        return [max(np.sqrt((np.abs(d) ** 2).sum(ax) / (np.abs(ref) ** 2).sum(ax)))
+                for ax in ((1, 2), (0, 2))]
+    auto, fp32 = worst(), worst(cprod=P.CPROD_4M)
+    print(f"rows {auto[0]:.1e} {fp32[0]:.1e} coils {auto[1]:.1e} {fp32[1]:.1e}")
+    assert auto[0] <= 2.0 * fp32[0] and auto[1] <= 2.0 * fp32[1]
