@@ -120,8 +120,9 @@ typedef struct {
  * pieces leave R at least as accurate as the FP32 instructions: sensitivities within
  * 2^12 of the largest over the unknown voxels (the largest coil's at each) and over
  * the coils, and a shift up to ten times the Gram's mean diagonal (the bound in full
- * stands at half_range in pinv_api.hip); elsewhere, and on 4M, they run on FP32
- * instructions. */
+ * stands at half_range in pinv_api.hip); elsewhere they run on FP32
+ * instructions.  4M keeps every product on FP32 instructions, the applies of an
+ * FP64-formed R (4M on AUTO, but on pieces) included. */
 typedef enum {
   PINV_CPROD_AUTO = 0,   /* 3M for FP32 plans, 4M for FP64 plans and FP64-formed R */
   PINV_CPROD_3M = 1,     /* three real products per complex product (Gauss):

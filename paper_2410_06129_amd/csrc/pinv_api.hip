@@ -208,6 +208,7 @@ struct pinv_plan {
   bool right = false;        // M < N: Gram, factor and L^-1 are the samples' (M x M)
   int G = 0;                 // order of the Gram and the factor: N, or M when right
   bool m3 = true;            // W, R and apply with three real products per complex product
+  bool pieces = false;       // FP32: applies of many frames may run on f16 pieces
   int gram_form = PINV_GRAM_SHARED;   // how the Gram was formed
   bool r_fp64 = false;       // FP32 plan whose W and R were formed in FP64
   int route = PINV_ROUTE_CHOLESKY;
@@ -577,6 +578,7 @@ bool half_range(const pinv_encoding* e, const Dims& d, double lam, int* es) {
 
 struct BuildForm {
   bool m3 = true;
+  bool pieces = false;   // applies of many frames may run on f16 pieces
   bool half = false;   // W and R on f16 pieces (pinv_half.hip)
   int es = 0;          // their power of two for E
   int nb = kDefaultNb;
@@ -915,12 +917,16 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
              : o->cprod == PINV_CPROD_4M ? false
                                          : o->prec != PINV_FP64 && !r_fp64;
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
+  // (an FP64-formed R has its products on 4M by default too: there 4M has to be asked for)
+  const bool ask4 = r_fp64 && o->cprod == PINV_CPROD_4M;
+  form->pieces = o->prec == PINV_FP32 && !no_r && (form->m3 || r_fp64) && !ask4;
   form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
                o->route == PINV_ROUTE_CHOLESKY && half_products(d->N, d->M, gram) &&
                half_range(e, *d, lam, &form->es);
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
-                   (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0);
+                   (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0) |
+                   (ask4 ? 1 << 10 : 0);
   form->key_bits = bits;
   if (key_out) *key_out = form_key(e, *d, lam, o->prec, *form);
   return PINV_OK;
@@ -1064,6 +1070,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   p->right = d.M < d.N;
   p->G = p->right ? d.M : d.N;
   p->m3 = form.m3;
+  p->pieces = form.pieces;
   p->gram_form = form.gram;
   p->r_fp64 = form.r_fp64;
   p->route = form.route;
@@ -1595,6 +1602,7 @@ extern "C++" pinv_status apply_items(pinv_context* c, int32_t n, const pinv_appl
         it.F = (int)items[i].F;
         it.N = p->N;
         it.M = p->M;
+        it.pieces = p->pieces;
       }
       ++i;
     }

@@ -615,13 +615,12 @@ static hipError_t run_apply(ApplyBatch b, Scratch& sc, hipStream_t s) {
   return err;
 }
 
-// Whether an FP32 apply of more than kStreamMaxF frames runs on f16 pieces: on
-// AUTO and 3M plans and on those with an FP64-formed R, from 3e8 complex
-// products.  Below, its packing launches cost more than the products save
+// Whether an FP32 apply of more than kStreamMaxF frames, of a plan that allows it, runs
+// on f16 pieces: from 3e8 complex products.  Below, its packing launches cost more than the products save
 // (N = 289, M = 416, 500 frames, 6e7: 41 us on FP32 tiles, 47 on f16 pieces;
 // N = 1024, M = 2048, 128 frames, 2.7e8: 48 and 51; 200 frames: 63 and 53).
-static bool half_apply(int F, int N, int M, bool m3, bool seg) {
-  return (m3 || seg) && (double)F * N * M >= 3e8;
+static bool half_apply(const ApplyItemDev& it) {
+  return it.pieces && (double)it.F * it.N * it.M >= 3e8;
 }
 
 template <typename T, bool M3, bool SEG>
@@ -638,7 +637,7 @@ static hipError_t apply_form(const ApplyBatch& b, Scratch& sc, hipStream_t s) {
         const hipError_t err = launch_apply_stream((const float*)it.R, (const float*)it.D,
                                                    (float*)it.X, it.N, it.M, it.F, M3, sc, s);
         if (err != hipSuccess) return err;
-      } else if (half_apply(it.F, it.N, it.M, M3, SEG)) {
+      } else if (half_apply(it)) {
         hipError_t err = launch_apply_half((const float*)it.R, (const float*)it.D, (float*)it.X, it.N,
                                            it.M, it.F, sc, s);
         if (err == hipErrorOutOfMemory) {   // the tiles need less scratch, or none

@@ -24,6 +24,7 @@ struct ApplyItemDev {
   int ntile;       // tiles of one split (set by the launcher)
   int splits;      // contraction splits over M (set by the launcher from F, N, M alone)
   int kchunk;      // rows of M per split
+  int pieces;      // FP32: may run on f16 pieces (from the plan)
   void* work;      // [splits][F][N] partial sums when splits > 1
 };
 

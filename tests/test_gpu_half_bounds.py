@@ -121,3 +121,31 @@ def test_uneven_sensitivities(P, ctx, axis, bits, lam, pieces):
     auto, fp32 = worst(), worst(cprod=P.CPROD_4M)
     print(f"rows {auto[0]:.1e} {fp32[0]:.1e} coils {auto[1]:.1e} {fp32[1]:.1e}")
     assert auto[0] <= 2.0 * fp32[0] and auto[1] <= 2.0 * fp32[1]
+
+
+def images(P, ctx, enc, d, lam, mode, **kw):
+    plan = P.pinv_build(ctx, enc, lam, mode, P.FP32, P.FLAG_UNCACHED | P.FLAG_R_FP64, **kw)
+    P.pinv_plan_wait(plan)
+    R = torch.empty((enc.N, enc.M), dtype=torch.complex64, device="cuda")
+    P.pinv_plan_copy_buffer(plan, P.BUF_R, R)
+    x = torch.full((d.shape[0], enc.N), float("nan"), dtype=torch.complex64, device="cuda")
+    P.pinv_apply(ctx, plan, d, x)
+    torch.cuda.synchronize()
+    P.pinv_plan_release(plan)
+    return x, R
+
+
+def test_4m_keeps_an_fp64_formed_r_on_fp32(P, ctx):
+    """AUTO's applies of many frames run on f16 pieces, 4M's on FP32 instructions, with the
+    same R; each has its own cache key."""
+    enc = synth.small_case(seed=325, nx=32, ny=32, C=4, K=2048, F=1).enc
+    g = torch.Generator(device="cuda").manual_seed(1)
+    d = torch.view_as_complex(torch.randn(100, enc.M, 2, device="cuda", generator=g))
+    assert 100 * enc.N * enc.M >= 3e8
+    x, R = images(P, ctx, enc, d, 1e-2, P.LAMBDA_REL_MEAN_DIAG)
+    y, S = images(P, ctx, enc, d, 1e-2, P.LAMBDA_REL_MEAN_DIAG, cprod=P.CPROD_4M)
+    assert torch.equal(R, S) and not torch.equal(x, y)
+    assert float(torch.linalg.vector_norm(x - y) / torch.linalg.vector_norm(x)) < 5e-6
+    key = [P.pinv_encoding_key(enc, 1e-2, prec=P.FP32, flags=P.FLAG_R_FP64, cprod=c)[0]
+           for c in (P.CPROD_AUTO, P.CPROD_4M)]
+    assert key[0] != key[1]
