@@ -531,12 +531,69 @@ bool half_products(int64_t N, int64_t M, int gram) {
   return N >= 256 && (double)N * N * M >= (N % 32 == 0 ? 3e8 : 1.5e9) && gram != PINV_GRAM_FULL;
 }
 
-// Whether E and W keep FP32's accuracy in two f16 pieces under one power of two each, a
-// bound on their range over the unknowns: with b_v = max_c |C_c(v)|, a_c = max_v |C_c(v)|
-// and the Gram's diagonal K g_v (every phase factor has modulus 1, so |E| is the coil
-// sensitivity):
-//   - b_v and a_c above 2^-12 of the largest: a value keeps 23 bits down to 2^-15 of the
-//     largest, and less below;
+// The coil sensitivities over the unknown voxels: |E| is the coil sensitivity, since
+// every phase factor has modulus 1.
+struct CoilRange {
+  bool finite = true;        // no infinity or NaN, and no power of two near a type's ends
+  std::vector<double> b, g;  // per voxel: the largest coil's, and the sum of squares
+  std::vector<double> a;     // per coil: the largest voxel's
+  double top = 1.0, mean = 1.0;   // the largest; g's mean
+};
+
+CoilRange coil_range(const pinv_encoding* e, const Dims& d) {
+  CoilRange r;
+  if (!d.has_coil) {
+    r.b = r.g = r.a = {1.0};
+    return r;
+  }
+  r.b.assign(d.V, 0.0);
+  r.g.assign(d.V, 0.0);
+  r.a.assign(d.C, 0.0);
+  r.top = r.mean = 0.0;
+  double* const b = r.b.data();
+  double* const g = r.g.data();
+  for (int c = 0; c < d.C; ++c) {
+    const double* z = e->coil + 2 * (size_t)c * d.Vg;
+    auto most = [&](auto voxel) {   // (no branch and short chains: 1.7 ns a value)
+      double a[4] = {0.0, 0.0, 0.0, 0.0};
+      for (int j0 = 0; j0 < d.V; j0 += 4)
+        for (int u = 0; u < 4; ++u) {
+          const int j = std::min(j0 + u, d.V - 1);
+          const double re = z[2 * voxel(j)], im = z[2 * voxel(j) + 1], ar = fabs(re), ai = fabs(im);
+          const double m = ar > ai ? ar : ai;
+          b[j] = m > b[j] ? m : b[j];
+          a[u] = m > a[u] ? m : a[u];
+          g[j] += j0 + u < d.V ? re * re + im * im : 0.0;
+        }
+      return std::max(std::max(a[0], a[1]), std::max(a[2], a[3]));
+    };
+    r.a[c] = d.masked ? most([&](int j) { return (size_t)e->voxels[j]; })
+                      : most([](int j) { return (size_t)j; });
+    r.top = std::max(r.top, r.a[c]);
+  }
+  for (double v : r.g) {
+    r.mean += v / d.V;
+    if (!(v <= 0x1p200)) r.finite = false;   // NaN included
+  }
+  r.finite = r.finite && r.top >= 0x1p-80;
+  return r;
+}
+
+// Whether R and the data keep FP32's accuracy in two f16 pieces under one power of two per
+// row and segment: sensitivities, of the largest coil at each voxel and of the coils, above
+// 2^-12 of the largest.  A value keeps 23 bits down to 2^-15 of its row's largest and less
+// below, and the samples of a weak coil lie in one segment with a strong one's; a voxel
+// that only the weak coil sees then takes its whole value from them.  Coils of one half of
+// 24 x 24 voxels each, 48 in turn, the other half's at 2^-20: that half's images are 2.2e-6
+// from R data on pieces, 1.5e-7 on FP32 instructions.
+bool pieces_range(const CoilRange& r) {
+  if (!r.finite) return false;
+  auto held = [&](double m) { return m == 0.0 || m >= 0x1p-12 * r.top; };
+  return std::all_of(r.b.begin(), r.b.end(), held) && std::all_of(r.a.begin(), r.a.end(), held);
+}
+
+// The same for E and W of a build, under one power of two each (besides pieces_range, with
+// b_v and a_c the sensitivities and K g_v the Gram's diagonal):
 //   - b_v^2 / (K g_v + lam) and a_c^2 / (K mean g + lam) at least 2^-23: a row of W has
 //     entries of about sqrt(b_v^2 / (K g_v + lam)), and 2^12 W loses bits below 2^-14;
 //   - lam up to ten times the mean diagonal.
@@ -546,33 +603,14 @@ bool half_products(int64_t N, int64_t M, int gram) {
 // 1.0e-6 and 1.9e-6 (1e-2); the worst row's against FP32's 0.8 times at sensitivities
 // over 2^10 (bound 2^-21.9) and lam 1e-3, but 64 over 2^20, 3.2 over 2^10 and lam 1
 // (2^-31.8); lam 1e4: 2.1e-7 and 1.1e-7.
-bool half_range(const pinv_encoding* e, const Dims& d, double lam, int* es) {
-  *es = 13;
-  if (!d.has_coil) return lam <= 10.0 * d.K && 1.0 >= 0x1p-23 * (d.K + lam);
-  std::vector<double> b(d.V, 0.0), g(d.V, 0.0), a(d.C, 0.0);
-  double top = 0.0, mean = 0.0;
-  for (int c = 0; c < d.C; ++c) {
-    for (int j = 0; j < d.V; ++j) {
-      const double* z = e->coil + 2 * ((size_t)c * d.Vg + (d.masked ? (size_t)e->voxels[j] : (size_t)j));
-      const double m = std::max(fabs(z[0]), fabs(z[1]));
-      if (!(m <= 0x1p100)) return false;   // NaN included
-      b[j] = std::max(b[j], m);
-      a[c] = std::max(a[c], m);
-      g[j] += z[0] * z[0] + z[1] * z[1];
-    }
-    top = std::max(top, a[c]);
-  }
-  if (!(top >= 0x1p-80)) return false;
-  for (double v : g) mean += v / d.V;
-  if (!(lam <= 10.0 * d.K * mean)) return false;
-  auto held = [&](double m, double diag) {
-    return m == 0.0 || (m >= 0x1p-12 * top && m * m >= 0x1p-23 * (d.K * diag + lam));
-  };
-  for (int j = 0; j < d.V; ++j)
-    if (!held(b[j], g[j])) return false;
-  for (double m : a)
-    if (!held(m, mean)) return false;
-  *es = 13 - ilogb(top);
+bool half_range(const CoilRange& r, const Dims& d, double lam, int* es) {
+  if (!(lam <= 10.0 * d.K * r.mean)) return false;
+  auto held = [&](double m, double diag) { return m == 0.0 || m * m >= 0x1p-23 * (d.K * diag + lam); };
+  for (size_t j = 0; j < r.b.size(); ++j)
+    if (!held(r.b[j], r.g[j])) return false;
+  for (double m : r.a)
+    if (!held(m, r.mean)) return false;
+  *es = 13 - ilogb(r.top);
   return true;
 }
 
@@ -919,10 +957,12 @@ static pinv_status check_build(const pinv_encoding* e, const pinv_build_opts* o,
   form->nb = o->nb == 0 ? kDefaultNb : o->nb;
   // (an FP64-formed R has its products on 4M by default too: there 4M has to be asked for)
   const bool ask4 = r_fp64 && o->cprod == PINV_CPROD_4M;
-  form->pieces = o->prec == PINV_FP32 && !no_r && (form->m3 || r_fp64) && !ask4;
-  form->half = o->prec == PINV_FP32 && !r_fp64 && !no_r && form->m3 && d->M >= d->N &&
-               o->route == PINV_ROUTE_CHOLESKY && half_products(d->N, d->M, gram) &&
-               half_range(e, *d, lam, &form->es);
+  if (o->prec == PINV_FP32 && !no_r && (form->m3 || r_fp64) && !ask4) {
+    const CoilRange r = coil_range(e, *d);
+    form->pieces = pieces_range(r);
+    form->half = form->pieces && !r_fp64 && d->M >= d->N && o->route == PINV_ROUTE_CHOLESKY &&
+                 half_products(d->N, d->M, gram) && half_range(r, *d, lam, &form->es);
+  }
   *lam_out = lam;
   const int bits = (form->m3 ? 1 : 0) | (gram << 1) | (r_fp64 ? 16 : 0) | (no_r ? 32 : 0) |
                    (form->route << 6) | (form->trunc << 7) | (form->nb == 128 ? 1 << 9 : 0) |

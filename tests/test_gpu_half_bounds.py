@@ -149,3 +149,32 @@ def test_4m_keeps_an_fp64_formed_r_on_fp32(P, ctx):
     key = [P.pinv_encoding_key(enc, 1e-2, prec=P.FP32, flags=P.FLAG_R_FP64, cprod=c)[0]
            for c in (P.CPROD_AUTO, P.CPROD_4M)]
     assert key[0] != key[1]
+
+
+def test_applies_of_uneven_sensitivities(P, ctx):
+    """Every second of 48 coils sees one half of the image, the others the other half and at
+    2^-20 of the first, so that a voxel's whole value comes from samples far below the
+    largest in their row: each half may be twice as far from R data as the FP32
+    instructions (4M) leave it."""
+    n, C, F = 24, 48, 300
+    rng = np.random.default_rng(6)
+    k = rng.uniform(-n / 2, n / 2, (100, 2))
+    coil = synth.unit_complex_noise((C, n * n), rng)
+    left = np.arange(n * n) % n < n // 2
+    coil[0::2, ~left] = 0
+    coil[1::2, left] = 0
+    coil[1::2] *= 2.0 ** -20
+    enc = synth.Encoding(n, n, k, t=None, coil=coil)
+    assert F * enc.N * enc.M >= 3e8
+    d = oracle.forward(enc, synth.unit_complex_noise((F, enc.N), rng))
+    d = torch.from_numpy(d.astype(np.complex64)).cuda()
+    err = {}
+    for form in (P.CPROD_AUTO, P.CPROD_4M):
+        x, R = images(P, ctx, enc, d, 2.0 ** -40, P.LAMBDA_ABS, cprod=form)
+        ref = d.to(torch.complex128) @ R.to(torch.complex128).T.contiguous()
+        e, ref = (v.reshape(F, n, n) for v in (x.to(torch.complex128) - ref, ref))
+        err[form] = [float(torch.linalg.vector_norm(e[..., s]) / torch.linalg.vector_norm(ref[..., s]))
+                     for s in (slice(0, n // 2), slice(n // 2, n))]
+    print(err)
+    for auto, fp32 in zip(err[P.CPROD_AUTO], err[P.CPROD_4M]):
+        assert auto <= 2.0 * fp32
