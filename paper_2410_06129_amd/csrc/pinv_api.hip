@@ -447,6 +447,13 @@ EncDev<T> enc_at(const Dims& d, const TableLayout& l, void* dev, const int* vxy,
   return ev;
 }
 
+// Whether `s` is being captured into a graph (the null stream cannot be).
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (s && hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
+}
+
 // Record that work just enqueued on `s` reads the plan.  Events whose work
 // has finished are re-recorded; one still pending is never overwritten, so a
 // stream handle that was destroyed and handed out again cannot hide work.
@@ -1738,6 +1745,9 @@ pinv_status pinv_apply_grouped(pinv_context* c, int32_t n, const pinv_apply_item
   if (refine_steps < 0 || refine_steps > 4) return fail(PINV_ERR_INVALID, "refine_steps in 0..4");
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(enter_device(c->device));
+  if (refine_steps > 0 && capturing(s))
+    return fail(PINV_ERR_UNSUPPORTED, "a refined apply cannot be recorded into a graph "
+                                      "(pinv_apply_noalloc can)");
   Scratch sc;   // blocks of the context's memory
   sc.cache = &c->mem;
   sc.reclaim = reclaim_memory;

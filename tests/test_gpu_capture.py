@@ -41,3 +41,34 @@ def test_replays_equal_eager_applies(F):
         P.pinv_plan_release(plan)
     finally:
         P.pinv_context_destroy(ctx)
+
+
+def test_refined_apply_is_refused_under_capture():
+    """Refused before anything is recorded, alone and in a group; the capture goes on."""
+    from paper_2410_06129_amd import pinv as P
+    enc = synth.small_case(seed=1201, nx=16, ny=12, C=2, K=300, F=1).enc
+    ctx = P.pinv_context_create(0)
+    try:
+        plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED)
+        P.pinv_plan_wait(plan)
+        d = torch.randn(1, enc.M, dtype=torch.complex64, device="cuda")
+        x, y = (torch.full((1, enc.N), float("nan"), dtype=torch.complex64, device="cuda") for _ in range(2))
+        P.pinv_apply(ctx, plan, d, y)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for call in (lambda: P.pinv_apply(ctx, plan, d, x, refine_steps=1),
+                         lambda: P.pinv_apply_grouped(ctx, [(plan, d, x)], 1)):
+                with pytest.raises(P.PinvError) as e:
+                    call()
+                assert e.value.status == P.ERR_UNSUPPORTED
+            P.pinv_apply(ctx, plan, d, x)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, y)
+        P.pinv_apply(ctx, plan, d, x, refine_steps=1)   # not under capture
+        torch.cuda.synchronize()
+        del graph
+        P.pinv_plan_release(plan)
+    finally:
+        P.pinv_context_destroy(ctx)
