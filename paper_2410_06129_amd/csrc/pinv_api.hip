@@ -61,9 +61,18 @@ size_t DeviceCache::rounded(size_t bytes) {
   return n;
 }
 
+// While this lives the calling thread may allocate, free and query although a stream of
+// the process, this thread's or another's, is being captured in a stricter mode: none of
+// it concerns the captured work.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
+  RelaxedCapture relaxed;
   const size_t need = rounded(bytes);
-  std::lock_guard<std::mutex> g(mu_);
   const size_t most = need + need / (need > (256u << 20) ? 64 : 8);
   // Under graph capture: a block that this capture gave back on this stream, or a new one,
   // kept until the context is destroyed.
@@ -71,42 +80,48 @@ hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
   unsigned long long id = 0;
   if (s && hipStreamGetCaptureInfo(s, &cap, &id) != hipSuccess) (void)hipGetLastError();
   if (cap == hipStreamCaptureStatusActive) {
-    for (auto& c : captured_) {
-      Captured& b = c.second;
-      if (!b.idle || b.id != id || b.s != s || b.bytes < need || b.bytes > most) continue;
-      b.idle = false;
-      *p = c.first;
-      return hipSuccess;
-    }
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // allows the allocation
-    hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
-    if (r != hipSuccess) return r;
-    r = hipMalloc(p, need);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (r == hipSuccess) captured_[*p] = Captured{need, id, s, false};
-    return r;
-  }
-  for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
-    Idle& b = it->second;
-    if (b.ev) {
-      const hipError_t q = hipEventQuery(b.ev);
-      (void)hipGetLastError();
-      if (q != hipSuccess) {
-        if (b.s != s) continue;
-        // the same stream, or another one that took over its handle
-        const hipError_t w = hipStreamWaitEvent(s, b.ev, 0);
-        if (w != hipSuccess) return w;
+    {
+      std::lock_guard<std::mutex> g(mu_);
+      for (auto& c : captured_) {
+        Captured& b = c.second;
+        if (!b.idle || b.id != id || b.s != s || b.bytes < need || b.bytes > most) continue;
+        b.idle = false;
+        *p = c.first;
+        return hipSuccess;
       }
-      events_.push_back(b.ev);
     }
-    *p = b.p;
-    live_[b.p] = it->first;
-    idle_.erase(it);
+    const hipError_t r = hipMalloc(p, need);
+    if (r != hipSuccess) return r;
+    std::lock_guard<std::mutex> g(mu_);
+    captured_[*p] = Captured{need, id, s, false};
     return hipSuccess;
   }
-  const hipError_t e = hipMalloc(p, need);
-  if (e == hipSuccess) live_[*p] = need;
-  return e;
+  {
+    std::lock_guard<std::mutex> g(mu_);
+    for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
+      Idle& b = it->second;
+      if (b.ev) {
+        const hipError_t q = hipEventQuery(b.ev);
+        (void)hipGetLastError();
+        if (q != hipSuccess) {
+          if (b.s != s) continue;
+          // the same stream, or another one that took over its handle
+          const hipError_t w = hipStreamWaitEvent(s, b.ev, 0);
+          if (w != hipSuccess) return w;
+        }
+        events_.push_back(b.ev);
+      }
+      *p = b.p;
+      live_[b.p] = it->first;
+      idle_.erase(it);
+      return hipSuccess;
+    }
+  }
+  const hipError_t e = hipMalloc(p, need);   // (other threads' calls go on meanwhile)
+  if (e != hipSuccess) return e;
+  std::lock_guard<std::mutex> g(mu_);
+  live_[*p] = need;
+  return hipSuccess;
 }
 
 void DeviceCache::add(void* p, hipEvent_t ev, hipStream_t s) {
@@ -117,6 +132,7 @@ void DeviceCache::add(void* p, hipEvent_t ev, hipStream_t s) {
 }
 
 hipError_t DeviceCache::put(void* p, hipStream_t s) {
+  RelaxedCapture relaxed;
   std::lock_guard<std::mutex> g(mu_);
   auto c = captured_.find(p);
   if (c != captured_.end()) {
@@ -148,6 +164,7 @@ void DeviceCache::put_idle(void* p) {
 }
 
 void DeviceCache::trim(bool wait) {
+  RelaxedCapture relaxed;
   std::lock_guard<std::mutex> g(mu_);
   for (auto it = idle_.begin(); it != idle_.end();) {
     hipEvent_t ev = it->second.ev;
@@ -1019,8 +1036,9 @@ extern "C++" void pinv_context_trim_scratch(pinv_context* c) { trim_memory(c, fa
 
 // After an allocation failed: the stream's own work completes, then all idle
 // memory (build workspaces and released plans included) goes back to the device.
+// (A capturing stream has no work to wait for, and the wait would end its capture.)
 static void reclaim_memory(void* arg, hipStream_t s) {
-  (void)hipStreamSynchronize(s);
+  if (!capturing(s)) (void)hipStreamSynchronize(s);
   trim_memory((pinv_context*)arg, true, true);
 }
 
