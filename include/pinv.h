@@ -294,7 +294,10 @@ pinv_status pinv_encoding_key(const pinv_encoding *e, const pinv_build_opts *o, 
  * M alone, and a frame's result does not depend on the values of the other
  * frames.  A stream under graph capture records the apply; with refine_steps > 0
  * that is refused (replays of a recorded refinement have faulted; pinv_apply_noalloc
- * takes refine_steps there).  Errors: INVALID, NOMEM (scratch), UNSUPPORTED (a refined
+ * takes refine_steps there).  Scratch of a recorded apply is allocated for its
+ * capture (up to 256 MB with many frames) and stays until
+ * pinv_context_release_captures or the context's end, also after the graph is gone.
+ * Errors: INVALID, NOMEM (scratch), UNSUPPORTED (a refined
  * apply under capture), DEVICE. */
 pinv_status pinv_apply(pinv_context *ctx, const pinv_plan *p, const void *data, int64_t F,
                        void *image, int32_t refine_steps, void *hip_stream);
@@ -408,6 +411,12 @@ pinv_status pinv_plan_release(pinv_plan *p);
  * workspaces when less than a quarter of the device is free, and for all of it
  * when a plan or workspace allocation fails. */
 pinv_status pinv_context_trim(pinv_context *ctx);
+
+/* Free the scratch of every apply recorded into a graph on this context (see
+ * pinv_apply): the library cannot see when a graph and its executable copies are
+ * destroyed.  To be called when they all are and no apply is being recorded; waits
+ * for the device. */
+pinv_status pinv_context_release_captures(pinv_context *ctx);
 
 /* Evict every cached plan no caller holds; returns the bytes freed in *freed. */
 pinv_status pinv_cache_trim(pinv_context *ctx, size_t *freed);

@@ -75,7 +75,7 @@ hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
   const size_t need = rounded(bytes);
   const size_t most = need + need / (need > (256u << 20) ? 64 : 8);
   // Under graph capture: a block that this capture gave back on this stream, or a new one,
-  // kept until the context is destroyed.
+  // kept until release_captured.
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   unsigned long long id = 0;
   if (s && hipStreamGetCaptureInfo(s, &cap, &id) != hipSuccess) (void)hipGetLastError();
@@ -181,6 +181,21 @@ void DeviceCache::trim(bool wait) {
     for (hipEvent_t e : events_) (void)hipEventDestroy(e);
     events_.clear();
   }
+}
+
+void DeviceCache::release_captured() {
+  RelaxedCapture relaxed;
+  std::lock_guard<std::mutex> g(mu_);
+  for (auto it = captured_.begin(); it != captured_.end();) {
+    // (a block not given back belongs to a call still under way)
+    if (it->second.idle) {
+      (void)hipFree(it->first);   // waits for the device
+      it = captured_.erase(it);
+    } else {
+      ++it;
+    }
+  }
+  (void)hipGetLastError();
 }
 
 void DeviceCache::release_all() {
@@ -1418,6 +1433,13 @@ extern "C" pinv_status pinv_context_trim(pinv_context* c) {
   if (!c) return fail(PINV_ERR_INVALID, "context is NULL");
   HIPCHK(enter_device(c->device));
   trim_memory(c, true, true);
+  return PINV_OK;
+}
+
+extern "C" pinv_status pinv_context_release_captures(pinv_context* c) {
+  if (!c) return fail(PINV_ERR_INVALID, "context is NULL");
+  HIPCHK(enter_device(c->device));
+  c->mem.release_captured();
   return PINV_OK;
 }
 

@@ -52,6 +52,8 @@ class DeviceCache {
   // Give idle blocks back to the device: those whose work has completed, or all
   // after waiting for it.
   void trim(bool wait);
+  // Blocks recorded into graphs, once those are gone.
+  void release_captured();
   // Everything, blocks still in use included; the device must be idle.
   void release_all();
   size_t idle_bytes();
@@ -68,8 +70,10 @@ class DeviceCache {
   std::multimap<size_t, Idle> idle_;
   std::map<void*, size_t> live_;
   std::vector<hipEvent_t> events_;   // spare events
-  // Blocks handed out to a stream under graph capture, which belong to that capture for
-  // good: a replay may use them at any time.
+  // Blocks handed out to a stream under graph capture, which belong to that capture until
+  // release_captured: a replay may use them at any time.  (A user object retained by the
+  // graph would tell of its end, but is not released with the graph's executable copies
+  // on this runtime.)
   struct Captured {
     size_t bytes;
     unsigned long long id;   // of the capture

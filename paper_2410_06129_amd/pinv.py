@@ -121,6 +121,7 @@ _sigs = {
                            ctypes.POINTER(ctypes.c_int32)],
     "pinv_plan_query": [_vp],
     "pinv_context_trim": [_vp],
+    "pinv_context_release_captures": [_vp],
     "pinv_encoding_key": [ctypes.POINTER(pinv_encoding), ctypes.POINTER(pinv_build_opts),
                           ctypes.POINTER(ctypes.c_uint64), ctypes.POINTER(ctypes.c_size_t)],
     "pinv_server_create": [_vp, ctypes.c_int, ctypes.POINTER(pinv_server_opts), ctypes.POINTER(_vp)],
@@ -435,6 +436,10 @@ def pinv_plan_query(plan: int) -> int:
 
 def pinv_context_trim(ctx: int) -> None:
     _check(_lib.pinv_context_trim(ctx), "pinv_context_trim")
+
+
+def pinv_context_release_captures(ctx: int) -> None:
+    _check(_lib.pinv_context_release_captures(ctx), "pinv_context_release_captures")
 
 
 def pinv_encoding_key(enc, lam: float, lambda_mode: int = LAMBDA_REL_MEAN_DIAG, prec: int = FP32,

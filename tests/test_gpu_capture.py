@@ -72,3 +72,50 @@ def test_refined_apply_is_refused_under_capture():
         P.pinv_plan_release(plan)
     finally:
         P.pinv_context_destroy(ctx)
+
+
+def test_scratch_of_gone_graphs_is_released():
+    """Recorded again and again, graphs leave their scratch with the context; it goes back
+    to the device on request, and later captures take new scratch."""
+    from paper_2410_06129_amd import pinv as P
+    F = 400
+    enc = synth.small_case(seed=1202, nx=32, ny=32, C=4, K=4000, F=1).enc
+    ctx = P.pinv_context_create(0)
+    try:
+        plan = P.pinv_build(ctx, enc, 1e-2, P.LAMBDA_REL_MEAN_DIAG, P.FP32, P.FLAG_UNCACHED)
+        P.pinv_plan_wait(plan)
+        d = torch.randn(F, enc.M, dtype=torch.complex64, device="cuda")
+        x, y = (torch.full((F, enc.N), float("nan"), dtype=torch.complex64, device="cuda") for _ in range(2))
+        P.pinv_apply(ctx, plan, d, y)
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+
+        def record():
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                P.pinv_apply(ctx, plan, d, x)
+            return graph
+
+        def used():
+            torch.cuda.synchronize()
+            free, total = torch.cuda.mem_get_info()
+            return total - free
+        first = record()
+        del first
+        P.pinv_context_release_captures(ctx)
+        before = used()
+        graphs = [record() for _ in range(6)]
+        scratch = 8 * (enc.N + F) * enc.M // 2    # at least half of R and the data, packed
+        assert used() - before >= 5 * scratch
+        del graphs
+        P.pinv_context_release_captures(ctx)
+        assert used() - before < scratch
+        graph = record()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, y)
+        del graph
+        P.pinv_plan_release(plan)
+    finally:
+        P.pinv_context_destroy(ctx)
