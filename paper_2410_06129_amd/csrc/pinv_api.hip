@@ -52,6 +52,9 @@ static hipError_t enter_device(int device) {
 // ---------------------------------------------------------------------------
 namespace pinv {
 
+// Idle blocks up to this total are kept whatever was in use.
+constexpr size_t kCacheSlack = (size_t)256 << 20;
+
 // Block sizes: powers of two up to 1 MB (few, so that small buffers are shared by
 // encodings of similar sizes), whole 2 MB beyond.
 size_t DeviceCache::rounded(size_t bytes) {
@@ -96,39 +99,92 @@ hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
     captured_[*p] = Captured{need, id, s, false};
     return hipSuccess;
   }
+  std::vector<Idle> out;
   {
     std::lock_guard<std::mutex> g(mu_);
-    for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
-      Idle& b = it->second;
-      if (b.ev) {
-        const hipError_t q = hipEventQuery(b.ev);
-        (void)hipGetLastError();
-        if (q != hipSuccess) {
-          if (b.s != s) continue;
-          // the same stream, or another one that took over its handle
-          const hipError_t w = hipStreamWaitEvent(s, b.ev, 0);
-          if (w != hipSuccess) return w;
-        }
-        events_.push_back(b.ev);
-      }
-      *p = b.p;
-      live_[b.p] = it->first;
-      idle_.erase(it);
-      return hipSuccess;
+    hipError_t r = take(p, need, most, s);
+    if (r != hipErrorNotFound) return r;
+    // A new block.  Where all blocks would come to more than twice what was ever in use at
+    // once, a larger idle one serves instead, or those that lay idle longest go.
+    const size_t bound = 2 * std::max(peak_, in_use_ + need) + kCacheSlack;
+    if (blocks_ + need > bound) {
+      r = take(p, need, 2 * need, s);
+      if (r != hipErrorNotFound) return r;
+      evict(blocks_ + need - bound, &out);
     }
+    blocks_ += need;
   }
+  drop(out);
   const hipError_t e = hipMalloc(p, need);   // (other threads' calls go on meanwhile)
-  if (e != hipSuccess) return e;
   std::lock_guard<std::mutex> g(mu_);
-  live_[*p] = need;
-  return hipSuccess;
+  if (e == hipSuccess)
+    hand_out(*p, need, need);
+  else
+    blocks_ -= need;
+  return e;
+}
+
+// The smallest idle block of need .. most bytes that work on `s` may use now, or
+// hipErrorNotFound.
+hipError_t DeviceCache::take(void** p, size_t need, size_t most, hipStream_t s) {
+  for (auto it = idle_.lower_bound(need); it != idle_.end() && it->first <= most; ++it) {
+    Idle& b = it->second;
+    if (b.ev) {
+      const hipError_t q = hipEventQuery(b.ev);
+      (void)hipGetLastError();
+      if (q != hipSuccess) {
+        if (b.s != s) continue;
+        // the same stream, or another one that took over its handle
+        const hipError_t w = hipStreamWaitEvent(s, b.ev, 0);
+        if (w != hipSuccess) return w;
+      }
+      events_.push_back(b.ev);
+    }
+    *p = b.p;
+    hand_out(b.p, it->first, need);
+    idle_.erase(it);
+    return hipSuccess;
+  }
+  return hipErrorNotFound;
+}
+
+void DeviceCache::hand_out(void* p, size_t bytes, size_t need) {
+  live_[p] = Live{bytes, need};
+  in_use_ += need;
+  peak_ = std::max(peak_, in_use_);
 }
 
 void DeviceCache::add(void* p, hipEvent_t ev, hipStream_t s) {
   auto it = live_.find(p);
   if (it == live_.end()) return;
-  idle_.emplace(it->second, Idle{p, ev, s});
+  idle_.emplace(it->second.bytes, Idle{p, ev, s, ++seq_});
+  in_use_ -= it->second.need;
   live_.erase(it);
+}
+
+// At least `bytes` of idle blocks whose work has completed into `out`, those idle
+// longest first (all there are, if fewer).
+void DeviceCache::evict(size_t bytes, std::vector<Idle>* out) {
+  std::vector<std::multimap<size_t, Idle>::iterator> age;
+  for (auto it = idle_.begin(); it != idle_.end(); ++it) age.push_back(it);
+  std::sort(age.begin(), age.end(), [](auto a, auto b) { return a->second.seq < b->second.seq; });
+  size_t got = 0;
+  for (auto it : age) {
+    if (got >= bytes) break;
+    if (it->second.ev && hipEventQuery(it->second.ev) != hipSuccess) continue;
+    got += it->first;
+    blocks_ -= it->first;
+    out->push_back(it->second);
+    idle_.erase(it);
+  }
+  (void)hipGetLastError();
+}
+
+void DeviceCache::drop(const std::vector<Idle>& out) {
+  for (const Idle& b : out) {
+    (void)hipFree(b.p);
+    if (b.ev) (void)hipEventDestroy(b.ev);
+  }
 }
 
 hipError_t DeviceCache::put(void* p, hipStream_t s) {
@@ -163,24 +219,16 @@ void DeviceCache::put_idle(void* p) {
   add(p, nullptr, nullptr);
 }
 
-void DeviceCache::trim(bool wait) {
+void DeviceCache::trim(size_t keep) {
   RelaxedCapture relaxed;
-  std::lock_guard<std::mutex> g(mu_);
-  for (auto it = idle_.begin(); it != idle_.end();) {
-    hipEvent_t ev = it->second.ev;
-    if (ev && (wait ? hipEventSynchronize(ev) : hipEventQuery(ev)) != hipSuccess && !wait) {
-      ++it;
-      continue;
-    }
-    (void)hipFree(it->second.p);
-    if (ev) (void)hipEventDestroy(ev);
-    it = idle_.erase(it);
+  std::vector<Idle> out;
+  {
+    std::lock_guard<std::mutex> g(mu_);
+    size_t idle = 0;
+    for (auto& kv : idle_) idle += kv.first;
+    if (idle > keep) evict(idle - keep, &out);
   }
-  (void)hipGetLastError();
-  if (wait) {
-    for (hipEvent_t e : events_) (void)hipEventDestroy(e);
-    events_.clear();
-  }
+  drop(out);
 }
 
 void DeviceCache::release_captured() {
@@ -199,10 +247,17 @@ void DeviceCache::release_captured() {
 }
 
 void DeviceCache::release_all() {
-  trim(true);
   std::lock_guard<std::mutex> g(mu_);
+  for (auto& kv : idle_) {
+    (void)hipFree(kv.second.p);
+    if (kv.second.ev) (void)hipEventDestroy(kv.second.ev);
+  }
+  idle_.clear();
+  for (hipEvent_t e : events_) (void)hipEventDestroy(e);
+  events_.clear();
   for (auto& kv : live_) (void)hipFree(kv.first);
   live_.clear();
+  blocks_ = in_use_ = 0;
   for (auto& kv : captured_) (void)hipFree(kv.first);
   captured_.clear();
 }
@@ -1028,21 +1083,32 @@ pinv_status pinv_encoding_key(const pinv_encoding* e, const pinv_build_opts* o, 
 // it (the caller's tensors) can use it: workspaces and scratch, and with `plans`
 // also released plans' buffers.  Unforced, only when less than a quarter of the
 // device is free and at least 2% of it is idle here: mapping a multi-GB buffer anew
-// costs the next build milliseconds and slows whatever else runs meanwhile.  Plan
-// memory is handed back only on request or when an allocation fails, so later
-// plans reuse it.
+// costs the next build milliseconds and slows whatever else runs meanwhile.  (The
+// serving loop keeps released plans' memory for the plans that replace them.)
 static void trim_memory(pinv_context* c, bool force, bool plans) {
   size_t fr = 0, tot = 0;
-  if (!force && hipMemGetInfo(&fr, &tot) == hipSuccess &&
-      (fr >= tot / 4 || c->mem.idle_bytes() < tot / 50))
-    return;
+  if (!force && hipMemGetInfo(&fr, &tot) == hipSuccess) {
+    if (fr >= tot / 4) return;
+    if (plans) drain_frees(c, false);
+    if (c->mem.idle_bytes() + (plans ? c->plan_mem.idle_bytes() : 0) < tot / 50) return;
+  }
   hipMemPool_t pool;   // metrics' temporaries
   if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
-  c->mem.trim(false);
+  c->mem.trim(0);
   if (plans) {
     drain_frees(c, false);
-    c->plan_mem.trim(false);
+    c->plan_mem.trim(0);
   }
+}
+
+// Idle memory of the context within what its plans leave of the budget.  (A plan of the
+// size of one released before it finds that one's memory here.)
+static void bound_idle(pinv_context* c) {
+  const size_t most = c->budget > c->used ? c->budget - c->used : 0;
+  if (c->mem.idle_bytes() + c->plan_mem.idle_bytes() <= most) return;
+  c->mem.trim(most / 2);
+  const size_t work = c->mem.idle_bytes();
+  c->plan_mem.trim(most > work ? most - work : 0);
 }
 
 // Idle memory back to the device under memory pressure (the serving loop calls
@@ -1133,6 +1199,7 @@ pinv_status pinv_build(pinv_context* c, const pinv_encoding* e, const pinv_build
   if (!room)
     return fail(PINV_ERR_NOMEM, "plan footprint " + std::to_string(foot) +
                                     " B exceeds the free budget");
+  bound_idle(c);
 
   pinv_plan* p = new pinv_plan();
   p->ctx = c;
@@ -1448,7 +1515,7 @@ pinv_status pinv_plan_wait(pinv_plan* p) {
   if (!p->waited) {
     HIPCHK(enter_device(p->ctx->device));
     HIPCHK(hipEventSynchronize(p->ev[4]));
-    trim_memory(p->ctx, false, false);
+    trim_memory(p->ctx, false, true);
     HIPCHK(hipMemcpy(&p->info_host, p->info, sizeof(int), hipMemcpyDeviceToHost));
     for (int i = 0; i < 4; ++i) HIPCHK(hipEventElapsedTime(&p->stage_ms[i], p->ev[i], p->ev[i + 1]));
     if (p->no_r) p->stage_ms[2] = p->stage_ms[3] = 0.f;   // no W or R was formed

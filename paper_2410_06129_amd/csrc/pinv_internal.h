@@ -38,8 +38,12 @@ struct ApplyBatch {     // passed by value as a kernel argument
 // scratch of applies).  put() hands a block back behind the work enqueued on `s`;
 // get() takes the smallest idle block of at least `bytes`, and at most an eighth
 // more (a 64th above 256 MB), whose last work has completed or was enqueued on the
-// same stream (behind which the caller's work then waits), else a new block.  Nothing waits on the
-// host.  All calls are safe from several threads and streams.  The runtime's
+// same stream (behind which the caller's work then waits), else a new block.  Nothing
+// waits on the host.  Blocks are neither split nor joined; together they come to at
+// most twice what was in use at once (and 256 MB), so that two sizes in turn each keep
+// theirs and many do not add up: beyond it a get() takes an idle block of up to twice
+// the size, or frees those idle longest (which waits for the device).  All calls are
+// safe from several threads and streams.  The runtime's
 // stream-ordered pools served this before: each hipFreeAsync took the host 15 to
 // 25 us, and with several sizes in turn they returned gigabyte blocks to the device
 // and mapped them again (50 ms, up to 2 s) in the middle of steady work.
@@ -49,9 +53,9 @@ class DeviceCache {
   hipError_t put(void* p, hipStream_t s);
   // As put, for a block whose work has completed.
   void put_idle(void* p);
-  // Give idle blocks back to the device: those whose work has completed, or all
-  // after waiting for it.
-  void trim(bool wait);
+  // Give idle blocks whose work has completed back to the device, until `keep` bytes are
+  // left.
+  void trim(size_t keep);
   // Blocks recorded into graphs, once those are gone.
   void release_captured();
   // Everything, blocks still in use included; the device must be idle.
@@ -63,12 +67,23 @@ class DeviceCache {
     void* p;
     hipEvent_t ev;     // null: no work pending
     hipStream_t s;
+    uint64_t seq;      // order of return
+  };
+  struct Live {
+    size_t bytes, need;   // of the block, asked for
   };
   static size_t rounded(size_t bytes);
-  void add(void* p, hipEvent_t ev, hipStream_t s);   // mu_ held
+  static void drop(const std::vector<Idle>& out);
+  // mu_ held:
+  hipError_t take(void** p, size_t need, size_t most, hipStream_t s);
+  void hand_out(void* p, size_t bytes, size_t need);
+  void add(void* p, hipEvent_t ev, hipStream_t s);
+  void evict(size_t bytes, std::vector<Idle>* out);
   std::mutex mu_;
   std::multimap<size_t, Idle> idle_;
-  std::map<void*, size_t> live_;
+  std::map<void*, Live> live_;
+  size_t blocks_ = 0, in_use_ = 0, peak_ = 0;   // bytes of all blocks; asked for and in use; its most
+  uint64_t seq_ = 0;
   std::vector<hipEvent_t> events_;   // spare events
   // Blocks handed out to a stream under graph capture, which belong to that capture until
   // release_captured: a replay may use them at any time.  (A user object retained by the
