@@ -1553,7 +1553,7 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
   const TS* d = (const TS*)data;
   TS* x = (TS*)image;
   void *b = nullptr, *rd = nullptr, *r = nullptr, *t = nullptr;
-  hipError_t e;
+  hipError_t e = hipSuccess;
   // (b before r and t: the forms of E^H d that take more scratch than the direct sum then
   // find half of a fixed region free whenever the whole call fits it, so they run there
   // as they do elsewhere)
@@ -1575,8 +1575,6 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
     if (e == hipSuccess && !formed)
       e = launch_adjoint<double, TS, TS, double>(p->e64, d, F, (const TS*)nullptr, 0.0, (double*)b,
                                                  sc, s);
-  } else {
-    e = sc.get(&rd, 16 * (size_t)F * M, s);
   }
   if (e == hipSuccess) e = sc.get(&r, 2 * sizeof(TS) * (size_t)F * N, s);
   if (e == hipSuccess) e = sc.get(&t, 2 * sizeof(TS) * (size_t)F * N, s);
@@ -1584,15 +1582,20 @@ static pinv_status refine_item(pinv_plan* p, const void* data, int F, void* imag
     if (p->gram_exact) {
       e = launch_resid<TS, TS>((const double*)p->gram, (const double*)b, x, F, p->N, p->lam, (TS*)r, sc, s);
     } else {
+      // (rd is given back before the triangular products, whose parts find its place in a
+      // fixed region)
+      if ((e = sc.get(&rd, 16 * (size_t)F * M, s)) != hipSuccess) break;
       e = launch_forward<double, TS, TS>(p->e64, x, F, d, (double*)rd, s);
       if (e == hipSuccess)
         e = launch_adjoint<double, double, TS, TS>(p->e64, (const double*)rd, F, x, p->lam, (TS*)r,
                                                    sc, s);
+      const hipError_t ferr = sc.put(rd, s);
+      if (e == hipSuccess) e = ferr;
     }
     if (e == hipSuccess) e = launch_tri_frames<TS, 0, TS>((const TS*)p->Linv, (const TS*)r, F, p->N, (TS*)t, sc, s);
     if (e == hipSuccess) e = launch_tri_frames<TS, 1, TS>((const TS*)p->Linv, (const TS*)t, F, p->N, x, sc, s);
   }
-  for (void* q : {t, r, rd, b})   // most recent first (the fixed-region scratch is a stack)
+  for (void* q : {t, r, b})   // most recent first (the fixed-region scratch is a stack)
     if (q) (void)sc.put(q, s);
   HIPCHK(e);
   return PINV_OK;
