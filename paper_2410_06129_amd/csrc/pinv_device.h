@@ -966,8 +966,9 @@ template <class Cfg, int OUTER> struct LoadSP {
 // column n of E, element (o, k) = E[o, k] (or its conjugate).  Each thread
 // generates KPT consecutive columns of one row and splits them into packed
 // hi/lo words as it goes (finish), so store_b3 only moves 16-byte pieces.
-// ALIGNED as for LoadGenRow.  (finish and store_b3: elements in FP32.)
-template <class Cfg, int OUTER, bool CONJ, int FEAT, bool ALIGNED = false, class ET = float>
+// ALIGNED as for LoadGenRow.  SIDE: a row's threads are neighbours, else a column group's.
+// (finish and store_b3: elements in FP32, not SIDE.)
+template <class Cfg, int OUTER, bool CONJ, int FEAT, bool ALIGNED = false, class ET = float, bool SIDE = false>
 struct LoadGenRowSP {
   typedef ET T;
   static constexpr int TPR = Cfg::NT / OUTER;        // threads per row
@@ -983,12 +984,12 @@ struct LoadGenRowSP {
   uint32_t pk[GPT][4][4];   // [group][plane][word]
   __device__ __forceinline__ void init(const EncDev<T>& enc, int o0) {
     e = enc;
-    const int m = o0 + threadIdx.x % OUTER;
+    const int m = o0 + (int)(SIDE ? threadIdx.x / TPR : threadIdx.x % OUTER);
     valid = m < e.M;
     const int mm = valid ? m : 0;
     c = mm / e.K;
     i = mm - c * e.K;
-    kk0 = (int)(threadIdx.x / OUTER) * KPT;
+    kk0 = (int)(SIDE ? threadIdx.x % TPR : threadIdx.x / OUTER) * KPT;
     if constexpr (ALIGNED && (FEAT & FEAT_B0) != 0) ti = e.t[i];
   }
   __device__ __forceinline__ void fetch(int k0, int kend) {

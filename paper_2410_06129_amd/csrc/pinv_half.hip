@@ -356,8 +356,11 @@ __global__ __launch_bounds__(256) void k_factor_pack(const double* __restrict__ 
 // conj(E), packed: rows m0 .. m0 + rows of samples, columns n, scaled by 2^es
 // ---------------------------------------------------------------------------
 // Workgroup b takes 64 rows and kGenChunksH chunks; thread t generates columns
-// 8 (t / 64) .. + 8 of row t % 64 of each chunk, in FP64, so that the split is E's only
-// rounding.
+// 8 (t % 4) .. + 8 of row t / 4 of each chunk, in FP64, so that the split is E's only
+// rounding.  Four neighbouring lanes read 512 contiguous bytes of a row's table and write
+// 64 of each plane: 620 us for N = 4096, M = 32768 (928 with a column group's rows side by
+// side; 522 from FP32 tables, whose roundings come on top of the split's), 5.5 ms for N =
+// 9216, M = 131072.
 constexpr int kGenChunksH = 16;
 struct GenHCfg { static constexpr int NT = 256, BK = 32; };
 
@@ -366,9 +369,9 @@ __global__ __launch_bounds__(256) void k_gen_e_h(EncDev<double> e, int m0, int r
                                                  char* __restrict__ Es) {
   const int nbc = (nc + kGenChunksH - 1) / kGenChunksH;
   const int r0 = (int)(blockIdx.x / nbc) * 64, cb = (int)(blockIdx.x % nbc);
-  LoadGenRowSP<GenHCfg, 64, true, FEAT, AL, double> g;
+  LoadGenRowSP<GenHCfg, 64, true, FEAT, AL, double, true> g;
   g.init(e, m0 + r0);
-  const int o = threadIdx.x % 64, gq = (int)(threadIdx.x / 64);
+  const int o = threadIdx.x / 4, gq = (int)(threadIdx.x % 4);
   const bool live = r0 + o < rows;
   for (int c = 0; c < kGenChunksH; ++c) {
     const int ck = cb * kGenChunksH + c;
