@@ -108,7 +108,7 @@ hipError_t DeviceCache::get(void** p, size_t bytes, hipStream_t s) {
     // once, a larger idle one serves instead, or those that lay idle longest go.
     const size_t bound = 2 * std::max(peak_, in_use_ + need) + kCacheSlack;
     if (blocks_ + need > bound) {
-      r = take(p, need, 2 * need, s);
+      r = take(p, need, loose_ ? SIZE_MAX : 2 * need, s);
       if (r != hipErrorNotFound) return r;
       evict(blocks_ + need - bound, &out);
     }
@@ -328,8 +328,8 @@ struct pinv_context {
   };
   std::mutex free_mu;
   std::vector<PendingFree> pending;
-  DeviceCache mem;        // build workspaces (Gram, FP64 factor, W) and scratch of applies
-  DeviceCache plan_mem;   // plan buffers (R, L^-1, Gram, tables)
+  DeviceCache mem{true};         // build workspaces (Gram, FP64 factor, W) and scratch of applies
+  DeviceCache plan_mem{false};   // plan buffers (R, L^-1, Gram, tables)
   // pinned staging for table uploads, reused by every build of the context:
   // stage_ev marks the completion of the last copies out of it
   std::mutex stage_mu;

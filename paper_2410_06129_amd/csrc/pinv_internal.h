@@ -41,14 +41,18 @@ struct ApplyBatch {     // passed by value as a kernel argument
 // same stream (behind which the caller's work then waits), else a new block.  Nothing
 // waits on the host.  Blocks are neither split nor joined; together they come to at
 // most twice what was in use at once (and 256 MB), so that two sizes in turn each keep
-// theirs and many do not add up: beyond it a get() takes an idle block of up to twice
-// the size, or frees those idle longest (which waits for the device).  All calls are
-// safe from several threads and streams.  The runtime's
-// stream-ordered pools served this before: each hipFreeAsync took the host 15 to
-// 25 us, and with several sizes in turn they returned gigabyte blocks to the device
-// and mapped them again (50 ms, up to 2 s) in the middle of steady work.
+// theirs and many do not add up: beyond it a get() takes a larger idle block, or frees
+// those idle longest (which waits for the device: 20 plans of sizes 6% apart in turn,
+// 100 MB to 3 GB each, 0.5 ms a plan; 48 GB were kept without the bound).  All calls are
+// safe from several threads and streams.  The runtime's stream-ordered pools served
+// this before: each hipFreeAsync took the host 15 to 25 us, and with several sizes in
+// turn they returned gigabyte blocks to the device and mapped them again (50 ms, up to
+// 2 s) in the middle of steady work.
 class DeviceCache {
  public:
+  // loose: for blocks soon given back, of which any larger idle one may serve a request
+  // beyond the bound (else up to twice the size).
+  explicit DeviceCache(bool loose) : loose_(loose) {}
   hipError_t get(void** p, size_t bytes, hipStream_t s);
   hipError_t put(void* p, hipStream_t s);
   // As put, for a block whose work has completed.
@@ -79,6 +83,7 @@ class DeviceCache {
   void hand_out(void* p, size_t bytes, size_t need);
   void add(void* p, hipEvent_t ev, hipStream_t s);
   void evict(size_t bytes, std::vector<Idle>* out);
+  const bool loose_;
   std::mutex mu_;
   std::multimap<size_t, Idle> idle_;
   std::map<void*, Live> live_;
