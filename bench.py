@@ -156,7 +156,7 @@ def cpu_baseline(enc, rows: int = 4096) -> dict:
 # ----------------------------------------------------------------------------
 
 DEVICE_SOURCES = ("pinv_device.h", "pinv_internal.h", "pinv_trmm.hip", "pinv_apply.hip",
-                  "pinv_split.hip")
+                  "pinv_split.hip", "pinv_half.hip")
 
 
 def kernel_source_hash() -> str:
@@ -236,7 +236,7 @@ def pmc_mfma_summary(d) -> dict:
     disp = defaultdict(set)
     names = dict(PMC_KERNELS, gram_psf="k_psf(", chol_trailing="k_chol_trailing", chol_panel="k_chol_panel",
                  gen_e_bf16x3="k_gen_e_sp<", gram_shared="k_gram_shared<", gram_full="k_gram<",
-                 chol_diag="k_chol_diag", adjoint_fp64="k_grid_spread<", resid="k_resid", tri_frames="k_tri_frames",
+                 chol_diag="k_chol_diag", gen_e_half="k_gen_e_h<", apply_pack="k_pack_half<", adjoint_fp64="k_grid_spread<", resid="k_resid", tri_frames="k_tri_frames",
                  trmm_w_fp64_formed="k_trmm_w<pinv::TileCfg<double",
                  trmm_r_fp64_formed="k_trmm_r<pinv::TileCfg<double, 64, 64, 8, false, 2>, float>",
                  apply_seg="k_apply<pinv::TileCfg<float, 128, 64, 8, false, 2>, true>")
@@ -250,7 +250,7 @@ def pmc_mfma_summary(d) -> dict:
         g = a.get("GRBM_GUI_ACTIVE", 0.0) / 8
         if g <= 0:
             continue
-        mops = {t: a.get("SQ_INSTS_VALU_MFMA_MOPS_" + t, 0.0) * 512 for t in ("F32", "F64", "BF16")}
+        mops = {t: a.get("SQ_INSTS_VALU_MFMA_MOPS_" + t, 0.0) * 512 for t in ("F32", "F64", "BF16", "F16")}
         out["kernels"][key] = {"dispatches": len(disp[key]), "cycles_per_xcd": g,
                                "mfma_busy": a.get("SQ_VALU_MFMA_BUSY_CYCLES", 0.0) / (g * 1024),
                                "lds_bank_conflict_frac": a.get("SQ_LDS_BANK_CONFLICT", 0.0) / 256 / g,
@@ -870,7 +870,10 @@ def pmc_run(args) -> None:
     few = {"fp32": (1, 16, 32), "bf16x3": (16,), "fp32_r_fp64": ()}
     for name, prec, flags, refine in (("fp32", P.FP32, 0, 1), ("bf16x3", P.BF16X3, 0, 0),
                                       ("fp32_r_fp64", P.FP32, P.FLAG_R_FP64, 0)):
-        p = P.pinv_build(ctx, enc, w.rel_lambda, P.LAMBDA_REL_MEAN_DIAG, prec, flags | P.FLAG_UNCACHED)
+        # (4M: the applies of an FP64-formed R on FP32 instructions, not on the pieces'
+        # kernels that the FP32 plan's apply counts)
+        p = P.pinv_build(ctx, enc, w.rel_lambda, P.LAMBDA_REL_MEAN_DIAG, prec, flags | P.FLAG_UNCACHED,
+                         cprod=P.CPROD_4M if flags else P.CPROD_AUTO)
         P.pinv_apply(ctx, p, d, x, refine_steps=refine)
         for f in few[name]:   # one pass over R each
             P.pinv_apply(ctx, p, d[:f].contiguous(), x[:f])

@@ -57,8 +57,9 @@ typedef enum {
 
 typedef enum {
   PINV_FP64 = 0,    /* everything in FP64 (complex128 data and images) */
-  PINV_FP32 = 1,    /* W, R and apply on FP32 MFMA; the Gram (default form) and the
-                       factorisation in FP64 */
+  PINV_FP32 = 1,    /* W, R and apply in FP32, on f16 pieces of the operands or on FP32 MFMA
+                       (see pinv_cprod); the Gram (default form) and the factorisation in
+                       FP64 */
   PINV_BF16X3 = 2   /* as FP32 but products as three BF16 MFMAs (hi*hi + hi*lo + lo*hi),
                        operands split into bf16 hi/lo once, where produced */
 } pinv_precision;
@@ -106,12 +107,12 @@ typedef struct {
                                    PINV_BF16X3 (the split products only form W and R). */
 #define PINV_FLAG_R_FP64 16     /* PINV_FP32 plans only: form W = L^-1 E^H and R = L^-H W in FP64
                                    (E generated from the FP64 tables, L^-1 kept in FP64) and round
-                                   R once to complex64.  Applies then run on FP32 MFMA with the
-                                   error of that one rounding (~u32 times the cancellation in
-                                   R*data, about 1e-6 relative) instead of kappa(G)*u32, so they
-                                   need no refinement for a 1e-5 target (Sec. 5: lower precision
-                                   for the bulk of the arithmetic, results stored at higher
-                                   precision).  The build costs what an FP64 build costs. */
+                                   R once to complex64.  Applies then run in FP32 (see
+                                   pinv_cprod) with the error of that one rounding (~u32 times
+                                   the cancellation in R*data, about 1e-6 relative) instead of
+                                   kappa(G)*u32, so they need no refinement for a 1e-5 target
+                                   (Sec. 5: lower precision for the bulk of the arithmetic,
+                                   results stored at higher precision).  The build costs what an FP64 build costs. */
 
 /* Complex-product form of the triangular products W, R and the apply (MFMA).
  * FP32 plans on AUTO or 3M with M >= N run all but small products W and R, and
@@ -120,9 +121,9 @@ typedef struct {
  * pieces leave R at least as accurate as the FP32 instructions: sensitivities within
  * 2^12 of the largest over the unknown voxels (the largest coil's at each) and over
  * the coils, and a shift up to ten times the Gram's mean diagonal (the bound in full
- * stands at half_range in pinv_api.hip); elsewhere they run on FP32
- * instructions.  4M keeps every product on FP32 instructions, the applies of an
- * FP64-formed R (4M on AUTO, but on pieces) included. */
+ * stands at half_range in pinv_api.hip); elsewhere they run on FP32 instructions.
+ * Their applies need the sensitivities' bound alone.  4M keeps every product on FP32
+ * instructions, the applies of an FP64-formed R (4M on AUTO, but on pieces) included. */
 typedef enum {
   PINV_CPROD_AUTO = 0,   /* 3M for FP32 plans, 4M for FP64 plans and FP64-formed R */
   PINV_CPROD_3M = 1,     /* three real products per complex product (Gauss):

@@ -154,12 +154,13 @@ template <class C> struct HalfLoader {
 // accumulators, so the sums between FP32 roundings of the whole are 32 columns
 // long.  The instruction aligns the products of a group of eight to the largest
 // and cuts what falls below towards minus infinity when they meet a larger sum:
-// a bias of one sign in every element, which adds up coherently over the samples
-// of an apply (one 64 x 64 coil, M = 8192: unrefined images 2.1e-3 off, after one
-// refinement step 1.0e-6; FP32 instructions 1.75e-3 and 3.8e-8).  So every second chunk of operand A is stored negated, and
-// its sums are subtracted (SUB): the bias of one chunk cancels the next one's
-// (5.9e-4 and 3.8e-8), at the same speed.  Sums kept apart by their sign instead,
-// ar br - ai bi, cost 12% of the products' time and left 7.6e-8.
+// a bias of one sign in every element, which adds up coherently over the samples of an
+// apply.  So every second chunk of operand A is stored negated, and its sums are
+// subtracted (SUB): the bias of one chunk cancels the next one's, at the same speed.  One
+// 64 x 64 coil, M = 8192, E from FP32 tables: unrefined images 2.1e-3 off with the bias,
+// 5.9e-4 without, FP32 instructions 1.75e-3; after one refinement step 1.0e-6, 3.8e-8,
+// 3.8e-8.  Sums kept apart by their sign instead, ar br - ai bi, cost 12% of the
+// products' time and left 7.6e-8.
 template <class C, bool SUB>
 __device__ __forceinline__ void half_compute(const char* s, HalfAcc<C>& acc) {
   const int lane = threadIdx.x & 63;
@@ -402,13 +403,14 @@ __global__ __launch_bounds__(256) void k_gen_e_h(EncDev<double> e, int m0, int r
 // ---------------------------------------------------------------------------
 // W^T (packed, rows m, k = n) and R
 // ---------------------------------------------------------------------------
-// Bound by the f16 pipe's power budget: at N = 9216, M = 131072 the two products
-// take 142 and 136 ms (the shader clock falls to 1.6-1.7 GHz, the pipe 0.7 busy),
-// R at 1310 TFLOP/s of executed f16 products, what a plain bf16 library product
-// of 16384^3 reaches on the same card (1330); three real FP32 products per complex
-// one took 329 and 313 ms.  128 x 128 tiles over eight
-// wavefronts fill the 160 KB of LDS with two stages of 80 KB; the LDS moves
-// 344 KB a chunk (2700 cycles) against 4096 cycles of matrix products.
+// Bound by the f16 pipe and its power budget: at N = 16384, M = 262144 the two products
+// take 880 and 876 ms, 1290 TFLOP/s of executed f16 products, with the pipe 0.67 busy at
+// a shader clock of 1.84 GHz (counters; 2.2 GHz under the kernels around them) and no LDS
+// bank conflicts; three real FP32 products per complex one took 2057 and 1969.  At N =
+// 9216, M = 131072: 137 and 138 ms, 1310 TFLOP/s, where a plain bf16 library product of
+// 16384^3 reaches 1330; 329 and 313 on FP32.  128 x 128 tiles over eight wavefronts fill
+// the 160 KB of LDS with two stages of 80 KB; the LDS moves 344 KB a chunk (2700 cycles)
+// against 4096 cycles of matrix products.
 typedef HalfCfg<128, 128, 2, 4, 3> TrmmH;
 
 __global__ __launch_bounds__(TrmmH::NT, 1) void k_trmm_wh(const char* __restrict__ Lm,
