@@ -409,10 +409,10 @@ pinv_status pinv_plan_release(pinv_plan *p);
 /* Hand device memory that the context keeps after
  * completed work (refinement scratch, build workspaces, buffers of released
  * plans) back to the device.  The library keeps at most twice what was in use at
- * once, and at a build no more than its plans leave of the budget; it hands all of it
- * back by itself when a plan or workspace allocation fails, and in pinv_plan_wait
- * when less than a quarter of the device is free (the serving loop: scratch and
- * workspaces, after each batch). */
+ * once, and at a build no more than its plans leave of the budget and an eighth of it;
+ * it hands all of it back by itself when a plan or workspace allocation fails, and in
+ * pinv_plan_wait when less than a quarter of the device is free (the serving loop:
+ * scratch and workspaces, after each batch and build). */
 pinv_status pinv_context_trim(pinv_context *ctx);
 
 /* Free the scratch of every apply recorded into a graph on this context (see

@@ -1101,14 +1101,15 @@ static void trim_memory(pinv_context* c, bool force, bool plans) {
   }
 }
 
-// Idle memory of the context within what its plans leave of the budget.  (A plan of the
-// size of one released before it finds that one's memory here.)
+// Idle memory of the context within what its plans leave of the budget and an eighth of
+// it; beyond that all past what they leave goes at once, because each free waits for the
+// device.  (A plan of the size of one released before it finds that one's memory here.)
 static void bound_idle(pinv_context* c) {
-  const size_t most = c->budget > c->used ? c->budget - c->used : 0;
-  if (c->mem.idle_bytes() + c->plan_mem.idle_bytes() <= most) return;
-  c->mem.trim(most / 2);
-  const size_t work = c->mem.idle_bytes();
-  c->plan_mem.trim(most > work ? most - work : 0);
+  const size_t left = c->budget > c->used ? c->budget - c->used : 0;
+  const size_t work = c->mem.idle_bytes(), plans = c->plan_mem.idle_bytes();
+  if (work + plans <= left + c->budget / 8) return;
+  c->mem.trim(std::min(work, left / 2));
+  c->plan_mem.trim(left - std::min(work, left / 2));
 }
 
 // Idle memory back to the device under memory pressure (the serving loop calls
@@ -1510,12 +1511,13 @@ extern "C" pinv_status pinv_context_release_captures(pinv_context* c) {
   return PINV_OK;
 }
 
-pinv_status pinv_plan_wait(pinv_plan* p) {
-  if (!p) return fail(PINV_ERR_INVALID, "plan is NULL");
+// The outcome of a build, waited for; `plans`: under memory pressure released plans'
+// memory goes back to the device too.
+static pinv_status build_outcome(pinv_plan* p, bool plans) {
   if (!p->waited) {
     HIPCHK(enter_device(p->ctx->device));
     HIPCHK(hipEventSynchronize(p->ev[4]));
-    trim_memory(p->ctx, false, true);
+    trim_memory(p->ctx, false, plans);
     HIPCHK(hipMemcpy(&p->info_host, p->info, sizeof(int), hipMemcpyDeviceToHost));
     for (int i = 0; i < 4; ++i) HIPCHK(hipEventElapsedTime(&p->stage_ms[i], p->ev[i], p->ev[i + 1]));
     if (p->no_r) p->stage_ms[2] = p->stage_ms[3] = 0.f;   // no W or R was formed
@@ -1528,13 +1530,19 @@ pinv_status pinv_plan_wait(pinv_plan* p) {
   return p->status;
 }
 
+pinv_status pinv_plan_wait(pinv_plan* p) {
+  if (!p) return fail(PINV_ERR_INVALID, "plan is NULL");
+  return build_outcome(p, true);
+}
+
+// (The serving loop asks here: the plans that follow take released ones' memory.)
 pinv_status pinv_plan_query(pinv_plan* p) {
   if (!p) return fail(PINV_ERR_INVALID, "plan is NULL");
-  if (p->waited) return p->status == PINV_OK ? PINV_OK : pinv_plan_wait(p);
+  if (p->waited) return p->status == PINV_OK ? PINV_OK : build_outcome(p, false);
   hipError_t q = hipEventQuery(p->ev[4]);
   if (q == hipErrorNotReady) return PINV_ERR_BUSY;
   if (q != hipSuccess) return fail(PINV_ERR_DEVICE, std::string("hipEventQuery: ") + hipGetErrorString(q));
-  return pinv_plan_wait(p);
+  return build_outcome(p, false);
 }
 
 // Iterative refinement on the normal equations (Eq. 6) for one item:
