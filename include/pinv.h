@@ -294,12 +294,11 @@ pinv_status pinv_encoding_key(const pinv_encoding *e, const pinv_build_opts *o, 
  * differently.  The path and the split of the sum over M follow from F, N and
  * M alone, and a frame's result does not depend on the values of the other
  * frames.  A stream under graph capture records the apply; with refine_steps > 0
- * that is refused (replays of a recorded refinement have faulted; pinv_apply_noalloc
- * takes refine_steps there).  Scratch of a recorded apply is allocated for its
- * capture (up to 256 MB with many frames) and stays until
- * pinv_context_release_captures or the context's end, also after the graph is gone.
- * Errors: INVALID, NOMEM (scratch), UNSUPPORTED (a refined
- * apply under capture), DEVICE. */
+ * that is refused (replays of a recorded refinement have faulted).  Scratch of a
+ * recorded apply is allocated for its capture (up to 256 MB with many frames) and
+ * stays until pinv_context_release_captures or the context's end, also after the
+ * graph is gone.  Errors: INVALID, NOMEM (scratch), UNSUPPORTED (a refined apply
+ * under capture), DEVICE. */
 pinv_status pinv_apply(pinv_context *ctx, const pinv_plan *p, const void *data, int64_t F,
                        void *image, int32_t refine_steps, void *hip_stream);
 

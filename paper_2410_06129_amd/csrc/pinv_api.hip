@@ -1864,8 +1864,7 @@ pinv_status pinv_apply_grouped(pinv_context* c, int32_t n, const pinv_apply_item
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(enter_device(c->device));
   if (refine_steps > 0 && capturing(s))
-    return fail(PINV_ERR_UNSUPPORTED, "a refined apply cannot be recorded into a graph "
-                                      "(pinv_apply_noalloc can)");
+    return fail(PINV_ERR_UNSUPPORTED, "a refined apply cannot be recorded into a graph");
   Scratch sc;   // blocks of the context's memory
   sc.cache = &c->mem;
   sc.reclaim = reclaim_memory;
